@@ -75,7 +75,9 @@ typedef struct fftseg_plan *fft_plan_t;
 /* Build a plan for `batch` segments of `segment_len` samples in direction
  * FFT_FORWARD or FFT_INVERSE.  Factorises the length, picks the kernel (one
  * LDS-resident pass up to 16384 samples, a two-pass "four-step" split
- * N = N1*N2 above, a radix-by-radix fallback otherwise; a tuned choice
+ * N = N1*N2 above; lengths without compiled tiles run a radix schedule
+ * chosen here, in one pass where a segment fits a workgroup's LDS and in
+ * two otherwise; a tuned choice
  * first, and for a batch that would give the length's default one-pass
  * kernel fewer than two workgroups per CU, the length's small-batch
  * kernel where it has one), uploads the
@@ -105,7 +107,7 @@ fft_plan_t fft_plan_create(size_t segment_len, size_t batch, int direction);
  * N/2 complex values z[m] = x[2m] + i x[2m+1].  Where N/2 has a one-pass
  * kernel the split into even and odd parts is fused into its store
  * (forward) or load (inverse), so each byte crosses HBM once.  Other even
- * lengths run the N/2-point complex plan (two passes or radix stages) and
+ * lengths run the N/2-point complex plan (two passes or a radix schedule) and
  * the split as a separate pass through a buffer of up to 2 GiB of N/2-point
  * rows (plus that plan's own scratch; fft_plan_scratch_bytes reports both).
  * Streaming, frames, graph and work-list entry points take complex plans
@@ -137,8 +139,8 @@ int fft_exec_segments_n(fft_plan_t plan, const void *in, void *out,
  * device array of the library, 2^15 + 2^24 + 32 complex64 samples (about
  * 128 MiB) per GPU, allocated when the library's code first runs on that
  * GPU and held until the process ends.  Supported: every length of
- * fft_plan_create up to 2^23 (lengths without a two-pass split need two
- * buffers of N samples); 2^24 gives FFT_ERR_UNSUPPORTED_LENGTH.  Every call
+ * fft_plan_create up to 2^23 (the buffer between two passes may take up to
+ * 2N samples); longer ones, up to 2^24, give FFT_ERR_UNSUPPORTED_LENGTH.  Every call
  * on one GPU uses the same array: calls that overlap in time on one GPU
  * (other streams, other threads) race and give wrong results.  Asynchronous
  * on stream. */
@@ -158,7 +160,9 @@ const char *fft_last_error(void);
  * ------------------------------------------------------------------------ */
 
 /* Factorise n into the radices the planner would use for one pass of up to
- * 16384 samples (or for the fallback path).  Writes up to `max` radices to
+ * 16384 samples (for a length without compiled tiles, those of its run-time
+ * schedule, the column pass's before the row pass's; a radix-9 stage is
+ * listed as its two radix-3 steps).  Writes up to `max` radices to
  * `radices` and returns their count, or a negative fft_status_t. */
 int fft_plan_factorize(size_t n, int *radices, int max);
 
@@ -268,8 +272,9 @@ int fft_host_free(void *ptr);
  * FFT_ERR_INVALID_ARG.  Lengths with a one-pass kernel read the frames in
  * place (with the plan's own kernel variant when it has a frame form, else
  * the length's default frame kernel; overlapping frames are loaded through
- * the cache), two-pass lengths in their first pass; other lengths gather
- * the windowed frames into out first and transform out in place. */
+ * the cache), two-pass lengths in their first pass; length 1, and two-pass
+ * plans on a tile variant without a frame form, gather the windowed frames
+ * into out first and transform out in place. */
 int fft_exec_frames(fft_plan_t plan, const void *in, size_t in_len, void *out,
                     size_t n_frames, size_t hop, const float *window, void *stream);
 

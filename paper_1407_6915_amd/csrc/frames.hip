@@ -6,10 +6,11 @@
 // real window before its transform, i.e. a short-time Fourier transform.
 // Lengths with an LDS-resident kernel read the frames directly through a
 // strided gather in the kernel's first stage, and two-pass lengths through
-// the column loads of their first pass, so the overlapping input is read
-// once per frame and nothing is staged; the radix-stage lengths first
-// gather the windowed frames into the output buffer and transform it in
-// place.
+// the column loads of their first pass (the run-time schedules through
+// their first loads, the same way), so the overlapping input is read
+// once per frame and nothing is staged.  Length 1 and two-pass plans on a
+// tile variant without a frame form first gather the windowed frames into
+// the output buffer and transform it in place.
 #include <stdlib.h>
 
 #include "fftseg.h"
@@ -89,6 +90,16 @@ int frames_enqueue(Plan *p, const c32 *in, c32 *out, uint64_t frames, uint64_t h
         p->last_stream_valid = true;
         return set_ok();
     }
+    if (p->kind == Plan::GENERIC) {
+        const hipError_t e = stages_enqueue(p, in, out, frames, hop, window, s);
+        if (e != hipSuccess)
+            return hip_error(e, "frame kernel launch");
+        p->used = true;
+        p->last_stream = s;
+        p->last_stream_valid = true;
+        return set_ok();
+    }
+    // length 1, and two-pass plans on a tile variant without a frame form
     const uint64_t total = frames * n;
     const unsigned grid = (unsigned)std::min<uint64_t>((total + 255) / 256, 1u << 20);
     hipLaunchKernelGGL(frame_gather_kernel, dim3(grid), dim3(256), 0, s, in, out, n, frames,

@@ -1,5 +1,4 @@
-// Four-step pass kernels (column pass A, row pass B) and the global-memory
-// radix-stage fallback.
+// Four-step pass kernels (column pass A, row pass B).
 #include "fsinst.hpp"
 
 namespace fftseg {
@@ -114,21 +113,6 @@ const RowDesc kRows[] = {
     RowInst<2048, 128, 8, 4, kNoHoist | kShifted, 16, 16, 8>::desc(5),
 };
 
-template <int R>
-void launch_stage(int dir, const void *in, void *out, const void *tl, const void *th,
-                  int sh, uint64_t n, uint64_t l, uint64_t batch, unsigned grid,
-                  hipStream_t s)
-{
-    if (dir < 0)
-        hipLaunchKernelGGL((stockham_global_stage_kernel<R, -1>), dim3(grid), dim3(256),
-                           0, s, (const c32 *)in, (c32 *)out, (const c32 *)tl,
-                           (const c32 *)th, sh, n, l, batch);
-    else
-        hipLaunchKernelGGL((stockham_global_stage_kernel<R, 1>), dim3(grid), dim3(256),
-                           0, s, (const c32 *)in, (c32 *)out, (const c32 *)tl,
-                           (const c32 *)th, sh, n, l, batch);
-}
-
 }  // namespace
 
 const ColumnDesc *column_table(int *count)
@@ -141,31 +125,6 @@ const RowDesc *row_table(int *count)
 {
     *count = (int)(sizeof(kRows) / sizeof(kRows[0]));
     return kRows;
-}
-
-bool generic_radix_supported(int radix)
-{
-    switch (radix) {
-    case 2: case 3: case 4: case 5: case 8: case 16:
-        return true;
-    default:
-        return false;
-    }
-}
-
-void launch_generic_stage(int radix, int dir, const void *in, void *out, const void *tl,
-                          const void *th, int sh, uint64_t n, uint64_t l, uint64_t batch,
-                          unsigned grid, hipStream_t s)
-{
-    switch (radix) {
-    case 2: launch_stage<2>(dir, in, out, tl, th, sh, n, l, batch, grid, s); break;
-    case 3: launch_stage<3>(dir, in, out, tl, th, sh, n, l, batch, grid, s); break;
-    case 4: launch_stage<4>(dir, in, out, tl, th, sh, n, l, batch, grid, s); break;
-    case 5: launch_stage<5>(dir, in, out, tl, th, sh, n, l, batch, grid, s); break;
-    case 8: launch_stage<8>(dir, in, out, tl, th, sh, n, l, batch, grid, s); break;
-    case 16: launch_stage<16>(dir, in, out, tl, th, sh, n, l, batch, grid, s); break;
-    default: break;
-    }
 }
 
 }  // namespace fftseg

@@ -21,9 +21,10 @@ namespace {
 
 // tables: W_N (one pass) or W_N1, W_N2 and the two-level W_N (two passes)
 constexpr uint64_t kTableSamples = 1ull << 15;
-// Y: 2^24 samples plus two lines: one sub-batch of a two-pass length (up to
-// 2^22 points, so at least 4 segments), or the two buffers of the
-// radix-stage path (lengths up to 2^23; 2^24 is refused)
+// Y: 2^24 samples plus two lines: one sub-batch of a two-pass length with
+// compiled tiles (up to 2^22 points, so at least 4 segments), or of a
+// run-time schedule (lengths up to 2^23, at least one segment: its Y is less
+// than twice the segment)
 constexpr uint64_t kYSamples = (1ull << 24) + 2 * kLineSamples;
 constexpr uint64_t kScratchBytes = (kTableSamples + kYSamples) * sizeof(c32);
 
@@ -77,11 +78,24 @@ __device__ c32 device_root(uint64_t m, uint64_t n)
     return c32{(float)c, (float)(-s)};
 }
 
-// Up to four consecutive tables: table t holds count[t] entries
-// W_{mod[t]}^{j * step[t]}, j < count[t].
+// Consecutive tables: table t holds count[t] entries W_{mod[t]}^{j step[t]},
+// j < count[t], or, with rows of l[t] entries (the twiddles of one stage of
+// a run-time schedule), W_{mod[t]}^{(1 + j / l[t]) (j mod l[t])}.
+constexpr int kMaxTables = 2 + 2 * kMaxLdsStages;
 struct TableSet {
-    uint64_t count[4], mod[4], step[4];
+    uint64_t count[kMaxTables], mod[kMaxTables], step[kMaxTables], l[kMaxTables];
 };
+
+// the tables of a schedule's stages from table t on; returns the next table
+int add_schedule(TableSet &ts, int t, const LdsSched &s)
+{
+    for (int i = 1; i < s.ns; ++i, ++t) {
+        ts.l[t] = (uint64_t)s.st[i].l;
+        ts.count[t] = (uint64_t)(s.st[i].r - 1) * ts.l[t];
+        ts.mod[t] = (uint64_t)s.st[i].r * ts.l[t];
+    }
+    return t;
+}
 
 __global__ void __launch_bounds__(256) static_tables_kernel(c32 *tables, TableSet ts,
                                                             uint64_t total)
@@ -90,11 +104,12 @@ __global__ void __launch_bounds__(256) static_tables_kernel(c32 *tables, TableSe
          i += (uint64_t)gridDim.x * 256) {
         uint64_t j = i;
         int t = 0;
-        while (t < 3 && j >= ts.count[t]) {
+        while (t + 1 < kMaxTables && j >= ts.count[t]) {
             j -= ts.count[t];
             ++t;
         }
-        tables[i] = device_root(j * ts.step[t], ts.mod[t]);
+        const uint64_t l = ts.l[t];
+        tables[i] = device_root(l ? (1 + j / l) * (j % l) : j * ts.step[t], ts.mod[t]);
     }
 }
 
@@ -109,9 +124,9 @@ int noalloc_enqueue(uint64_t n, uint64_t batch, int dir, const void *in, void *o
         p.sub_batch = std::min<uint64_t>(batch, kYSamples / 2 / n);
     if (p.kind != Plan::COPY && p.kind != Plan::SINGLE && p.sub_batch == 0)
         return set_error(FFT_ERR_UNSUPPORTED_LENGTH,
-                         "length %llu runs radix stage by stage through two buffers of "
-                         "%llu samples; the static scratch holds %llu",
-                         (unsigned long long)n, (unsigned long long)n,
+                         "length %llu needs up to %llu samples of scratch; the static "
+                         "scratch holds %llu",
+                         (unsigned long long)n, (unsigned long long)(2 * n),
                          (unsigned long long)kYSamples);
     TableSet ts{};
     uint64_t total = 0;
@@ -122,19 +137,25 @@ int noalloc_enqueue(uint64_t n, uint64_t batch, int dir, const void *in, void *o
         break;
     case Plan::FOURSTEP:
     case Plan::GENERIC: {
+        if (p.kind == Plan::GENERIC && p.stages.passes == 1) {
+            add_schedule(ts, 0, p.stages.a);
+            break;
+        }
         const uint64_t lo = 1ull << p.sh;
         ts.count[0] = lo; ts.mod[0] = n; ts.step[0] = 1;                  // tl
         ts.count[1] = (n + lo - 1) / lo; ts.mod[1] = n; ts.step[1] = lo;  // th
         if (p.kind == Plan::FOURSTEP) {
             ts.count[2] = p.n1; ts.mod[2] = p.n1; ts.step[2] = 1;         // W_N1
             ts.count[3] = p.n2; ts.mod[3] = p.n2; ts.step[3] = 1;         // W_N2
+        } else {
+            add_schedule(ts, add_schedule(ts, 2, p.stages.a), p.stages.b);
         }
         break;
     }
     default:
         return set_error(FFT_ERR_INVALID_ARG, "real plans are not served here");
     }
-    for (int t = 0; t < 4; ++t)
+    for (int t = 0; t < kMaxTables; ++t)
         total += ts.count[t];
     if (total > kTableSamples)
         return set_error(FFT_ERR_UNSUPPORTED_LENGTH,
@@ -160,8 +181,14 @@ int noalloc_enqueue(uint64_t n, uint64_t batch, int dir, const void *in, void *o
         p.scratch = y;
         break;
     case Plan::GENERIC:
+        if (p.stages.passes == 1) {
+            p.tw = tables;
+            break;
+        }
         p.tl = tables;
         p.th = tables + ts.count[0];
+        p.tw = tables + ts.count[0] + ts.count[1];
+        p.tw2 = (c32 *)p.tw + lds_table_size(p.stages.a);
         p.scratch = y;
         break;
     default: break;

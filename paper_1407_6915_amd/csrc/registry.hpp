@@ -130,10 +130,4 @@ RowDesc radix32_row_desc(int config, int variant);
 const ColumnDesc *column_table(int *count);
 const RowDesc *row_table(int *count);
 
-// Fallback radix stage over global memory (radix in {2,3,4,5,8,16}).
-bool generic_radix_supported(int radix);
-void launch_generic_stage(int radix, int dir, const void *in, void *out,
-                          const void *tl, const void *th, int sh, uint64_t n,
-                          uint64_t l, uint64_t batch, unsigned grid, hipStream_t s);
-
 }  // namespace fftseg

@@ -74,15 +74,18 @@ c32 root_forward(uint64_t m, uint64_t n)
     return c32{(float)c, (float)(-s)};
 }
 
-namespace {
-
 std::vector<c32> root_table(uint64_t n)
 {
+    // the upper half is the lower half's conjugates
     std::vector<c32> t(n);
-    for (uint64_t m = 0; m < n; ++m)
+    for (uint64_t m = 0; m <= n / 2; ++m)
         t[m] = root_forward(m, n);
+    for (uint64_t m = n / 2 + 1; m < n; ++m)
+        t[m] = c32{t[n - m].x, -t[n - m].y};
     return t;
 }
+
+namespace {
 
 int ilog2_ceil(uint64_t v)
 {
@@ -104,7 +107,7 @@ bool smooth235(uint64_t n)
     return n == 1;
 }
 
-// greedy radix list for the global-memory fallback
+// greedy radix list of a two-pass length as a whole (fft_plan_factorize)
 std::vector<int> generic_radices(uint64_t n)
 {
     std::vector<int> r;
@@ -117,20 +120,42 @@ std::vector<int> generic_radices(uint64_t n)
     return r;
 }
 
-hipError_t upload(const std::vector<c32> &h, void **d)
+// The plan's tables in one allocation (p->tables), each from a 256-byte
+// boundary on, uploaded in one copy; `dev` receives the table's address.
+struct HostTable {
+    const std::vector<c32> &host;
+    void **dev;
+};
+
+int upload_tables(Plan *p, std::initializer_list<HostTable> set)
 {
-    *d = nullptr;
-    hipError_t e = hipMalloc(d, h.size() * sizeof(c32));
+    constexpr size_t kAlign = 256 / sizeof(c32);
+    std::vector<c32> all;
+    size_t total = 0;
+    for (const HostTable &t : set)
+        total += (t.host.size() + kAlign - 1) / kAlign * kAlign;
+    hipError_t e = hipMalloc(&p->tables, total * sizeof(c32));
     if (e != hipSuccess) {
-        *d = nullptr;
-        return e;
+        p->tables = nullptr;
+        (void)hipGetLastError();
+        return e == hipErrorOutOfMemory ? set_error(FFT_ERR_OUT_OF_MEMORY, "twiddles")
+                                        : hip_error(e, "twiddle upload");
     }
-    e = hipMemcpy(*d, h.data(), h.size() * sizeof(c32), hipMemcpyHostToDevice);
-    if (e != hipSuccess) {
-        (void)hipFree(*d);
-        *d = nullptr;
+    if (set.size() > 1)
+        all.reserve(total);
+    size_t at = 0;
+    for (const HostTable &t : set) {
+        *t.dev = (c32 *)p->tables + at;
+        at += (t.host.size() + kAlign - 1) / kAlign * kAlign;
+        if (set.size() > 1) {
+            all.insert(all.end(), t.host.begin(), t.host.end());
+            all.resize(at);
+        }
     }
-    return e;
+    const std::vector<c32> &src = set.size() > 1 ? all : set.begin()->host;
+    e = hipMemcpy(p->tables, src.data(), src.size() * sizeof(c32), hipMemcpyHostToDevice);
+    // (on failure plan_free releases the allocation)
+    return e == hipSuccess ? set_ok() : hip_error(e, "twiddle upload");
 }
 
 // the tuning table: preferred single-pass variant and grid per length
@@ -533,9 +558,17 @@ int plan_choose(Plan *p, uint64_t n, uint64_t batch, int dir, int forced_variant
         p->scratch_bytes = (p->sub_batch * n + kLineSamples) * sizeof(c32);
     } else {
         p->kind = Plan::GENERIC;
-        p->radices = generic_radices(n);
+        if (!stages_choose(n, batch, device_cus(p->device), &p->stages))
+            return set_error(FFT_ERR_UNSUPPORTED_LENGTH, "no schedule for length %llu",
+                             (unsigned long long)n);
         p->sub_batch = std::min<uint64_t>(batch, max_sub_samples / n);
-        p->scratch_bytes = 2 * p->sub_batch * n * sizeof(c32);
+        if (p->stages.passes == 2) {
+            // Y pads the last row tile of a segment
+            if (p->sub_batch > 1)
+                p->sub_batch = std::max<uint64_t>(
+                    1, std::min(p->sub_batch, max_sub_samples / p->stages.y_samples));
+            p->scratch_bytes = p->sub_batch * p->stages.y_samples * sizeof(c32);
+        }
     }
     if (p->sub_batch == 0)
         return set_error(FFT_ERR_INVALID_ARG,
@@ -556,30 +589,23 @@ int plan_build(Plan *p, uint64_t n, uint64_t batch, int dir, int forced_variant,
                          max_sub);
     if (st != FFT_OK || p->kind == Plan::COPY)
         return st;
-    hipError_t e;
-    if (p->kind == Plan::SINGLE) {
-        if ((e = upload(root_table(n), &p->tw)) != hipSuccess)
-            return e == hipErrorOutOfMemory ? set_error(FFT_ERR_OUT_OF_MEMORY, "twiddles")
-                                            : hip_error(e, "twiddle upload");
-        return set_ok();
-    }
-    {
-        const uint64_t lo = 1ull << p->sh;
-        std::vector<c32> tl(lo), th((n + lo - 1) / lo);
-        for (uint64_t j = 0; j < lo; ++j)
-            tl[j] = root_forward(j, n);
-        for (uint64_t j = 0; j < th.size(); ++j)
-            th[j] = root_forward(j * lo, n);
-        if ((e = upload(tl, &p->tl)) != hipSuccess || (e = upload(th, &p->th)) != hipSuccess)
-            return e == hipErrorOutOfMemory ? set_error(FFT_ERR_OUT_OF_MEMORY, "twiddles")
-                                            : hip_error(e, "twiddle upload");
-    }
-    if (p->kind == Plan::FOURSTEP &&
-        ((e = upload(root_table(p->n1), &p->tw)) != hipSuccess ||
-         (e = upload(root_table(p->n2), &p->tw2)) != hipSuccess))
-        return e == hipErrorOutOfMemory ? set_error(FFT_ERR_OUT_OF_MEMORY, "twiddles")
-                                        : hip_error(e, "twiddle upload");
-    e = hipMalloc(&p->scratch, p->scratch_bytes);
+    const bool four = p->kind == Plan::FOURSTEP;
+    if (p->kind == Plan::SINGLE)
+        return upload_tables(p, {{root_table(n), &p->tw}});
+    if (!four && p->stages.passes == 1)
+        return upload_tables(p, {{lds_table(p->stages.a), &p->tw}});
+    const uint64_t lo = 1ull << p->sh;
+    std::vector<c32> tl(lo), th((n + lo - 1) / lo);
+    for (uint64_t j = 0; j < lo; ++j)
+        tl[j] = root_forward(j, n);
+    for (uint64_t j = 0; j < th.size(); ++j)
+        th[j] = root_forward(j * lo, n);
+    if (upload_tables(p, {{four ? root_table(p->n1) : lds_table(p->stages.a), &p->tw},
+                          {four ? root_table(p->n2) : lds_table(p->stages.b), &p->tw2},
+                          {tl, &p->tl},
+                          {th, &p->th}}) != FFT_OK)
+        return last_status();
+    hipError_t e = hipMalloc(&p->scratch, p->scratch_bytes);
     if (e != hipSuccess) {
         p->scratch = nullptr;
         (void)hipGetLastError();
@@ -601,17 +627,12 @@ int plan_build_real(Plan *p, uint64_t n, uint64_t batch, int dir)
     std::vector<c32> hw(m + 1);
     for (uint64_t k = 0; k <= m; ++k)
         hw[k] = root_forward(k, n);
-    hipError_t e;
     p->sp = find_aux(m);
     if (p->sp && p->sp->launch_real) {
         // the split fused into the m-point one-pass kernel
         p->kind = Plan::REAL;
         p->grid_mult = p->sp->grid_mult;
-        if ((e = upload(root_table(m), &p->tw)) != hipSuccess ||
-            (e = upload(hw, &p->tw2)) != hipSuccess)
-            return e == hipErrorOutOfMemory ? set_error(FFT_ERR_OUT_OF_MEMORY, "twiddles")
-                                            : hip_error(e, "twiddle upload");
-        return set_ok();
+        return upload_tables(p, {{root_table(m), &p->tw}, {hw, &p->tw2}});
     }
     // the m-point complex plan over sub-batches, the split as its own pass
     p->sp = nullptr;
@@ -621,11 +642,10 @@ int plan_build_real(Plan *p, uint64_t n, uint64_t batch, int dir)
     p->inner = new Plan();
     if (plan_build(p->inner, m, p->sub_batch, dir, -1) != FFT_OK)
         return last_status();
-    if ((e = upload(hw, &p->tw2)) != hipSuccess)
-        return e == hipErrorOutOfMemory ? set_error(FFT_ERR_OUT_OF_MEMORY, "twiddles")
-                                        : hip_error(e, "twiddle upload");
+    if (upload_tables(p, {{hw, &p->tw2}}) != FFT_OK)
+        return last_status();
     const size_t zb = p->sub_batch * m * sizeof(c32);
-    if ((e = hipMalloc(&p->zbuf, zb)) != hipSuccess) {
+    if (hipMalloc(&p->zbuf, zb) != hipSuccess) {
         p->zbuf = nullptr;
         (void)hipGetLastError();
         return set_error(FFT_ERR_OUT_OF_MEMORY, "split buffer of %zu bytes", zb);
@@ -646,7 +666,7 @@ void plan_free(Plan *p)
 {
     if (p->used && p->last_stream_valid)
         (void)hipStreamSynchronize(p->last_stream);
-    for (void *q : {p->tw, p->tw2, p->tl, p->th, p->scratch, p->zbuf})
+    for (void *q : {p->tables, p->scratch, p->zbuf})
         if (q)
             (void)hipFree(q);
     if (p->inner) {
@@ -664,7 +684,7 @@ void plan_free(Plan *p)
     p->graph_exec = nullptr;
     p->graph = nullptr;
     p->capture_stream = nullptr;
-    p->tw = p->tw2 = p->tl = p->th = p->scratch = p->zbuf = nullptr;
+    p->tables = p->tw = p->tw2 = p->tl = p->th = p->scratch = p->zbuf = nullptr;
 }
 
 // ---------------------------------------------------------------------------
@@ -760,6 +780,23 @@ int identity_copy(const void *in, void *out, uint64_t n, hipStream_t s)
                        (const T *)in, (T *)out, n);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? FFT_OK : hip_error(e, "identity copy");
+}
+
+// GENERIC plans: segment s starts at in + s * hop, times window (or null)
+hipError_t stages_enqueue(const Plan *p, const void *in, void *out, uint64_t batch, uint64_t hop,
+                          const float *window, hipStream_t s)
+{
+    if (p->stages.passes == 1)
+        return stages_one_pass(p->stages, p->dir, in, out, p->tw, batch, hop, window, s);
+    for (uint64_t s0 = 0; s0 < batch; s0 += p->sub_batch) {
+        const hipError_t e = stages_two_pass(
+            p->stages, p->dir, (const c32 *)in + s0 * hop, (c32 *)out + s0 * p->n, p->scratch,
+            p->tw, p->tw2, p->tl, p->th, p->sh, std::min(p->sub_batch, batch - s0), hop, window,
+            s);
+        if (e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
 }
 
 // enqueue the transform of `batch` segments (arguments already checked)
@@ -884,32 +921,9 @@ int plan_enqueue(Plan *p, const void *in, void *out, uint64_t batch, hipStream_t
         break;
     }
     case Plan::GENERIC: {
-        const int ns = (int)p->radices.size();
-        c32 *bufs[2] = {(c32 *)p->scratch, (c32 *)p->scratch + p->sub_batch * n};
-        for (uint64_t s0 = 0; s0 < batch; s0 += p->sub_batch) {
-            const uint64_t sb = std::min(p->sub_batch, batch - s0);
-            const c32 *x = (const c32 *)in + s0 * n;
-            c32 *y = (c32 *)out + s0 * n;
-            const uint64_t threads_total = sb * n;
-            uint64_t l = 1;
-            for (int i = 0; i < ns; ++i) {
-                const int r = p->radices[i];
-                const void *src = i == 0 ? (const void *)x : (const void *)bufs[(i - 1) & 1];
-                void *dst = (i == ns - 1 && !(ns == 1 && in == out)) ? (void *)y
-                                                                     : (void *)bufs[i & 1];
-                const uint64_t work = threads_total / r;
-                const unsigned grid =
-                    (unsigned)std::min<uint64_t>((work + 255) / 256, 1ull << 20);
-                launch_generic_stage(r, dir, src, dst, p->tl, p->th, p->sh, n, l, sb, grid, s);
-                l *= (uint64_t)r;
-            }
-            if (ns == 1 && in == out) {
-                hipError_t e = hipMemcpyAsync(y, bufs[0], sb * n * sizeof(c32),
-                                              hipMemcpyDeviceToDevice, s);
-                if (e != hipSuccess)
-                    return hip_error(e, "fallback copy");
-            }
-        }
+        const hipError_t e = stages_enqueue(p, in, out, batch, n, nullptr, s);
+        if (e != hipSuccess)
+            return hip_error(e, "radix-stage launch");
         break;
     }
     }
@@ -984,14 +998,25 @@ int plan_describe(const Plan *p, std::string &js)
              ",\"complex_plan\":" + inner + "}";
         return FFT_OK;
     }
-    case Plan::GENERIC:
+    case Plan::GENERIC: {
+        std::vector<int> r;
+        const StagesPlan &g = p->stages;
+        lds_radices(g.a, &r);
+        if (g.passes == 2)
+            lds_radices(g.b, &r);
         snprintf(buf, sizeof buf,
                  "{\"kind\":\"radix_stages\",\"n\":%llu,\"batch\":%llu,\"direction\":%d,"
-                 "\"radices\":%s,\"sub_batch\":%llu,\"scratch_bytes\":%zu}",
+                 "\"radices\":%s,\"passes\":%d,\"n1\":%d,\"n2\":%d,"
+                 "\"segments_per_workgroup\":%d,\"columns_per_workgroup\":%d,"
+                 "\"rows_per_workgroup\":%d,\"threads\":[%d,%d],\"sub_batch\":%llu,"
+                 "\"scratch_bytes\":%zu}",
                  (unsigned long long)p->n, (unsigned long long)p->batch, p->dir,
-                 rad(p->radices.data(), (int)p->radices.size()).c_str(),
+                 rad(r.data(), (int)r.size()).c_str(), g.passes, g.a.n, g.passes == 2 ? g.b.n : 1,
+                 g.passes == 1 ? g.segs : 0, g.passes == 2 ? 1 << g.lc : 0,
+                 g.passes == 2 ? 1 << g.lr : 0, g.threads_a, g.threads_b,
                  (unsigned long long)p->sub_batch, p->scratch_bytes);
         break;
+    }
     }
     js = buf;
     return FFT_OK;
@@ -1029,10 +1054,18 @@ int factorize(uint64_t n, int *radices, int max)
     const SinglePassDesc *d = find_single(n, v < 0 ? 0 : v);
     if (!d)
         d = find_single(n, 0);
-    if (d)
+    const ColumnDesc *cd = nullptr;
+    const RowDesc *rd = nullptr;
+    StagesPlan g;
+    if (d) {
         r.assign(d->radices, d->radices + d->nrad);
-    else
+    } else if (n > 1 && !find_split(n, &cd, &rd, 0, 0) && stages_choose(n, 1, 1, &g)) {
+        lds_radices(g.a, &r);
+        if (g.passes == 2)
+            lds_radices(g.b, &r);
+    } else {
         r = generic_radices(n);
+    }
     if (!radices && max != 0)
         return set_error(FFT_ERR_INVALID_ARG, "radices is NULL");
     for (int i = 0; i < (int)r.size() && i < max; ++i)

@@ -10,6 +10,7 @@
 
 #include "radix.hpp"
 #include "registry.hpp"
+#include "stages.hpp"
 
 namespace fftseg {
 
@@ -23,9 +24,12 @@ struct Plan {
     const ColumnDesc *col = nullptr;
     const RowDesc *row = nullptr;
     uint64_t n1 = 0, n2 = 0;
-    std::vector<int> radices;   // fallback path
-    void *tw = nullptr;         // W_N (single pass) or W_N1 (four-step) table
-    void *tw2 = nullptr;        // W_N2 table (four-step); W_N^k, k <= N/2 (real)
+    StagesPlan stages;          // GENERIC: run-time radix schedules
+    void *tables = nullptr;     // the allocation that holds the tables below
+    void *tw = nullptr;         // W_N (single pass) or W_N1 (four-step) table;
+                                // GENERIC: the first schedule's table
+    void *tw2 = nullptr;        // W_N2 table (four-step); W_N^k, k <= N/2 (real);
+                                // GENERIC: the row schedule's table
     void *tl = nullptr, *th = nullptr;  // two-level W_N table
     int sh = 0;
     void *scratch = nullptr;
@@ -58,6 +62,8 @@ int last_status();
 const char *last_message();
 
 c32 root_forward(uint64_t m, uint64_t n);
+// W_n^m, m < n
+std::vector<c32> root_table(uint64_t n);
 const SinglePassDesc *find_single(uint64_t n, int variant);
 const SinglePassDesc *find_aux(uint64_t n);
 // the length's default frame kernel: the first row of n with one
@@ -86,11 +92,14 @@ int plan_build(Plan *p, uint64_t n, uint64_t batch, int dir, int forced_variant,
                int forced_split_variants = -1, uint64_t forced_n1 = 0);
 // the kernels, split and sub-batch of a plan (host only: no device memory);
 // a sub-batch fills at most max_sub_samples samples of each scratch buffer
-// (two-pass plans have one, the radix-stage path two)
+// (two-pass plans have one)
 int plan_choose(Plan *p, uint64_t n, uint64_t batch, int dir, int forced_variant,
                 int forced_split_variants, uint64_t forced_n1, uint64_t max_sub_samples);
 void plan_free(Plan *p);
 int plan_enqueue(Plan *p, const void *in, void *out, uint64_t batch, hipStream_t s);
+// GENERIC plans: segment s starts at in + s * hop, times window (or null)
+hipError_t stages_enqueue(const Plan *p, const void *in, void *out, uint64_t batch, uint64_t hop,
+                          const float *window, hipStream_t s);
 // real-input plans: length n = 2m through the m-point one-pass kernel, or,
 // where m has none, through the m-point complex plan and a separate split pass
 int plan_build_real(Plan *p, uint64_t n, uint64_t batch, int dir);

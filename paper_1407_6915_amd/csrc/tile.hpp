@@ -1480,44 +1480,4 @@ __global__ void __launch_bounds__(Pol::kThreads) __attribute__((amdgpu_waves_per
     }
 }
 
-// ---------------------------------------------------------------------------
-// Fallback for lengths without a compiled tile: one launch per Stockham
-// stage over global memory, one thread per butterfly, radix R at run-time
-// stride L.  Twiddle W_N^m = th[m >> sh] * tl[m & mask] as in pass A.
-template <int R, int D>
-__global__ void __launch_bounds__(256)
-    stockham_global_stage_kernel(const c32 *in, c32 *out, const c32 *__restrict__ tl,
-                                 const c32 *__restrict__ th, int sh,
-                                 uint64_t n, uint64_t l, uint64_t batch)
-{
-    const uint64_t nb = n / R;
-    const uint64_t total = nb * batch;
-    const uint64_t tw_stride = n / (l * R);
-    const unsigned mask = (1u << sh) - 1u;
-    for (uint64_t gid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; gid < total;
-         gid += (uint64_t)gridDim.x * blockDim.x) {
-        const uint64_t seg = gid / nb;
-        const uint64_t b = gid - seg * nb;
-        const c32 *x = in + seg * n;
-        c32 *y = out + seg * n;
-        c32 v[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-            v[r] = x[b + r * nb];
-        const uint64_t k = b % l;
-        if (l > 1) {
-#pragma unroll
-            for (int r = 1; r < R; ++r) {
-                const unsigned m = (unsigned)(r * k * tw_stride);
-                v[r] = twiddle<D>(v[r], cmul(th[m >> sh], tl[m & mask]));
-            }
-        }
-        dft<R, D>(v);
-        const uint64_t base = (b / l) * (l * R) + k;
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-            y[base + r * l] = v[r];
-    }
-}
-
 }  // namespace fftseg

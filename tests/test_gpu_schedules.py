@@ -1,0 +1,70 @@
+"""Lengths without compiled tiles: run-time radix schedules, in one pass
+(whole segments in LDS) or two (columns, rows), against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1407_6915_amd as fs
+
+from gpu_helpers import announce, check, noise, run
+
+pytestmark = pytest.mark.gpu
+
+# (length, batch, passes): the shortest; one stage; copied through LDS (below
+# 256 points) and not; ragged last workgroups; the longest in one pass; the
+# shortest in two; odd lengths (partial lines everywhere); tiles narrower
+# than 16 columns or rows
+CASES = [(3, 5000, 1), (25, 700, 1), (243, 1000, 1), (250, 1000, 1), (270, 1000, 1),
+         (360, 4099, 1), (2187, 301, 1), (3000, 700, 1), (12288, 5, 1), (15625, 3, 1),
+         (19200, 3, 1), (18432, 3, 2), (19683, 40, 2), (78125, 5, 2), (48000, 40, 2),
+         (3 << 20, 1, 2), (1953125, 1, 2), (15625000, 1, 2), (14348907, 1, 2)]
+
+
+@pytest.mark.parametrize("n,batch,passes", CASES)
+def test_schedules_match_oracle(n, batch, passes):
+    announce("schedule n=%d batch=%d" % (n, batch))
+    with fs.Plan(n, batch) as p:
+        d = p.describe()
+        assert d["kind"] == "radix_stages" and d["passes"] == passes, d
+        assert int(np.prod(d["radices"], dtype=np.int64)) == n
+    x = noise(n, batch, seed=n % 9973)
+    for dr in (fs.FORWARD, fs.INVERSE):
+        check(n, run(n, x, dr, inplace=dr > 0), x, dr)
+
+
+@pytest.mark.parametrize("n,hop,frames", [(100, 33, 2000), (360, 90, 500), (15000, 7500, 7),
+                                          (48000, 60001, 3), (78125, 20000, 5)])
+@pytest.mark.parametrize("windowed", [True, False])
+def test_schedule_frames_match_oracle(n, hop, frames, windowed):
+    """Overlapping (and, for 48000, gapped) frames read in place by the
+    schedules' first loads."""
+    import torch
+    announce("schedule frames n=%d hop=%d frames=%d" % (n, hop, frames))
+    x = noise((frames - 1) * hop + n, 1, seed=n + hop)[0]
+    w = np.hanning(n).astype(np.float32) if windowed else None
+    with fs.Plan(n, frames) as p:
+        y = p.exec_frames(torch.from_numpy(x).cuda(), hop,
+                          window=None if w is None else torch.from_numpy(w).cuda())
+        got = y.cpu().numpy().reshape(frames, n)
+    ref = np.stack([x[s * hop:s * hop + n] for s in range(frames)]).astype(np.complex128)
+    if windowed:
+        ref = ref * w.astype(np.float64)
+    assert np.all(oracle.rel_l2(got, oracle.fft_recursive(ref, n)) <= oracle.tolerance(n))
+
+
+def test_schedules_across_sub_batches(monkeypatch):
+    """Two-pass schedules whose batch runs as several sub-batches through
+    one Y buffer, a ragged last one, with and without frames."""
+    import torch
+    n, b, sub = 48000, 7, 2
+    announce("schedule sub-batches n=%d" % n)
+    monkeypatch.setenv("FFTSEG_SUB_SAMPLES", str(sub * n))
+    x = noise(n, b, seed=77)
+    with fs.Plan(n, b) as p:
+        assert p.describe()["sub_batch"] == sub
+        y = p.exec(torch.from_numpy(x.reshape(-1)).cuda()).cpu().numpy().reshape(b, n)
+        z = p.exec_frames(torch.from_numpy(x.reshape(-1)).cuda(), n // 2, n_frames=b)
+        z = z.cpu().numpy().reshape(b, n)
+    check(n, y, x)
+    f = x.reshape(-1)
+    check(n, z, np.stack([f[s * n // 2:s * n // 2 + n] for s in range(b)]))
