@@ -28,8 +28,9 @@ struct LdsSched {
     LdsStage st[kMaxLdsStages];
 };
 
-// Butterflies of one stage that a thread may own: `natural` keeps it near 16
-// values, `most` is what the kernels are compiled for.
+// Butterflies of one stage that a thread may own.  `most`: in the kernels
+// for tiles that 1024 threads hold only so; the others keep to the smaller
+// count, near 16 values, and to fewer registers.
 constexpr int lds_units(int r, bool most)
 {
     switch (r) {
@@ -45,12 +46,15 @@ constexpr int lds_units(int r, bool most)
 }
 
 // The schedule of an n-point transform (n >= 2, prime factors 2, 3, 5);
-// false if it would take more than kMaxLdsStages stages.
-bool lds_schedule(int n, LdsSched *s);
+// false if it would take more than kMaxLdsStages stages.  group > 1: the
+// last stage's lanes take butterflies in groups of `group` (column pass), so
+// the last radix is the one that fills them best.
+bool lds_schedule(int n, LdsSched *s, int group = 1);
 // Threads of a workgroup whose tile holds `tiles` transforms of the
 // schedule (the last stage's butterflies of each in groups of `group`);
-// 0 if 1024 threads cannot hold it.
-int lds_threads(const LdsSched &s, int tiles, int group);
+// 0 if 1024 threads cannot hold it.  *most: it needs the kernels compiled
+// for lds_units(r, true).
+int lds_threads(const LdsSched &s, int tiles, int group, bool *most);
 // entries of the schedule's twiddle table (s.n - first radix)
 int lds_table_size(const LdsSched &s);
 std::vector<c32> lds_table(const LdsSched &s);
@@ -63,9 +67,9 @@ struct StagesPlan {
     int passes = 0;          // 1: whole segments in LDS; 2: columns, then rows
     LdsSched a{}, b{};       // the pass (or column pass), the row pass
     int segs = 1;            // one pass: segments per workgroup
-    int staged = 0;          // one pass: segments copied through LDS on both sides
     int lc = 0, lr = 0;      // two passes: log2 of the columns / rows per workgroup
     int threads_a = 0, threads_b = 0;
+    bool most_a = false, most_b = false;  // see lds_threads
     uint64_t y_samples = 0;  // two passes: samples of Y per segment
 };
 // false if the length has no plan (none of the supported lengths)
