@@ -107,9 +107,10 @@ fft_plan_t fft_plan_create(size_t segment_len, size_t batch, int direction);
  * N/2 complex values z[m] = x[2m] + i x[2m+1].  Where N/2 has a one-pass
  * kernel the split into even and odd parts is fused into its store
  * (forward) or load (inverse), so each byte crosses HBM once.  Other even
- * lengths run the N/2-point complex plan (two passes or a radix schedule) and
- * the split as a separate pass through a buffer of up to 2 GiB of N/2-point
- * rows (plus that plan's own scratch; fft_plan_scratch_bytes reports both).
+ * lengths run a radix schedule of N/2 points in one pass, with the split in
+ * the same kernel, or in two, with the split in the pass at the spectra's
+ * side, through a buffer of up to 2 GiB of N/2-point rows and their padding
+ * (fft_plan_scratch_bytes reports it).
  * Streaming, frames, graph and work-list entry points take complex plans
  * only. */
 fft_plan_t fft_plan_create_real(size_t segment_len, size_t batch, int direction);

@@ -56,14 +56,16 @@ c32 root_forward(uint64_t m, uint64_t n)
     m %= n;
     // angle 2 pi m / n = (pi/4) (o + r/n) with 8m = o*n + r; quadrant
     // j = floor((o + 1) / 2) and x = (pi/4) (o - 2j + r/n) in [-pi/4, pi/4)
-    const unsigned __int128 m8 = (unsigned __int128)m * 8u;
-    const uint64_t o = (uint64_t)(m8 / n);
-    const uint64_t r = (uint64_t)(m8 - (unsigned __int128)o * n);
+    // (n <= 2^24: 8 m fits)
+    const uint64_t m8 = m * 8u;
+    const uint64_t o = m8 / n;
+    const uint64_t r = m8 - o * n;
     const uint64_t j = (o + 1) / 2;
     const double quarter_pi = 0.78539816339744830961566084581987572;
     const double x = ((double)((long long)o - 2 * (long long)j) + (double)r / (double)n) *
                      quarter_pi;
-    const double cx = std::cos(x), sx = std::sin(x);
+    double cx, sx;
+    sincos(x, &sx, &cx);
     double c, s;
     switch (j & 3) {
     case 0: c = cx; s = sx; break;
@@ -93,6 +95,27 @@ int ilog2_ceil(uint64_t v)
     while ((1ull << k) < v)
         ++k;
     return k;
+}
+
+// the two-level table of W_n: low entries W_n^j, j < 2^sh, and high ones
+// W_n^{j 2^sh}
+int two_level_shift(uint64_t n) { return ilog2_ceil(n) / 2 + (ilog2_ceil(n) & 1); }
+
+std::vector<c32> two_level_low(uint64_t n, int *sh)
+{
+    *sh = two_level_shift(n);
+    std::vector<c32> t((size_t)1 << *sh);
+    for (uint64_t j = 0; j < t.size(); ++j)
+        t[j] = root_forward(j, n);
+    return t;
+}
+
+std::vector<c32> two_level_high(uint64_t n, int sh)
+{
+    std::vector<c32> t((n + (1ull << sh) - 1) >> sh);
+    for (uint64_t j = 0; j < t.size(); ++j)
+        t[j] = root_forward(j << sh, n);
+    return t;
 }
 
 bool is_pow2(uint64_t v) { return v && !(v & (v - 1)); }
@@ -525,7 +548,7 @@ int plan_choose(Plan *p, uint64_t n, uint64_t batch, int dir, int forced_variant
             p->grid_mult = tuned_grid_mult(n, p->sp->variant, p->sp->grid_mult);
         return set_ok();
     }
-    p->sh = ilog2_ceil(n) / 2 + (ilog2_ceil(n) & 1);
+    p->sh = two_level_shift(n);
     int cv = 0, rv = 0;
     uint64_t n1 = forced_n1;
     if (forced_split_variants >= 0) {
@@ -577,16 +600,21 @@ int plan_choose(Plan *p, uint64_t n, uint64_t batch, int dir, int forced_variant
     return set_ok();
 }
 
-int plan_build(Plan *p, uint64_t n, uint64_t batch, int dir, int forced_variant,
-               int forced_split_variants, uint64_t forced_n1)
+// 4 GiB of complex64 per scratch buffer; FFTSEG_SUB_SAMPLES caps a
+// sub-batch at fewer samples
+static uint64_t max_scratch_samples()
 {
-    // 4 GiB of complex64 per scratch buffer (the radix-stage path has two);
-    // FFTSEG_SUB_SAMPLES caps a sub-batch at fewer samples
     uint64_t max_sub = 1ull << 29;
     if (const char *e = getenv("FFTSEG_SUB_SAMPLES"))
         max_sub = std::max<uint64_t>(1, std::min<uint64_t>(max_sub, strtoull(e, nullptr, 10)));
+    return max_sub;
+}
+
+int plan_build(Plan *p, uint64_t n, uint64_t batch, int dir, int forced_variant,
+               int forced_split_variants, uint64_t forced_n1)
+{
     int st = plan_choose(p, n, batch, dir, forced_variant, forced_split_variants, forced_n1,
-                         max_sub);
+                         max_scratch_samples());
     if (st != FFT_OK || p->kind == Plan::COPY)
         return st;
     const bool four = p->kind == Plan::FOURSTEP;
@@ -594,12 +622,7 @@ int plan_build(Plan *p, uint64_t n, uint64_t batch, int dir, int forced_variant,
         return upload_tables(p, {{root_table(n), &p->tw}});
     if (!four && p->stages.passes == 1)
         return upload_tables(p, {{lds_table(p->stages.a), &p->tw}});
-    const uint64_t lo = 1ull << p->sh;
-    std::vector<c32> tl(lo), th((n + lo - 1) / lo);
-    for (uint64_t j = 0; j < lo; ++j)
-        tl[j] = root_forward(j, n);
-    for (uint64_t j = 0; j < th.size(); ++j)
-        th[j] = root_forward(j * lo, n);
+    const std::vector<c32> tl = two_level_low(n, &p->sh), th = two_level_high(n, p->sh);
     if (upload_tables(p, {{four ? root_table(p->n1) : lds_table(p->stages.a), &p->tw},
                           {four ? root_table(p->n2) : lds_table(p->stages.b), &p->tw2},
                           {tl, &p->tl},
@@ -624,33 +647,52 @@ int plan_build_real(Plan *p, uint64_t n, uint64_t batch, int dir)
         return set_error(FFT_ERR_HIP, "no HIP device available");
     }
     const uint64_t m = n / 2;
-    std::vector<c32> hw(m + 1);
-    for (uint64_t k = 0; k <= m; ++k)
-        hw[k] = root_forward(k, n);
+    auto roots = [](uint64_t count, uint64_t mod) {
+        std::vector<c32> t(count);
+        for (uint64_t k = 0; k < count; ++k)
+            t[k] = root_forward(k, mod);
+        return t;
+    };
     p->sp = find_aux(m);
     if (p->sp && p->sp->launch_real) {
         // the split fused into the m-point one-pass kernel
         p->kind = Plan::REAL;
         p->grid_mult = p->sp->grid_mult;
-        return upload_tables(p, {{root_table(m), &p->tw}, {hw, &p->tw2}});
+        return upload_tables(p, {{root_table(m), &p->tw}, {roots(m + 1, n), &p->tw2}});
     }
-    // the m-point complex plan over sub-batches, the split as its own pass
+    // a run-time schedule of the m-point transform, the split fused into it
     p->sp = nullptr;
-    p->kind = Plan::REAL_SPLIT;
-    const uint64_t max_sub_samples = 1ull << 28;  // 2 GiB of complex64 in the split buffer
-    p->sub_batch = std::max<uint64_t>(1, std::min<uint64_t>(batch, max_sub_samples / m));
-    p->inner = new Plan();
-    if (plan_build(p->inner, m, p->sub_batch, dir, -1) != FFT_OK)
-        return last_status();
-    if (upload_tables(p, {{hw, &p->tw2}}) != FFT_OK)
-        return last_status();
-    const size_t zb = p->sub_batch * m * sizeof(c32);
-    if (hipMalloc(&p->zbuf, zb) != hipSuccess) {
-        p->zbuf = nullptr;
-        (void)hipGetLastError();
-        return set_error(FFT_ERR_OUT_OF_MEMORY, "split buffer of %zu bytes", zb);
+    p->kind = Plan::REAL_STAGES;
+    if (!stages_choose(m, batch, device_cus(p->device), &p->stages, dir))
+        return set_error(FFT_ERR_UNSUPPORTED_LENGTH, "no schedule for length %llu",
+                         (unsigned long long)m);
+    // (the cap on a sub-batch refuses what a plan of m points refuses)
+    if (max_scratch_samples() < m)
+        return set_error(FFT_ERR_INVALID_ARG,
+                         "one %llu-point segment needs more scratch than %llu samples",
+                         (unsigned long long)m, (unsigned long long)max_scratch_samples());
+    if (p->stages.passes == 1) {
+        p->sub_batch = batch;
+        return upload_tables(
+            p, {{lds_table(p->stages.a), &p->tw}, {roots(m / 2 + 1, n), &p->w1}});
     }
-    p->scratch_bytes = zb + p->inner->scratch_bytes;
+    const uint64_t max_sub_samples = 1ull << 28;  // 2 GiB of complex64, before Y's padding
+    p->sub_batch = std::max<uint64_t>(1, std::min<uint64_t>(batch, max_sub_samples / m));
+    const uint64_t n1 = (uint64_t)p->stages.a.n, n2 = (uint64_t)p->stages.b.n;
+    const std::vector<c32> tl = two_level_low(m, &p->sh), th = two_level_high(m, p->sh);
+    if (upload_tables(p, {{lds_table(p->stages.a), &p->tw},
+                          {lds_table(p->stages.b), &p->tw2},
+                          {tl, &p->tl},
+                          {th, &p->th},
+                          {roots((dir < 0 ? n1 : n2) / 2 + 1, n), &p->w1},
+                          {roots(dir < 0 ? n2 : n1, 2 * (dir < 0 ? n2 : n1)), &p->w2}}) != FFT_OK)
+        return last_status();
+    p->scratch_bytes = p->sub_batch * p->stages.y_samples * sizeof(c32);
+    if (hipMalloc(&p->scratch, p->scratch_bytes) != hipSuccess) {
+        p->scratch = nullptr;
+        (void)hipGetLastError();
+        return set_error(FFT_ERR_OUT_OF_MEMORY, "scratch of %zu bytes", p->scratch_bytes);
+    }
     return set_ok();
 }
 
@@ -666,14 +708,9 @@ void plan_free(Plan *p)
 {
     if (p->used && p->last_stream_valid)
         (void)hipStreamSynchronize(p->last_stream);
-    for (void *q : {p->tables, p->scratch, p->zbuf})
+    for (void *q : {p->tables, p->scratch})
         if (q)
             (void)hipFree(q);
-    if (p->inner) {
-        plan_free(p->inner);
-        delete p->inner;
-        p->inner = nullptr;
-    }
     stream_state_free(p);
     if (p->graph_exec)
         (void)hipGraphExecDestroy(p->graph_exec);
@@ -684,7 +721,7 @@ void plan_free(Plan *p)
     p->graph_exec = nullptr;
     p->graph = nullptr;
     p->capture_stream = nullptr;
-    p->tables = p->tw = p->tw2 = p->tl = p->th = p->scratch = p->zbuf = nullptr;
+    p->tables = p->tw = p->tw2 = p->tl = p->th = p->w1 = p->w2 = p->scratch = nullptr;
 }
 
 // ---------------------------------------------------------------------------
@@ -845,24 +882,24 @@ int plan_enqueue(Plan *p, const void *in, void *out, uint64_t batch, hipStream_t
         d->launch_real(dir, in, out, p->tw, p->tw2, batch, grid, s);
         break;
     }
-    case Plan::REAL_SPLIT: {
+    case Plan::REAL_STAGES: {
         const uint64_t m = n / 2;
+        if (p->stages.passes == 1) {
+            const hipError_t e =
+                stages_real_one_pass(p->stages, in, out, p->tw, p->w1, batch, s);
+            if (e != hipSuccess)
+                return hip_error(e, "real-input launch");
+            break;
+        }
+        // rows of m complex values (n floats) and of m + 1 bins
+        const uint64_t ir = dir < 0 ? m : m + 1, orow = dir < 0 ? m + 1 : m;
         for (uint64_t s0 = 0; s0 < batch; s0 += p->sub_batch) {
-            const uint64_t sb = std::min(p->sub_batch, batch - s0);
-            int st;
-            if (dir < 0) {
-                // n floats per row in = m complex; m + 1 complex per row out
-                if ((st = plan_enqueue(p->inner, (const c32 *)in + s0 * m, p->zbuf, sb, s)) !=
-                        FFT_OK ||
-                    (st = real_split_enqueue(dir, p->zbuf, (c32 *)out + s0 * (m + 1), p->tw2, m,
-                                             sb, s)) != FFT_OK)
-                    return st;
-            } else {
-                if ((st = real_split_enqueue(dir, (const c32 *)in + s0 * (m + 1), p->zbuf,
-                                             p->tw2, m, sb, s)) != FFT_OK ||
-                    (st = plan_enqueue(p->inner, p->zbuf, (c32 *)out + s0 * m, sb, s)) != FFT_OK)
-                    return st;
-            }
+            const hipError_t e = stages_real_two_pass(
+                p->stages, (const c32 *)in + s0 * ir, (c32 *)out + s0 * orow, p->scratch, p->tw,
+                p->tw2, p->tl, p->th, p->sh, p->w1, p->w2, std::min(p->sub_batch, batch - s0),
+                s);
+            if (e != hipSuccess)
+                return hip_error(e, "real-input launch");
         }
         break;
     }
@@ -987,16 +1024,23 @@ int plan_describe(const Plan *p, std::string &js)
                  (unsigned long long)(p->n / 2), rad(p->sp->radices, p->sp->nrad).c_str(),
                  p->sp->threads, p->sp->segs_per_wg, p->grid_mult);
         break;
-    case Plan::REAL_SPLIT: {
-        std::string inner;
-        plan_describe(p->inner, inner);
-        js = "{\"kind\":\"real\",\"n\":" + std::to_string(p->n) +
-             ",\"batch\":" + std::to_string(p->batch) + ",\"direction\":" +
-             std::to_string(p->dir) + ",\"complex_length\":" + std::to_string(p->n / 2) +
-             ",\"separate_split\":1,\"sub_batch\":" + std::to_string(p->sub_batch) +
-             ",\"scratch_bytes\":" + std::to_string(p->scratch_bytes) +
-             ",\"complex_plan\":" + inner + "}";
-        return FFT_OK;
+    case Plan::REAL_STAGES: {
+        std::vector<int> r;
+        const StagesPlan &g = p->stages;
+        lds_radices(g.a, &r);
+        if (g.passes == 2)
+            lds_radices(g.b, &r);
+        snprintf(buf, sizeof buf,
+                 "{\"kind\":\"real\",\"n\":%llu,\"batch\":%llu,\"direction\":%d,"
+                 "\"complex_length\":%llu,\"separate_split\":%d,\"radices\":%s,\"passes\":%d,"
+                 "\"n1\":%d,\"n2\":%d,\"threads\":[%d,%d],\"sub_batch\":%llu,"
+                 "\"scratch_bytes\":%zu}",
+                 (unsigned long long)p->n, (unsigned long long)p->batch, p->dir,
+                 (unsigned long long)(p->n / 2), g.passes == 2,
+                 rad(r.data(), (int)r.size()).c_str(), g.passes, g.a.n,
+                 g.passes == 2 ? g.b.n : 1, g.threads_a, g.threads_b,
+                 (unsigned long long)p->sub_batch, p->scratch_bytes);
+        break;
     }
     case Plan::GENERIC: {
         std::vector<int> r;

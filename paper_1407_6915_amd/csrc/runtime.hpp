@@ -15,7 +15,7 @@
 namespace fftseg {
 
 struct Plan {
-    enum Kind { COPY, SINGLE, FOURSTEP, GENERIC, REAL, REAL_SPLIT };
+    enum Kind { COPY, SINGLE, FOURSTEP, GENERIC, REAL, REAL_STAGES };
     uint64_t n = 0, batch = 0;
     int dir = -1;
     int device = 0;
@@ -24,13 +24,14 @@ struct Plan {
     const ColumnDesc *col = nullptr;
     const RowDesc *row = nullptr;
     uint64_t n1 = 0, n2 = 0;
-    StagesPlan stages;          // GENERIC: run-time radix schedules
+    StagesPlan stages;          // GENERIC, REAL_STAGES: run-time radix schedules
     void *tables = nullptr;     // the allocation that holds the tables below
     void *tw = nullptr;         // W_N (single pass) or W_N1 (four-step) table;
                                 // GENERIC: the first schedule's table
     void *tw2 = nullptr;        // W_N2 table (four-step); W_N^k, k <= N/2 (real);
                                 // GENERIC: the row schedule's table
     void *tl = nullptr, *th = nullptr;  // two-level W_N table
+    void *w1 = nullptr, *w2 = nullptr;  // REAL_STAGES: the split's factors
     int sh = 0;
     void *scratch = nullptr;
     size_t scratch_bytes = 0;
@@ -47,13 +48,9 @@ struct Plan {
     void *graph_out = nullptr;
     hipStream_t capture_stream = nullptr;
     void *stream_state = nullptr;  // pinned host ring of the streaming path
-    // REAL_SPLIT: the complex n/2-point plan (batch = sub_batch) and the
-    // buffer of its spectra (forward) or inputs (inverse), sub_batch rows
-    Plan *inner = nullptr;
-    void *zbuf = nullptr;
 };
 
-inline bool is_real(const Plan *p) { return p->kind == Plan::REAL || p->kind == Plan::REAL_SPLIT; }
+inline bool is_real(const Plan *p) { return p->kind == Plan::REAL || p->kind == Plan::REAL_STAGES; }
 
 int set_ok();
 int set_error(int status, const char *fmt, ...);
@@ -101,10 +98,8 @@ int plan_enqueue(Plan *p, const void *in, void *out, uint64_t batch, hipStream_t
 hipError_t stages_enqueue(const Plan *p, const void *in, void *out, uint64_t batch, uint64_t hop,
                           const float *window, hipStream_t s);
 // real-input plans: length n = 2m through the m-point one-pass kernel, or,
-// where m has none, through the m-point complex plan and a separate split pass
+// where m has none, through a run-time schedule of m points
 int plan_build_real(Plan *p, uint64_t n, uint64_t batch, int dir);
-int real_split_enqueue(int dir, const void *in, void *out, const void *hw, uint64_t m,
-                       uint64_t batch, hipStream_t s);
 // entry points that only take complex segments refuse real plans
 int reject_real(const Plan *p, const char *what);
 int plan_describe(const Plan *p, std::string &js);

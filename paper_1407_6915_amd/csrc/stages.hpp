@@ -70,10 +70,14 @@ struct StagesPlan {
     int lc = 0, lr = 0;      // two passes: log2 of the columns / rows per workgroup
     int threads_a = 0, threads_b = 0;
     bool most_a = false, most_b = false;  // see lds_threads
+    unsigned blocks_a = 0, blocks_b = 0;  // two passes: tiles of a segment
+    int real = 0;            // real segments of 2n samples: -1 forward (the row tiles pair
+                             // rows k1 and n1 - k1), +1 inverse (the column tiles pair
+                             // columns)
     uint64_t y_samples = 0;  // two passes: samples of Y per segment
 };
 // false if the length has no plan (none of the supported lengths)
-bool stages_choose(uint64_t n, uint64_t batch, int cus, StagesPlan *p);
+bool stages_choose(uint64_t n, uint64_t batch, int cus, StagesPlan *p, int real = 0);
 // Launches of `batch` segments: segment s starts at in + s * hop and is
 // multiplied by window[0..n) if that is not null; its spectrum goes to
 // out + s * n.
@@ -84,5 +88,47 @@ hipError_t stages_two_pass(const StagesPlan &p, int dir, const void *in, void *o
                            const void *tw_a, const void *tw_b, const void *tl, const void *th,
                            int sh, uint64_t batch, uint64_t hop, const float *window,
                            hipStream_t s);
+
+hipError_t stages_rows(const StagesPlan &p, int dir, const void *y, void *out, const void *tw,
+                       uint64_t batch, hipStream_t s);
+// Real segments of N = 2n samples (plans of stages_choose with `real`): the
+// batch's rows of N float32 (n complex values) and of n + 1 bins.  One pass:
+// hw = W_N^k, k <= n/2.  Two: w1 = W_N^j for the first half of the paired
+// rows (columns) j, w2 = W_{2 n2}^k, k < n2 (forward) or W_{2 n1}^i, i < n1
+// (inverse).
+hipError_t stages_real_one_pass(const StagesPlan &p, const void *in, void *out, const void *tw,
+                                const void *hw, uint64_t batch, hipStream_t s);
+hipError_t stages_real_two_pass(const StagesPlan &p, const void *in, void *out, void *y,
+                                const void *tw_a, const void *tw_b, const void *tl,
+                                const void *th, int sh, const void *w1, const void *w2,
+                                uint64_t batch, hipStream_t s);
+
+constexpr int kLdsBytes = 160 * 1024;
+
+// LDS of a column tile (with the last stage's W_N factors) and of a row tile
+inline size_t columns_lds(const LdsSched &s, int lc)
+{
+    return ((size_t)s.n * ((1u << lc) + 1) + ((size_t)s.st[s.ns - 1].r << lc)) * sizeof(c32);
+}
+inline size_t rows_lds(const LdsSched &s, int lr) { return ((size_t)s.n << lr) * sizeof(c32); }
+
+// fast_div's multiplier for a division by d: exact for x d < 2^32
+inline uint32_t reciprocal(int d)
+{
+    return d <= 1 ? 0u : (uint32_t)((1ull << 32) / (uint64_t)d + 1);
+}
+
+// a workgroup's LDS may go past the runtime's default limit
+template <class K>
+hipError_t allow_lds(K kernel, size_t bytes)
+{
+    if (bytes <= 64 * 1024)
+        return hipSuccess;
+    return hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               kLdsBytes);
+}
+
+// grid of `tiles` workgroups for xcd_tile
+inline unsigned xcd_grid(uint64_t tiles) { return (unsigned)((tiles + 7) / 8 * 8); }
 
 }  // namespace fftseg

@@ -1,0 +1,383 @@
+// Device side of the run-time radix schedules: the stage engine and the
+// accessors of its tiles (whole segments, columns, rows).
+#pragma once
+
+#include "stages.hpp"
+#include "tile.hpp"
+
+namespace fftseg {
+namespace stages {
+
+__device__ __forceinline__ int fast_div(int x, uint32_t m)
+{
+    return m ? (int)__umulhi((unsigned)x, m) : x;
+}
+
+// Memory seen through a buffer descriptor: an access is at a uniform
+// offset (in samples) plus a lane's offset (in bytes).  The element strides
+// of a butterfly are uniform, so its R accesses share one offset register
+// and take the rest from scalar ones.  Offsets stay below 2^31 bytes.
+struct Buffer {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ explicit Buffer(const void *p)
+        : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, 0x7fffffff, 0x00027000))
+    {
+    }
+    __device__ __forceinline__ c32 load(unsigned lane, int uniform) const
+    {
+        return __builtin_bit_cast(c32,
+                                  __builtin_amdgcn_raw_buffer_load_b64(r, lane, 8 * uniform, 0));
+    }
+    __device__ __forceinline__ float load_float(unsigned lane, int uniform) const
+    {
+        return __builtin_bit_cast(float,
+                                  __builtin_amdgcn_raw_buffer_load_b32(r, lane, 4 * uniform, 0));
+    }
+    __device__ __forceinline__ void store(unsigned lane, int uniform, c32 v) const
+    {
+        typedef unsigned u2v __attribute__((ext_vector_type(2)));
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2v, v), r, lane, 8 * uniform, 0);
+    }
+};
+
+// One stage of the tile.  Io maps a butterfly number g to butterfly b of
+// transform c, gives the LDS slots of a transform's elements, and does the
+// first stage's loads (gl) and the last stage's stores (gs), unless the
+// tile is filled before (kFirstLds) or read after (kLastLds) through LDS.
+template <int R, int D, bool Most, class Io>
+__device__ __forceinline__ void lds_stage(const Io &io, const LdsStage &st, bool gl, bool gs,
+                                          c32 *lds, const Buffer &tw)
+{
+    constexpr int U = lds_units(R, Most);
+    c32 v[U][R];
+    int bb[U], cc[U];
+    bool ok[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        ok[u] = io.map(st, gs, (int)threadIdx.x + u * (int)blockDim.x, bb[u], cc[u]);
+        if (ok[u]) {
+            if (gl) {
+                io.template load<R>(v[u], bb[u], cc[u], st.nb);
+            } else {
+                const c32 *p = lds + io.slot(bb[u], cc[u]);
+                const int d = st.nb * io.step();
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    v[u][r] = p[r * d];
+            }
+        }
+    }
+    if (!gl && !gs)
+        __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (ok[u]) {
+            const int b = bb[u];
+            int q = b, k = 0;
+            if (st.l > 1) {
+                q = fast_div(b, st.ml);
+                k = b - q * st.l;
+                // radices from 12 on read theirs in pairs (tw_pair_low)
+                constexpr int R1 = tw_pair_low(R);
+                if constexpr (R1 > 0) {
+                    c32 wl[R1];
+#pragma unroll
+                    for (int j = 1; j < R1; ++j) {
+                        wl[j] = tw.load(8u * k, st.tw + (j - 1) * st.l);
+                        v[u][j] = twiddle<D>(v[u][j], wl[j]);
+                    }
+#pragma unroll
+                    for (int h = 1; h < R / R1; ++h) {
+                        const c32 wh = tw.load(8u * k, st.tw + (h * R1 - 1) * st.l);
+                        v[u][h * R1] = twiddle<D>(v[u][h * R1], wh);
+#pragma unroll
+                        for (int j = 1; j < R1; ++j)
+                            v[u][h * R1 + j] = twiddle<D>(v[u][h * R1 + j], cmul(wh, wl[j]));
+                    }
+                } else {
+#pragma unroll
+                    for (int r = 1; r < R; ++r)
+                        v[u][r] = twiddle<D>(v[u][r], tw.load(8u * k, st.tw + (r - 1) * st.l));
+                }
+            }
+            dft<R, D>(v[u]);
+            if (gs) {
+                io.template finish<R, D>(v[u], b, cc[u], st.nb);
+                io.template store<R>(v[u], b, cc[u], st.nb);
+            } else {
+                c32 *p = lds + io.slot(q * st.l * R + k, cc[u]);
+                const int d = st.l * io.step();
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    p[r * d] = v[u][r];
+            }
+        }
+    }
+    if (!gs)
+        __syncthreads();
+}
+
+template <int D, bool Most, class Io>
+__device__ __forceinline__ void run_stages(const Io &io, const LdsSched &s, c32 *lds,
+                                           const c32 *table)
+{
+    const Buffer tw(table);
+    for (int i = 0; i < s.ns; ++i) {
+        const LdsStage &st = s.st[i];
+        const bool gl = i == 0 && !Io::kFirstLds, gs = i + 1 == s.ns && !Io::kLastLds;
+        switch (st.r) {
+        case 2: lds_stage<2, D, Most>(io, st, gl, gs, lds, tw); break;
+        case 3: lds_stage<3, D, Most>(io, st, gl, gs, lds, tw); break;
+        case 4: lds_stage<4, D, Most>(io, st, gl, gs, lds, tw); break;
+        case 5: lds_stage<5, D, Most>(io, st, gl, gs, lds, tw); break;
+        case 6: lds_stage<6, D, Most>(io, st, gl, gs, lds, tw); break;
+        case 8: lds_stage<8, D, Most>(io, st, gl, gs, lds, tw); break;
+        case 9: lds_stage<9, D, Most>(io, st, gl, gs, lds, tw); break;
+        case 10: lds_stage<10, D, Most>(io, st, gl, gs, lds, tw); break;
+        case 12: lds_stage<12, D, Most>(io, st, gl, gs, lds, tw); break;
+        case 15: lds_stage<15, D, Most>(io, st, gl, gs, lds, tw); break;
+        case 16: lds_stage<16, D, Most>(io, st, gl, gs, lds, tw); break;
+        default: lds_stage<25, D, Most>(io, st, gl, gs, lds, tw); break;
+        }
+    }
+}
+
+// Whole segments: transform c is segment c of the tile, its elements in
+// consecutive slots; butterflies of a segment on consecutive lanes, so the
+// first stage loads and the last stage stores runs of nb samples.
+struct SegmentIo {
+    static constexpr bool kFirstLds = false, kLastLds = false;
+    const c32 *x;
+    c32 *y;
+    const float *window;
+    uint64_t hop;
+    int n, segs;  // segments the tile holds
+    template <int R, int D>
+    __device__ __forceinline__ void finish(c32 *, int, int, int) const
+    {
+    }
+    __device__ __forceinline__ bool map(const LdsStage &st, bool, int g, int &b, int &c) const
+    {
+        c = fast_div(g, st.mnb);
+        b = g - c * st.nb;
+        return c < segs;
+    }
+    __device__ __forceinline__ int slot(int i, int c) const { return c * n + i; }
+    __device__ __forceinline__ int step() const { return 1; }
+    template <int R>
+    __device__ __forceinline__ void load(c32 *v, int b, int c, int nb) const
+    {
+        // (the launch keeps segs * hop below 2^28 samples)
+        const Buffer xb(x);
+        const unsigned at = 8u * ((unsigned)c * (unsigned)hop + (unsigned)b);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            v[r] = xb.load(at, r * nb);
+        if (window) {
+            const Buffer w(window);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const float f = w.load_float(4u * b, r * nb);
+                v[r] = c32{v[r].x * f, v[r].y * f};
+            }
+        }
+    }
+    template <int R>
+    __device__ __forceinline__ void store(const c32 *v, int b, int c, int nb) const
+    {
+        const Buffer yb(y);
+        const unsigned at = 8u * (unsigned)(c * n + b);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            yb.store(at, r * nb, v[r]);
+    }
+};
+
+// Four-step column pass: transform c is column first + c of the segment
+// (elements n2 samples apart), columns on consecutive lanes, slots of one
+// element row 2^lc + 1 apart.  The last stage instead puts 2^lr consecutive
+// outputs k1 on consecutive lanes, then the columns: Y keeps the rows of one
+// row tile together,
+//     Y[(k1 >> lr)][n2][k1 mod 2^lr],
+// so that a wave stores one run here and the row pass loads its tile as one
+// W_N^{n2 k1} of output k1 = b + r nb is W_N^{n2 b}, looked up once per
+// butterfly, times W_N^{n2 r nb}, looked up once per tile into LDS: a lookup
+// is two gathers from tables of a few thousand entries, and one per output
+// held the pass to half its rate (20000 points: 606 us per 2^26 samples).
+// PairRows (real segments, forward): a row tile holds rows k1 and n1 - k1,
+// the first half of its slots and the second, so Y groups the rows so.
+// PairColumns (real segments, inverse): the tile holds columns n2' and
+// n2 - n2' in the same way, and LDS is filled before the first stage.
+template <bool PairRows, bool PairColumns>
+struct ColumnIo {
+    static constexpr bool kFirstLds = PairColumns, kLastLds = false;
+    const c32 *x;
+    c32 *y;
+    const float *window;
+    const c32 *__restrict__ tl;
+    const c32 *__restrict__ th;
+    const c32 *wr;  // LDS: W_N^{n2 r nb} of the last stage's outputs, [r][column]
+    int sh, n2, first, lc, lr;
+    unsigned n1;
+    __device__ __forceinline__ c32 root(unsigned m) const
+    {
+        return cmul(th[m >> sh], tl[m & ((1u << sh) - 1u)]);
+    }
+    __device__ __forceinline__ bool map(const LdsStage &st, bool gs, int g, int &b, int &c) const
+    {
+        if (gs) {
+            c = (g >> lr) & ((1 << lc) - 1);
+            b = ((g >> (lr + lc)) << lr) | (g & ((1 << lr) - 1));
+        } else {
+            c = g & ((1 << lc) - 1);
+            b = g >> lc;
+        }
+        return b < st.nb && has(c);
+    }
+    // column of slot c, and whether the slot holds one
+    __device__ __forceinline__ int column(int c) const
+    {
+        const int half = 1 << (lc - 1);
+        return !PairColumns || c < half ? first + c : n2 - (first + c - half);
+    }
+    __device__ __forceinline__ bool has(int c) const
+    {
+        const int half = 1 << (lc - 1), p = first + c - half;
+        if (!PairColumns)
+            return first + c < n2;
+        return c < half ? 2 * (first + c) <= n2 : p > 0 && 2 * p < n2;
+    }
+    __device__ __forceinline__ int step() const { return (1 << lc) + 1; }
+    __device__ __forceinline__ int slot(int i, int c) const { return i * step() + c; }
+    template <int R>
+    __device__ __forceinline__ void load(c32 *v, int b, int c, int nb) const
+    {
+        const Buffer xb(x);
+        const unsigned at = 8u * (unsigned)(b * n2 + first + c);
+        const int d = nb * n2;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            v[r] = xb.load(at, r * d);
+        if (window) {
+            const Buffer w(window);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const float f = w.load_float(at / 2, r * d);
+                v[r] = c32{v[r].x * f, v[r].y * f};
+            }
+        }
+    }
+    template <int R>
+    __device__ __forceinline__ void store(const c32 *v, int b, int c, int nb) const
+    {
+        const unsigned col = (unsigned)column(c);
+        const Buffer yb(y);
+        if (!PairRows && (nb & ((1 << lr) - 1)) == 0) {
+            const unsigned at = 8u * y_at((unsigned)b, col);
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                yb.store(at, r * nb * n2, v[r]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                yb.store(8u * y_at((unsigned)(b + r * nb), col), 0, v[r]);
+        }
+    }
+    __device__ __forceinline__ unsigned y_at(unsigned k1, unsigned col) const
+    {
+        unsigned at = k1;
+        if constexpr (PairRows) {
+            const unsigned half = 1u << (lr - 1), high = 2 * k1 > n1 ? 1u : 0u;
+            const unsigned p = high ? n1 - k1 : k1;
+            at = ((p >> (lr - 1)) << lr) | (high ? half : 0u) | (p & (half - 1u));
+        }
+        return (((at >> lr) * (unsigned)n2 + col) << lr) | (at & ((1u << lr) - 1u));
+    }
+    template <int R, int D>
+    __device__ __forceinline__ void finish(c32 *v, int b, int c, int) const
+    {
+        const c32 wb = root((unsigned)column(c) * (unsigned)b);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            v[r] = twiddle<D>(v[r], cmul(wb, wr[(r << lc) + c]));
+    }
+};
+
+// Four-step row pass: transform c is row first + c of Y (one contiguous tile,
+// the rows on consecutive lanes), stored transposed as X[k1 + n1 k2].
+// Pair: the tile of rows first + c and n1 - (first + c) (see ColumnIo), left
+// in LDS by the last stage.
+template <bool Pair>
+struct RowIo {
+    static constexpr bool kFirstLds = false, kLastLds = Pair;
+    const c32 *x;  // the tile
+    c32 *y;        // segment output
+    int n1, first, lr;
+    template <int R, int D>
+    __device__ __forceinline__ void finish(c32 *, int, int, int) const
+    {
+    }
+    __device__ __forceinline__ bool map(const LdsStage &st, bool, int g, int &b, int &c) const
+    {
+        c = g & ((1 << lr) - 1);
+        b = g >> lr;
+        return b < st.nb && has(c);
+    }
+    __device__ __forceinline__ bool has(int c) const
+    {
+        const int half = 1 << (lr - 1), p = first + c - half;
+        if (!Pair)
+            return first + c < n1;
+        return c < half ? 2 * (first + c) <= n1 : p > 0 && 2 * p < n1;
+    }
+    __device__ __forceinline__ int step() const { return 1 << lr; }
+    __device__ __forceinline__ int slot(int i, int c) const { return (i << lr) + c; }
+    template <int R>
+    __device__ __forceinline__ void load(c32 *v, int b, int c, int nb) const
+    {
+        const Buffer xb(x);
+        const unsigned at = 8u * (unsigned)slot(b, c);
+        const int d = nb << lr;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            v[r] = xb.load(at, r * d);
+    }
+    template <int R>
+    __device__ __forceinline__ void store(const c32 *v, int b, int c, int nb) const
+    {
+        const Buffer yb(y);
+        const unsigned at = 8u * (unsigned)(b * n1 + first + c);
+        const int d = nb * n1;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            yb.store(at, r * d, v[r]);
+    }
+};
+
+// Tile w of a grid of 8 * per workgroups, dealt so that each XCD (workgroup
+// mod 8) takes consecutive tiles: neighbours share cache lines where the
+// lengths are no multiple of 16.
+__device__ __forceinline__ uint64_t xcd_tile()
+{
+    return (uint64_t)(blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+}
+
+extern __shared__ c32 stage_lds[];
+
+// Factors W_N^{n2 r nb} of a column tile's last stage into LDS behind the
+// tile (read after the barriers of the first exchange)
+template <class Io>
+__device__ __forceinline__ c32 *column_factors(const Io &io, const LdsSched &s)
+{
+    c32 *wr = stage_lds + s.n * ((1 << io.lc) + 1);
+    const LdsStage &last = s.st[s.ns - 1];
+    for (int e = threadIdx.x; e < last.r << io.lc; e += blockDim.x) {
+        const int r = e >> io.lc, c = e & ((1 << io.lc) - 1);
+        if (io.has(c))
+            wr[e] = io.root((unsigned)io.column(c) * (unsigned)(r * last.nb));
+    }
+    return wr;
+}
+
+}  // namespace stages
+}  // namespace fftseg

@@ -68,3 +68,31 @@ def test_schedules_across_sub_batches(monkeypatch):
     check(n, y, x)
     f = x.reshape(-1)
     check(n, z, np.stack([f[s * n // 2:s * n // 2 + n] for s in range(b)]))
+
+
+# (real length, batch): half lengths 3 (one stage), 5 x 5, odd and even halves
+# in one pass, the longest there; two passes with odd and even n1 and n2,
+# paired tiles narrower than 16, one row pair, long compiled halves
+@pytest.mark.parametrize("n,batch", [(6, 3000), (50, 1001), (250, 400), (720, 301), (4374, 40),
+                                     (38400, 3), (36864, 3), (39366, 3), (100000, 3),
+                                     (156250, 2), (1 << 18, 2), (3 << 20, 1), (3906250, 1),
+                                     (1 << 24, 1)])
+def test_real_schedules_match_oracle(n, batch):
+    import siggen
+    import torch
+    announce("real schedule n=%d batch=%d" % (n, batch))
+    z = siggen.Signal(seed=n % 9973, seg_len=n, sigma=1.0).samples(0, n * batch // 2 + 1)
+    x = z.view(np.float32)[:n * batch].copy()
+    ref = oracle.real_forward(x, n)
+    with fs.RealPlan(n, batch) as p:
+        got = p.exec(torch.from_numpy(x).cuda()).cpu().numpy().reshape(batch, n // 2 + 1)
+    assert np.all(oracle.rel_l2(got, ref) <= oracle.tolerance(n))
+    spec = ref.astype(np.complex64)
+    want = oracle.real_inverse(spec, n)
+    # (imaginary parts of bins 0 and n/2 are ignored)
+    spec[:, 0] += 3j
+    spec[:, n // 2] -= 5j
+    with fs.RealPlan(n, batch, fs.INVERSE) as p:
+        back = p.exec(torch.from_numpy(spec.reshape(-1)).cuda()).cpu().numpy().reshape(batch, n)
+    err = np.linalg.norm(back - want, axis=1) / np.linalg.norm(want, axis=1)
+    assert np.all(err <= oracle.tolerance(n)), err.max()
