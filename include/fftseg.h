@@ -162,8 +162,8 @@ const char *fft_last_error(void);
 
 /* Factorise n into the radices the planner would use for one pass of up to
  * 16384 samples (for a length without compiled tiles, those of its run-time
- * schedule, the column pass's before the row pass's; a radix-9 stage is
- * listed as its two radix-3 steps).  Writes up to `max` radices to
+ * schedule, the column pass's before the row pass's, with radix 9, 18, 24,
+ * 27 and 30 stages listed as their in-register steps).  Writes up to `max` radices to
  * `radices` and returns their count, or a negative fft_status_t. */
 int fft_plan_factorize(size_t n, int *radices, int max);
 

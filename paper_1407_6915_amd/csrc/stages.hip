@@ -8,13 +8,13 @@
 // stage is a uniform switch, so one kernel serves every length.
 //
 // Bound by HBM: 16 B/sample in one pass, 32 in two, where one launch per
-// radix moved 16 B/sample per stage with scattered stores (30011 segments
-// of 360 points: 152 us before, 45 now; 1001 of 15625: 290 and 78; 16 of
-// 3 x 2^20: 1188 and 478; 2 of 2^24: 1028 and 492).  One pass moves 4.4 to
-// 5.1 TB/s up to 4096 points and 3.0 to 4.0 above, where one or two
-// workgroups fill a CU's LDS and little of a tile's loads overlaps another's
-// stages; two passes 4.2 to 5.3 with tiles of two workgroups a CU, 2.5 to
-// 3.9 with larger ones (2^26 samples).
+// radix moved 16 B/sample per stage with scattered stores.  What keeps a
+// pass below the copy rate of 5.8 TB/s is the LDS exchange between stages
+// (about 10 % of a pass each) and, above 10000 points or in tiles of more
+// than half a CU's LDS, that little of a tile's loads overlaps another's
+// stages: 5.0 to 5.6 TB/s with two stages, 4.5 to 5.1 with three, 3.5 to 4.1
+// from 10000 points on; two passes move 4.2 to 5.3 with tiles of two
+// workgroups a CU and 2.5 to 3.9 with larger ones (2^26 samples).
 #include "stages.hpp"
 
 #include <algorithm>
@@ -29,8 +29,8 @@ namespace {
 
 using namespace stages;
 
-template <int D, bool Most>
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
+template <int D, int F>
+__global__ void STAGES_KERNEL(F, false)
     stages_segments_kernel(const c32 *in, c32 *out, const c32 *__restrict__ tw, LdsSched s,
                            int segs, uint64_t batch, uint64_t hop,
                            const float *__restrict__ window)
@@ -38,11 +38,11 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)
     const uint64_t seg = (uint64_t)blockIdx.x * (unsigned)segs;
     const int have = (int)(batch - seg < (uint64_t)segs ? batch - seg : (uint64_t)segs);
     const SegmentIo io{in + seg * hop, out + seg * (unsigned)s.n, window, hop, s.n, have};
-    run_stages<D, Most>(io, s, stage_lds, tw);
+    run_stages<D, F>(io, s, stage_lds, tw);
 }
 
-template <int D, bool Most>
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
+template <int D, int F>
+__global__ void STAGES_KERNEL(F, true)
     stages_columns_kernel(const c32 *in, c32 *ybuf, const c32 *__restrict__ tw,
                           const c32 *__restrict__ tl, const c32 *__restrict__ th, int sh,
                           LdsSched s, int n2, int lc, int lr, unsigned blocks, uint64_t tiles,
@@ -56,11 +56,11 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)
     ColumnIo<false, false> io{in + seg * hop, ybuf + seg * ysamples, window, tl, th, nullptr, sh,
                               n2, first, lc, lr, (unsigned)s.n};
     io.wr = column_factors(io, s);
-    run_stages<D, Most>(io, s, stage_lds, tw);
+    run_stages<D, F>(io, s, stage_lds, tw);
 }
 
-template <int D, bool Most>
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
+template <int D, int F>
+__global__ void STAGES_KERNEL(F, false)
     stages_rows_kernel(const c32 *ybuf, c32 *out, const c32 *__restrict__ tw, LdsSched s, int n1,
                        int lr, unsigned blocks, uint64_t tiles, uint64_t ysamples)
 {
@@ -71,17 +71,17 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)
     const unsigned blk = (unsigned)(t - seg * blocks);
     const RowIo<false> io{ybuf + seg * ysamples + ((uint64_t)blk << lr) * (unsigned)s.n,
                    out + seg * ((uint64_t)n1 * (unsigned)s.n), n1, (int)(blk << lr), lr};
-    run_stages<D, Most>(io, s, stage_lds, tw);
+    run_stages<D, F>(io, s, stage_lds, tw);
 }
 
 // ---------------------------------------------------------------------------
 // planner
 
-constexpr int kRadixList[] = {25, 16, 15, 12, 10, 9, 8, 6, 5, 4, 3, 2};
+constexpr int kRadixList[] = {32, 30, 27, 25, 24, 20, 18, 16, 15, 12, 10, 9, 8, 6, 5, 4, 3, 2};
 
 // fewest stages, then the smallest sum of radices (the work of a stage grows
 // with neither, its registers and idle threads do)
-void best_radices(int n, int from, std::vector<int> &cur, std::vector<int> &best)
+void best_radices(int n, int from, bool wide, std::vector<int> &cur, std::vector<int> &best)
 {
     if (n == 1) {
         auto sum = [](const std::vector<int> &v) {
@@ -100,37 +100,21 @@ void best_radices(int n, int from, std::vector<int> &cur, std::vector<int> &best
     for (int i = from; i < (int)(sizeof(kRadixList) / sizeof(kRadixList[0])); ++i) {
         // (one stage of a composite length would put the lanes of a load n
         // samples apart: two stages ran at 4.6 TB/s where one ran at 2.8)
-        if (n % kRadixList[i] || (cur.empty() && n == kRadixList[i] && n > 5))
+        if (n % kRadixList[i] || (!wide && kRadixList[i] > 16 && kRadixList[i] != 25) ||
+            (cur.empty() && n == kRadixList[i] && n > 5))
             continue;
         cur.push_back(kRadixList[i]);
-        best_radices(n / kRadixList[i], i, cur, best);
+        best_radices(n / kRadixList[i], i, wide, cur, best);
         cur.pop_back();
     }
 }
 
-// log2 of a tile's columns or rows: the widest of 16 and 8 that leaves room
-// for two workgroups on a CU (one loads while the other computes: 1000-point
-// columns 325 us per 2^26 samples with 8, 356 with 16), else the widest that
-// fits; -1 if none does.  A paired tile's runs are half as long: 16 slots
-// wherever they fit.
-template <class Lds>
-int widest(Lds lds, bool paired)
-{
-    for (int l = 4; l >= (paired ? 4 : 3); --l)
-        if (lds(l) <= (size_t)kLdsBytes / 2)
-            return l;
-    for (int l = 4; l >= 0; --l)
-        if (lds(l) <= (size_t)kLdsBytes)
-            return l;
-    return -1;
-}
-
 }  // namespace
 
-bool lds_schedule(int n, LdsSched *s, int group)
+bool lds_schedule(int n, LdsSched *s, bool wide, int group)
 {
     std::vector<int> cur, best;
-    best_radices(n, 0, cur, best);
+    best_radices(n, 0, wide, cur, best);
     if (best.empty() || (int)best.size() > kMaxLdsStages)
         return false;
     // the smallest odd radix first: the first stage writes LDS at a stride of
@@ -168,22 +152,22 @@ bool lds_schedule(int n, LdsSched *s, int group)
     return true;
 }
 
-int lds_threads(const LdsSched &s, int tiles, int group, bool *most)
+int lds_threads(const LdsSched &s, int tiles, int group, int form, bool column)
 {
-    int t = 64;
-    *most = false;
+    const int most = form_threads(form, column);
+    long long t = 64;
     for (int i = 0; i < s.ns; ++i) {
         int nb = s.st[i].nb;
         if (i + 1 == s.ns)
             nb = (nb + group - 1) / group * group;
         const long long total = (long long)nb * tiles;
-        const int un = lds_units(s.st[i].r, false), um = lds_units(s.st[i].r, true);
-        if ((total + um - 1) / um > 1024)
+        if ((total + lds_units(s.st[i].r, form) - 1) / lds_units(s.st[i].r, form) > most)
             return 0;
-        *most |= (total + un - 1) / un > 1024;
-        t = std::max<int>(t, (int)std::min<long long>(1024, (total + un - 1) / un));
+        // (kMost: as many threads as the other forms would take, if they fit)
+        const int u = lds_units(s.st[i].r, form == kMost ? kNarrow : form);
+        t = std::max(t, std::min<long long>(most, (total + u - 1) / u));
     }
-    return (t + 63) / 64 * 64;
+    return (int)((t + 63) / 64 * 64);
 }
 
 int lds_table_size(const LdsSched &s)
@@ -210,30 +194,96 @@ std::vector<c32> lds_table(const LdsSched &s)
 void lds_radices(const LdsSched &s, std::vector<int> *out)
 {
     for (int i = 0; i < s.ns; ++i) {
-        if (s.st[i].r == 9)
-            out->insert(out->end(), {3, 3});
-        else
-            out->push_back(s.st[i].r);
+        switch (s.st[i].r) {
+        case 9: out->insert(out->end(), {3, 3}); break;
+        case 18: out->insert(out->end(), {2, 3, 3}); break;
+        case 24: out->insert(out->end(), {4, 6}); break;
+        case 27: out->insert(out->end(), {3, 3, 3}); break;
+        case 30: out->insert(out->end(), {2, 15}); break;
+        default: out->push_back(s.st[i].r); break;
+        }
     }
 }
+
+namespace {
+
+struct Tile {
+    LdsSched s{};
+    int form = kNarrow, threads = 0, l = 0;
+};
+
+// The schedule, form and threads of a workgroup for `tiles` transforms of n
+// points: the wide form where its radices save a stage (2^26 samples: 360
+// points 229 us to 194, 600 224 to 192, 8000 273 to 226, 20000 442 in two
+// passes to 272 in one), except in tiles of half a CU's LDS and more with
+// several transforms (two rows of 8192: 406 us to 550).
+bool choose_form(int n, int tiles, int group, bool column, Tile *t)
+{
+    LdsSched narrow, wide;
+    if (!lds_schedule(n, &narrow, false, group))
+        return false;
+    if ((tiles == 1 || (size_t)n * tiles * sizeof(c32) <= (size_t)kLdsBytes / 2) &&
+        lds_schedule(n, &wide, true, group) && wide.ns < narrow.ns &&
+        (t->threads = lds_threads(wide, tiles, group, kWide, column))) {
+        t->s = wide;
+        t->form = kWide;
+        return true;
+    }
+    t->s = narrow;
+    for (t->form = kNarrow; t->form <= kMost; ++t->form)
+        if ((t->threads = lds_threads(narrow, tiles, group, t->form, column)))
+            return true;
+    return false;
+}
+
+size_t tile_bytes(uint64_t n, int l, bool column)
+{
+    return n * ((1u << l) + (column ? 1 : 0)) * sizeof(c32);
+}
+size_t tile_lds(const Tile &t, bool column)
+{
+    return column ? columns_lds(t.s, t.l) : rows_lds(t.s, t.l);
+}
+
+// A tile of 2^l columns or rows of n points: the widest of 16 and 8 that
+// leaves room for two workgroups on a CU (one loads while the other
+// computes: 1000-point columns 325 us per 2^26 samples with 8, 356 with 16),
+// else the widest that fits.  A paired tile's runs are half as long: 16 slots
+// wherever they fit.
+bool choose_tile(int n, bool column, int group, bool paired, Tile *t)
+{
+    for (int fill : {2, 1})
+        for (t->l = 4; t->l >= (fill == 1 ? (paired ? 1 : 0) : paired ? 4 : 3); --t->l)
+            if (tile_bytes(n, t->l, column) <= (size_t)kLdsBytes / fill &&
+                choose_form(n, 1 << t->l, group, column, t) &&
+                tile_lds(*t, column) <= (size_t)kLdsBytes / fill)
+                return true;
+    return false;
+}
+
+}  // namespace
 
 bool stages_choose(uint64_t n, uint64_t batch, int cus, StagesPlan *p, int real)
 {
     *p = StagesPlan{};
     p->real = real;
-    if (n * sizeof(c32) <= (uint64_t)kLdsBytes && lds_schedule((int)n, &p->a)) {
+    Tile t;
+    if (n * sizeof(c32) <= (uint64_t)kLdsBytes) {
         // 3072 samples a workgroup (24 KB of LDS, six workgroups a CU; 4096
         // and 2048 were up to 30 % and 10 % slower: 1200 points 158 and 113 us
         // against 115, 60 points 112 and 116 against 110, each 2^25 samples),
         // fewer where the batch would leave CUs without work; where there is
         // one stage (3 or 5 points) one butterfly a thread
-        int segs = p->a.ns == 1 ? 256 : std::max(1, 3072 / (int)n);
-        while (p->a.ns > 1 && segs > 1 && (batch + segs - 1) / segs < 2 * (uint64_t)cus)
+        const bool one = n == 2 || n == 3 || n == 4 || n == 5;
+        int segs = one ? 256 : std::max(1, 3072 / (int)n);
+        while (!one && segs > 1 && (batch + segs - 1) / segs < 2 * (uint64_t)cus)
             segs = (segs + 1) / 2;
-        p->segs = segs;
-        p->threads_a = p->a.ns == 1 ? segs : lds_threads(p->a, segs, 1, &p->most_a);
-        if (p->threads_a) {
+        if (choose_form((int)n, segs, 1, false, &t)) {
             p->passes = 1;
+            p->a = t.s;
+            p->form_a = t.form;
+            p->segs = segs;
+            p->threads_a = one ? segs : t.threads;
             return true;
         }
     }
@@ -261,42 +311,38 @@ bool stages_choose(uint64_t n, uint64_t batch, int cus, StagesPlan *p, int real)
             lc -= real > 0 && lc > 0;
             lr -= real < 0 && lr > 0;
             return column[lc][lc2] * (groups ? 1 : 1.25) * (n2 % 16 ? 1.08 : 1) +
-                   row[lr][lr2] * (n1 % 16 ? 1.15 : 1) + 0.03 * stages;
+                   row[lr][lr2] * (n1 % 16 ? 1.15 : 1) + 0.12 * stages;
         };
         // what the sizes alone allow, before any schedule is looked for
-        const int lr0 = widest([&](int l) { return (n2 << l) * sizeof(c32); }, real < 0);
-        const int lc0 =
-            widest([&](int l) { return n1 * ((1u << l) + 1) * sizeof(c32); }, real > 0);
+        auto widest = [](uint64_t m, bool column, bool paired) {
+            for (int l = 4; l >= (paired ? 4 : 3); --l)
+                if (tile_bytes(m, l, column) <= kHalf)
+                    return l;
+            for (int l = 4; l >= 0; --l)
+                if (tile_bytes(m, l, column) <= (size_t)kLdsBytes)
+                    return l;
+            return -1;
+        };
+        const int lc0 = widest(n1, true, real > 0), lr0 = widest(n2, false, real < 0);
         if (lr0 < 0 || lc0 < 0 ||
-            score(lc0, lr0, (n1 * ((1u << lc0) + 1) * sizeof(c32)) <= kHalf,
-                  (n2 << lr0) * sizeof(c32) <= kHalf, true, 2) >= best)
+            score(lc0, lr0, tile_bytes(n1, lc0, true) <= kHalf,
+                  tile_bytes(n2, lr0, false) <= kHalf, true, 4) >= best)
             continue;
-        LdsSched a, b;
-        bool most;
-        if (!lds_schedule((int)n2, &b))
+        Tile a, b;
+        if (!choose_tile((int)n2, false, 1, real < 0, &b) ||
+            !choose_tile((int)n1, true, 1 << b.l, real > 0, &a) || a.s.ns < 2)
             continue;
-        const int lr = widest(
-            [&](int l) { return lds_threads(b, 1 << l, 1, &most) ? rows_lds(b, l) : SIZE_MAX; },
-            real < 0);
-        if (lr < (real < 0 ? 1 : 0) || !lds_schedule((int)n1, &a, 1 << lr) || a.ns < 2)
-            continue;
-        const int lc = widest(
-            [&](int l) {
-                return lds_threads(a, 1 << l, 1 << lr, &most) ? columns_lds(a, l) : SIZE_MAX;
-            },
-            real > 0);
-        if (lc < (real > 0 ? 1 : 0))
-            continue;
-        const double cost = score(lc, lr, columns_lds(a, lc) <= kHalf, rows_lds(b, lr) <= kHalf,
-                                  a.st[a.ns - 1].nb % (1 << lr) == 0, a.ns + b.ns);
+        const double cost =
+            score(a.l, b.l, tile_lds(a, true) <= kHalf, tile_lds(b, false) <= kHalf,
+                  a.s.st[a.s.ns - 1].nb % (1 << b.l) == 0, a.s.ns + b.s.ns);
         if (cost >= best)
             continue;
         best = cost;
         p->passes = 2;
-        p->a = a;
-        p->b = b;
-        p->lc = lc;
-        p->lr = lr;
+        p->a = a.s;
+        p->b = b.s;
+        p->lc = a.l;
+        p->lr = b.l;
     }
     if (p->passes != 2)
         return false;
@@ -306,8 +352,16 @@ bool stages_choose(uint64_t n, uint64_t batch, int cus, StagesPlan *p, int real)
         --p->lc;
     while (p->lr > 2 && batch * ((n1 + (1u << p->lr) - 1) >> p->lr) < (uint64_t)cus)
         --p->lr;
-    p->threads_a = lds_threads(p->a, 1 << p->lc, 1 << p->lr, &p->most_a);
-    p->threads_b = lds_threads(p->b, 1 << p->lr, 1, &p->most_b);
+    Tile a, b;
+    if (!choose_form((int)n1, 1 << p->lc, 1 << p->lr, true, &a) ||
+        !choose_form((int)n2, 1 << p->lr, 1, false, &b) || a.s.ns < 2)
+        return false;
+    p->a = a.s;
+    p->form_a = a.form;
+    p->threads_a = a.threads;
+    p->b = b.s;
+    p->form_b = b.form;
+    p->threads_b = b.threads;
     // paired tiles: the columns or rows up to the middle one, half a tile's
     // slots each
     const uint64_t rows = real < 0 ? 2 * (n1 / 2 + 1) : n1;
@@ -315,53 +369,53 @@ bool stages_choose(uint64_t n, uint64_t batch, int cus, StagesPlan *p, int real)
     p->blocks_a = (unsigned)((columns + (1u << p->lc) - 1) >> p->lc);
     p->blocks_b = (unsigned)((rows + (1u << p->lr) - 1) >> p->lr);
     p->y_samples = ((uint64_t)p->blocks_b << p->lr) * n2;
-    return p->threads_a && p->threads_b;
+    return true;
 }
 
 namespace {
 
-template <int D, bool Most>
+template <int D, int F>
 hipError_t launch_segments(const StagesPlan &p, const c32 *in, c32 *out, const c32 *tw,
                            uint64_t batch, uint64_t hop, const float *window, hipStream_t s)
 {
     // the lanes' offsets within a workgroup's segments are 32-bit byte counts
     const int segs = hop < (1ull << 28) / (unsigned)p.segs ? p.segs : 1;
     const size_t lds = (size_t)segs * p.a.n * sizeof(c32);
-    const hipError_t e = allow_lds(stages_segments_kernel<D, Most>, lds);
+    const hipError_t e = allow_lds(stages_segments_kernel<D, F>, lds);
     if (e != hipSuccess)
         return e;
     const uint64_t groups = (batch + segs - 1) / segs;
-    hipLaunchKernelGGL((stages_segments_kernel<D, Most>), dim3((unsigned)groups),
+    hipLaunchKernelGGL((stages_segments_kernel<D, F>), dim3((unsigned)groups),
                        dim3(p.threads_a), (unsigned)lds, s, in, out, tw, p.a, segs, batch, hop, window);
     return hipGetLastError();
 }
 
-template <int D, bool Most>
+template <int D, int F>
 hipError_t launch_columns(const StagesPlan &p, const c32 *in, c32 *y, const c32 *tw,
                           const c32 *tl, const c32 *th, int sh, uint64_t batch, uint64_t hop,
                           const float *window, hipStream_t s)
 {
     const size_t lds = columns_lds(p.a, p.lc);
-    const hipError_t e = allow_lds(stages_columns_kernel<D, Most>, lds);
+    const hipError_t e = allow_lds(stages_columns_kernel<D, F>, lds);
     if (e != hipSuccess)
         return e;
     const unsigned blocks = p.blocks_a;
-    hipLaunchKernelGGL((stages_columns_kernel<D, Most>), dim3(xcd_grid(batch * blocks)),
+    hipLaunchKernelGGL((stages_columns_kernel<D, F>), dim3(xcd_grid(batch * blocks)),
                        dim3(p.threads_a), (unsigned)lds, s, in, y, tw, tl, th, sh, p.a, p.b.n,
                        p.lc, p.lr, blocks, batch * blocks, p.y_samples, hop, window);
     return hipGetLastError();
 }
 
-template <int D, bool Most>
+template <int D, int F>
 hipError_t launch_rows(const StagesPlan &p, const c32 *y, c32 *out, const c32 *tw,
                        uint64_t batch, hipStream_t s)
 {
     const size_t lds = rows_lds(p.b, p.lr);
-    const hipError_t e = allow_lds(stages_rows_kernel<D, Most>, lds);
+    const hipError_t e = allow_lds(stages_rows_kernel<D, F>, lds);
     if (e != hipSuccess)
         return e;
     const unsigned blocks = p.blocks_b;
-    hipLaunchKernelGGL((stages_rows_kernel<D, Most>), dim3(xcd_grid(batch * blocks)),
+    hipLaunchKernelGGL((stages_rows_kernel<D, F>), dim3(xcd_grid(batch * blocks)),
                        dim3(p.threads_b), (unsigned)lds, s, y, out, tw, p.b, p.a.n, p.lr, blocks,
                        batch * blocks, p.y_samples);
     return hipGetLastError();
@@ -373,17 +427,19 @@ hipError_t stages_one_pass(const StagesPlan &p, int dir, const void *in, void *o
                            const void *tw, uint64_t batch, uint64_t hop, const float *window,
                            hipStream_t s)
 {
-    const auto f = dir < 0 ? (p.most_a ? launch_segments<-1, true> : launch_segments<-1, false>)
-                           : (p.most_a ? launch_segments<1, true> : launch_segments<1, false>);
-    return f(p, (const c32 *)in, (c32 *)out, (const c32 *)tw, batch, hop, window, s);
+    static constexpr auto f = {launch_segments<-1, kNarrow>, launch_segments<-1, kMost>,
+                               launch_segments<-1, kWide>,   launch_segments<1, kNarrow>,
+                               launch_segments<1, kMost>,    launch_segments<1, kWide>};
+    return f.begin()[p.form_a + (dir < 0 ? 0 : 3)](p, (const c32 *)in, (c32 *)out, (const c32 *)tw, batch, hop, window, s);
 }
 
 hipError_t stages_rows(const StagesPlan &p, int dir, const void *y, void *out, const void *tw,
                        uint64_t batch, hipStream_t s)
 {
-    const auto f = dir < 0 ? (p.most_b ? launch_rows<-1, true> : launch_rows<-1, false>)
-                           : (p.most_b ? launch_rows<1, true> : launch_rows<1, false>);
-    return f(p, (const c32 *)y, (c32 *)out, (const c32 *)tw, batch, s);
+    static constexpr auto f = {launch_rows<-1, kNarrow>, launch_rows<-1, kMost>,
+                               launch_rows<-1, kWide>,   launch_rows<1, kNarrow>,
+                               launch_rows<1, kMost>,    launch_rows<1, kWide>};
+    return f.begin()[p.form_b + (dir < 0 ? 0 : 3)](p, (const c32 *)y, (c32 *)out, (const c32 *)tw, batch, s);
 }
 
 hipError_t stages_two_pass(const StagesPlan &p, int dir, const void *in, void *out, void *y,
@@ -391,9 +447,10 @@ hipError_t stages_two_pass(const StagesPlan &p, int dir, const void *in, void *o
                            int sh, uint64_t batch, uint64_t hop, const float *window,
                            hipStream_t s)
 {
-    const auto fc = dir < 0 ? (p.most_a ? launch_columns<-1, true> : launch_columns<-1, false>)
-                            : (p.most_a ? launch_columns<1, true> : launch_columns<1, false>);
-    const hipError_t e = fc(p, (const c32 *)in, (c32 *)y, (const c32 *)tw_a, (const c32 *)tl,
+    static constexpr auto f = {launch_columns<-1, kNarrow>, launch_columns<-1, kMost>,
+                               launch_columns<-1, kWide>,   launch_columns<1, kNarrow>,
+                               launch_columns<1, kMost>,    launch_columns<1, kWide>};
+    const hipError_t e = f.begin()[p.form_a + (dir < 0 ? 0 : 3)](p, (const c32 *)in, (c32 *)y, (const c32 *)tw_a, (const c32 *)tl,
                             (const c32 *)th, sh, batch, hop, window, s);
     return e == hipSuccess ? stages_rows(p, dir, y, out, tw_b, batch, s) : e;
 }

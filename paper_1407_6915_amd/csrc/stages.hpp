@@ -28,11 +28,18 @@ struct LdsSched {
     LdsStage st[kMaxLdsStages];
 };
 
-// Butterflies of one stage that a thread may own.  `most`: in the kernels
-// for tiles that 1024 threads hold only so; the others keep to the smaller
-// count, near 16 values, and to fewer registers.
-constexpr int lds_units(int r, bool most)
+// The kernels come in three forms.  kNarrow: radices up to 16 (and 25), near
+// 16 values a thread.  kMost: the same radices with more butterflies a
+// thread, for tiles that 1024 threads hold only so.  kWide: radices up to 32
+// and near 32 values a thread (column tiles: at most 512 threads, for their
+// registers): one LDS exchange where the others need two.
+enum StagesForm { kNarrow, kMost, kWide };
+
+// Butterflies of one stage that a thread may own.
+constexpr int lds_units(int r, int form)
 {
+    if (form == kWide)
+        return r <= 4 ? 8 : r == 5 ? 6 : r == 6 ? 5 : r == 8 ? 4 : r <= 10 ? 3 : r <= 16 ? 2 : 1;
     switch (r) {
     case 2: return 8;
     case 3: return 6;
@@ -40,26 +47,29 @@ constexpr int lds_units(int r, bool most)
     case 5: return 4;
     case 6: return 3;
     case 8: case 9: case 10: return 2;
-    case 12: case 15: case 16: return most ? 2 : 1;
+    case 12: case 15: case 16: return form == kMost ? 2 : 1;
     default: return 1;  // 25
     }
+}
+constexpr int form_threads(int form, bool column)
+{
+    return form == kWide && column ? 512 : 1024;
 }
 
 // The schedule of an n-point transform (n >= 2, prime factors 2, 3, 5);
 // false if it would take more than kMaxLdsStages stages.  group > 1: the
 // last stage's lanes take butterflies in groups of `group` (column pass), so
-// the last radix is the one that fills them best.
-bool lds_schedule(int n, LdsSched *s, int group = 1);
+// the last radix is the one that fills them best.  wide: radices above 16.
+bool lds_schedule(int n, LdsSched *s, bool wide, int group = 1);
 // Threads of a workgroup whose tile holds `tiles` transforms of the
 // schedule (the last stage's butterflies of each in groups of `group`);
-// 0 if 1024 threads cannot hold it.  *most: it needs the kernels compiled
-// for lds_units(r, true).
-int lds_threads(const LdsSched &s, int tiles, int group, bool *most);
+// 0 if the form's largest workgroup cannot hold it.
+int lds_threads(const LdsSched &s, int tiles, int group, int form, bool column);
 // entries of the schedule's twiddle table (s.n - first radix)
 int lds_table_size(const LdsSched &s);
 std::vector<c32> lds_table(const LdsSched &s);
-// the radices as the planner reports them: a radix-9 stage as its two
-// radix-3 steps
+// the radices as the planner reports them: radix 9, 18, 24, 27 and 30 stages
+// as their in-register steps
 void lds_radices(const LdsSched &s, std::vector<int> *out);
 
 // The plan of a length without compiled tiles.
@@ -69,7 +79,7 @@ struct StagesPlan {
     int segs = 1;            // one pass: segments per workgroup
     int lc = 0, lr = 0;      // two passes: log2 of the columns / rows per workgroup
     int threads_a = 0, threads_b = 0;
-    bool most_a = false, most_b = false;  // see lds_threads
+    int form_a = kNarrow, form_b = kNarrow;
     unsigned blocks_a = 0, blocks_b = 0;  // two passes: tiles of a segment
     int real = 0;            // real segments of 2n samples: -1 forward (the row tiles pair
                              // rows k1 and n1 - k1), +1 inverse (the column tiles pair

@@ -5,6 +5,11 @@
 #include "stages.hpp"
 #include "tile.hpp"
 
+// (a register budget of four waves per SIMD, or two for the wide columns)
+#define STAGES_KERNEL(F, COLUMN)               \
+    __launch_bounds__(form_threads(F, COLUMN)) \
+        __attribute__((amdgpu_waves_per_eu(form_threads(F, COLUMN) / 256, 4)))
+
 namespace fftseg {
 namespace stages {
 
@@ -44,11 +49,11 @@ struct Buffer {
 // transform c, gives the LDS slots of a transform's elements, and does the
 // first stage's loads (gl) and the last stage's stores (gs), unless the
 // tile is filled before (kFirstLds) or read after (kLastLds) through LDS.
-template <int R, int D, bool Most, class Io>
+template <int R, int D, int F, class Io>
 __device__ __forceinline__ void lds_stage(const Io &io, const LdsStage &st, bool gl, bool gs,
                                           c32 *lds, const Buffer &tw)
 {
-    constexpr int U = lds_units(R, Most);
+    constexpr int U = lds_units(R, F);
     c32 v[U][R];
     int bb[U], cc[U];
     bool ok[U];
@@ -117,7 +122,7 @@ __device__ __forceinline__ void lds_stage(const Io &io, const LdsStage &st, bool
         __syncthreads();
 }
 
-template <int D, bool Most, class Io>
+template <int D, int F, class Io>
 __device__ __forceinline__ void run_stages(const Io &io, const LdsSched &s, c32 *lds,
                                            const c32 *table)
 {
@@ -126,18 +131,32 @@ __device__ __forceinline__ void run_stages(const Io &io, const LdsSched &s, c32 
         const LdsStage &st = s.st[i];
         const bool gl = i == 0 && !Io::kFirstLds, gs = i + 1 == s.ns && !Io::kLastLds;
         switch (st.r) {
-        case 2: lds_stage<2, D, Most>(io, st, gl, gs, lds, tw); break;
-        case 3: lds_stage<3, D, Most>(io, st, gl, gs, lds, tw); break;
-        case 4: lds_stage<4, D, Most>(io, st, gl, gs, lds, tw); break;
-        case 5: lds_stage<5, D, Most>(io, st, gl, gs, lds, tw); break;
-        case 6: lds_stage<6, D, Most>(io, st, gl, gs, lds, tw); break;
-        case 8: lds_stage<8, D, Most>(io, st, gl, gs, lds, tw); break;
-        case 9: lds_stage<9, D, Most>(io, st, gl, gs, lds, tw); break;
-        case 10: lds_stage<10, D, Most>(io, st, gl, gs, lds, tw); break;
-        case 12: lds_stage<12, D, Most>(io, st, gl, gs, lds, tw); break;
-        case 15: lds_stage<15, D, Most>(io, st, gl, gs, lds, tw); break;
-        case 16: lds_stage<16, D, Most>(io, st, gl, gs, lds, tw); break;
-        default: lds_stage<25, D, Most>(io, st, gl, gs, lds, tw); break;
+        case 2: lds_stage<2, D, F>(io, st, gl, gs, lds, tw); break;
+        case 3: lds_stage<3, D, F>(io, st, gl, gs, lds, tw); break;
+        case 4: lds_stage<4, D, F>(io, st, gl, gs, lds, tw); break;
+        case 5: lds_stage<5, D, F>(io, st, gl, gs, lds, tw); break;
+        case 6: lds_stage<6, D, F>(io, st, gl, gs, lds, tw); break;
+        case 8: lds_stage<8, D, F>(io, st, gl, gs, lds, tw); break;
+        case 9: lds_stage<9, D, F>(io, st, gl, gs, lds, tw); break;
+        case 10: lds_stage<10, D, F>(io, st, gl, gs, lds, tw); break;
+        case 12: lds_stage<12, D, F>(io, st, gl, gs, lds, tw); break;
+        case 15: lds_stage<15, D, F>(io, st, gl, gs, lds, tw); break;
+        case 16: lds_stage<16, D, F>(io, st, gl, gs, lds, tw); break;
+        default:
+            if constexpr (F == kWide) {
+                switch (st.r) {
+                case 18: lds_stage<18, D, F>(io, st, gl, gs, lds, tw); break;
+                case 20: lds_stage<20, D, F>(io, st, gl, gs, lds, tw); break;
+                case 24: lds_stage<24, D, F>(io, st, gl, gs, lds, tw); break;
+                case 27: lds_stage<27, D, F>(io, st, gl, gs, lds, tw); break;
+                case 30: lds_stage<30, D, F>(io, st, gl, gs, lds, tw); break;
+                case 32: lds_stage<32, D, F>(io, st, gl, gs, lds, tw); break;
+                default: lds_stage<25, D, F>(io, st, gl, gs, lds, tw); break;
+                }
+            } else {
+                lds_stage<25, D, F>(io, st, gl, gs, lds, tw);
+            }
+            break;
         }
     }
 }

@@ -67,8 +67,8 @@ struct RealSegmentIo : SegmentIo {
 };
 
 // mp: reciprocal of M/2 + 1, the pairs of a segment
-template <int D, bool Most>
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
+template <int D, int F>
+__global__ void STAGES_KERNEL(F, false)
     stages_real_segments_kernel(const c32 *in, c32 *out, const c32 *__restrict__ tw,
                                 const c32 *__restrict__ hw, LdsSched s, int segs, uint32_t mp,
                                 uint64_t batch)
@@ -118,7 +118,7 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)
             });
         __syncthreads();
     }
-    run_stages<D, Most>(io, s, stage_lds, tw);
+    run_stages<D, F>(io, s, stage_lds, tw);
     if constexpr (D < 0)
         walk_pairs(total, pair, [&](int i) {
             const int k = vk[i];
@@ -135,8 +135,8 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)
 }
 
 // Columns of a forward transform: the complex pass with Y's rows in pairs.
-template <bool Most>
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
+template <int F>
+__global__ void STAGES_KERNEL(F, true)
     stages_real_columns_kernel(const c32 *in, c32 *ybuf, const c32 *__restrict__ tw,
                                const c32 *__restrict__ tl, const c32 *__restrict__ th, int sh,
                                LdsSched s, int n2, int lc, int lr, unsigned blocks,
@@ -150,14 +150,14 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)
     ColumnIo<true, false> io{in + seg * ((uint64_t)s.n * (unsigned)n2), ybuf + seg * ysamples,
                              nullptr, tl, th, nullptr, sh, n2, first, lc, lr, (unsigned)s.n};
     io.wr = column_factors(io, s);
-    run_stages<-1, Most>(io, s, stage_lds, tw);
+    run_stages<-1, F>(io, s, stage_lds, tw);
 }
 
 // Rows of a forward transform and the split: bin k = k1 + n1 k2 of row k1
 // pairs with bin n1 - k1 + n1 (n2 - 1 - k2) of row n1 - k1; row 0 and (n1
 // even) row n1/2 pair within themselves.
-template <bool Most>
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
+template <int F>
+__global__ void STAGES_KERNEL(F, false)
     stages_real_rows_kernel(const c32 *ybuf, c32 *out, const c32 *__restrict__ tw,
                             const c32 *__restrict__ w1, const c32 *__restrict__ w2, LdsSched s,
                             int n1, int lr, unsigned blocks, uint64_t tiles, uint64_t ysamples)
@@ -170,7 +170,7 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)
     const int n2 = s.n, m = n1 * n2, half = 1 << (lr - 1);
     const RowIo<true> io{ybuf + seg * ysamples + ((uint64_t)blk << lr) * (unsigned)n2,
                          out + seg * (uint64_t)(m + 1), n1, (int)blk * half, lr};
-    run_stages<-1, Most>(io, s, stage_lds, tw);
+    run_stages<-1, F>(io, s, stage_lds, tw);
     c32 wa[kAhead], wb[kAhead];
     int vk[kAhead], va[kAhead], vz[kAhead];  // k (< 0: none), slots of the pair
     walk_pairs(
@@ -204,8 +204,8 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)
 // Columns of an inverse transform and the split before them: bin i n2 + j of
 // column j pairs with bin (n1 - 1 - i) n2 + n2 - j of column n2 - j; column
 // 0 and (n2 even) column n2/2 pair within themselves.
-template <bool Most>
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
+template <int F>
+__global__ void STAGES_KERNEL(F, true)
     stages_real_inverse_columns_kernel(const c32 *in, c32 *ybuf, const c32 *__restrict__ tw,
                                        const c32 *__restrict__ tl, const c32 *__restrict__ th,
                                        int sh, const c32 *__restrict__ w1,
@@ -256,55 +256,55 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)
                 stage_lds[sz[q]] = hi;
         });
     __syncthreads();
-    run_stages<1, Most>(io, s, stage_lds, tw);
+    run_stages<1, F>(io, s, stage_lds, tw);
 }
 
-template <int D, bool Most>
+template <int D, int F>
 hipError_t launch_segments(const StagesPlan &p, const c32 *in, c32 *out, const c32 *tw,
                            const c32 *hw, uint64_t batch, hipStream_t s)
 {
     const size_t lds = (size_t)p.segs * p.a.n * sizeof(c32);
-    const hipError_t e = allow_lds(stages_real_segments_kernel<D, Most>, lds);
+    const hipError_t e = allow_lds(stages_real_segments_kernel<D, F>, lds);
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL((stages_real_segments_kernel<D, Most>),
+    hipLaunchKernelGGL((stages_real_segments_kernel<D, F>),
                        dim3((unsigned)((batch + p.segs - 1) / p.segs)), dim3(p.threads_a),
                        (unsigned)lds, s, in, out, tw, hw, p.a, p.segs, reciprocal(p.a.n / 2 + 1),
                        batch);
     return hipGetLastError();
 }
 
-template <bool Most>
+template <int F>
 hipError_t launch_columns(const StagesPlan &p, const c32 *in, c32 *y, const c32 *tw,
                           const c32 *tl, const c32 *th, int sh, const c32 *w1, const c32 *w2,
                           uint64_t batch, hipStream_t s)
 {
     const size_t lds = columns_lds(p.a, p.lc);
     const dim3 grid(xcd_grid(batch * p.blocks_a)), threads(p.threads_a);
-    hipError_t e = p.real < 0 ? allow_lds(stages_real_columns_kernel<Most>, lds)
-                              : allow_lds(stages_real_inverse_columns_kernel<Most>, lds);
+    hipError_t e = p.real < 0 ? allow_lds(stages_real_columns_kernel<F>, lds)
+                              : allow_lds(stages_real_inverse_columns_kernel<F>, lds);
     if (e != hipSuccess)
         return e;
     if (p.real < 0)
-        hipLaunchKernelGGL(stages_real_columns_kernel<Most>, grid, threads, (unsigned)lds, s, in,
+        hipLaunchKernelGGL(stages_real_columns_kernel<F>, grid, threads, (unsigned)lds, s, in,
                            y, tw, tl, th, sh, p.a, p.b.n, p.lc, p.lr, p.blocks_a,
                            batch * p.blocks_a, p.y_samples);
     else
-        hipLaunchKernelGGL(stages_real_inverse_columns_kernel<Most>, grid, threads, (unsigned)lds,
+        hipLaunchKernelGGL(stages_real_inverse_columns_kernel<F>, grid, threads, (unsigned)lds,
                            s, in, y, tw, tl, th, sh, w1, w2, p.a, p.b.n, p.lc, p.lr, p.blocks_a,
                            batch * p.blocks_a, p.y_samples);
     return hipGetLastError();
 }
 
-template <bool Most>
+template <int F>
 hipError_t launch_rows(const StagesPlan &p, const c32 *y, c32 *out, const c32 *tw, const c32 *w1,
                        const c32 *w2, uint64_t batch, hipStream_t s)
 {
     const size_t lds = rows_lds(p.b, p.lr);
-    const hipError_t e = allow_lds(stages_real_rows_kernel<Most>, lds);
+    const hipError_t e = allow_lds(stages_real_rows_kernel<F>, lds);
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL(stages_real_rows_kernel<Most>, dim3(xcd_grid(batch * p.blocks_b)),
+    hipLaunchKernelGGL(stages_real_rows_kernel<F>, dim3(xcd_grid(batch * p.blocks_b)),
                        dim3(p.threads_b), (unsigned)lds, s, y, out, tw, w1, w2, p.b, p.a.n, p.lr,
                        p.blocks_b, batch * p.blocks_b, p.y_samples);
     return hipGetLastError();
@@ -315,9 +315,10 @@ hipError_t launch_rows(const StagesPlan &p, const c32 *y, c32 *out, const c32 *t
 hipError_t stages_real_one_pass(const StagesPlan &p, const void *in, void *out, const void *tw,
                                 const void *hw, uint64_t batch, hipStream_t s)
 {
-    const auto f = p.real < 0 ? (p.most_a ? launch_segments<-1, true> : launch_segments<-1, false>)
-                              : (p.most_a ? launch_segments<1, true> : launch_segments<1, false>);
-    return f(p, (const c32 *)in, (c32 *)out, (const c32 *)tw, (const c32 *)hw, batch, s);
+    static constexpr auto f = {launch_segments<-1, kNarrow>, launch_segments<-1, kMost>,
+                               launch_segments<-1, kWide>,   launch_segments<1, kNarrow>,
+                               launch_segments<1, kMost>,    launch_segments<1, kWide>};
+    return f.begin()[p.form_a + (p.real < 0 ? 0 : 3)](p, (const c32 *)in, (c32 *)out, (const c32 *)tw, (const c32 *)hw, batch, s);
 }
 
 hipError_t stages_real_two_pass(const StagesPlan &p, const void *in, void *out, void *y,
@@ -325,15 +326,16 @@ hipError_t stages_real_two_pass(const StagesPlan &p, const void *in, void *out, 
                                 const void *th, int sh, const void *w1, const void *w2,
                                 uint64_t batch, hipStream_t s)
 {
-    const auto fc = p.most_a ? launch_columns<true> : launch_columns<false>;
-    const auto fr = p.most_b ? launch_rows<true> : launch_rows<false>;
-    const hipError_t e = fc(p, (const c32 *)in, (c32 *)y, (const c32 *)tw_a, (const c32 *)tl,
+    static constexpr auto fc = {launch_columns<kNarrow>, launch_columns<kMost>,
+                                launch_columns<kWide>};
+    static constexpr auto fr = {launch_rows<kNarrow>, launch_rows<kMost>, launch_rows<kWide>};
+    const hipError_t e = fc.begin()[p.form_a](p, (const c32 *)in, (c32 *)y, (const c32 *)tw_a, (const c32 *)tl,
                             (const c32 *)th, sh, (const c32 *)w1, (const c32 *)w2, batch, s);
     if (e != hipSuccess)
         return e;
     if (p.real > 0)
         return stages_rows(p, 1, y, out, tw_b, batch, s);
-    return fr(p, (const c32 *)y, (c32 *)out, (const c32 *)tw_b, (const c32 *)w1,
+    return fr.begin()[p.form_b](p, (const c32 *)y, (c32 *)out, (const c32 *)tw_b, (const c32 *)w1,
               (const c32 *)w2, batch, s);
 }
 

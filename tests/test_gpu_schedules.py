@@ -15,8 +15,8 @@ pytestmark = pytest.mark.gpu
 # shortest in two; odd lengths (partial lines everywhere); tiles narrower
 # than 16 columns or rows
 CASES = [(3, 5000, 1), (25, 700, 1), (243, 1000, 1), (250, 1000, 1), (270, 1000, 1),
-         (360, 4099, 1), (2187, 301, 1), (3000, 700, 1), (12288, 5, 1), (15625, 3, 1),
-         (19200, 3, 1), (18432, 3, 2), (19683, 40, 2), (78125, 5, 2), (48000, 40, 2),
+         (360, 4099, 1), (900, 500, 1), (8000, 301, 1), (2187, 301, 1), (3000, 700, 1), (12288, 5, 1), (15625, 3, 1),
+         (19683, 40, 1), (20480, 3, 1), (20736, 3, 2), (78125, 5, 2), (48000, 40, 2),
          (3 << 20, 1, 2), (1953125, 1, 2), (15625000, 1, 2), (14348907, 1, 2)]
 
 
