@@ -21,10 +21,13 @@ namespace fs {
 // per-tile LDS table (kLdsTw, ColumnPolicy); stages that reload their
 // twiddles read them as pairs (kTwPair, tw_pair_low); both passes also come
 // in a form with Y in blocks of 16 columns (kYBlocked, see kYBlock), which a
-// plan takes when its column and row tiles both have it
+// plan takes when its column and row tiles both have it; the planner's row
+// tile where the default's would leave most CUs without one (kFewTiles), or
+// up to kMidSamples samples (kMidSize)
 constexpr int kNT = 1, kNoHoist = 2, kXcd = 4, kHoistLast = 8, kW2 = 16, kPlainLane = 32,
               kSplit = 64, kW4 = 128, kW8 = 256, kFrames = 1024, kShifted = 2048,
-              kIndexed = 4096, kLdsTw = 8192, kTwPair = 16384, kYBlocked = 32768;
+              kIndexed = 4096, kLdsTw = 8192, kTwPair = 16384, kYBlocked = 32768,
+              kFewTiles = 65536, kMidSize = 131072;
 
 template <int NS, int F>
 constexpr int hoist_mask()
@@ -253,6 +256,8 @@ struct RowInst {
     static RowDesc desc(int variant)
     {
         RowDesc d{};
+        d.few_tiles = (F & kFewTiles) != 0;
+        d.mid_size = (F & kMidSize) != 0;
         d.n2 = M;
         d.variant = variant;
         d.flags = F;

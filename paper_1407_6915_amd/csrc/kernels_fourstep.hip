@@ -84,7 +84,7 @@ const RowDesc kRows[] = {
     radix32_row_desc(1, 0),
     RowInst<512, 64, 8, 4, 0, 8, 8, 8>::desc(1),
     RowInst<512, 64, 8, 4, kXcd, 8, 8, 8>::desc(2),
-    RowInst<512, 64, 8, 4, kXcd | kPlainLane, 8, 8, 8>::desc(3),
+    RowInst<512, 64, 8, 4, kXcd | kPlainLane | kFewTiles, 8, 8, 8>::desc(3),
     radix32_row_desc(2, 4),
     radix32_row_desc(4, 5),
     split_row_desc(4, 6),
@@ -94,7 +94,7 @@ const RowDesc kRows[] = {
     RowInst<1024, 64, 8, 4, kXcd, 16, 16, 4>::desc(2),
     RowInst<1024, 64, 8, 4, kNT | kXcd, 16, 16, 4>::desc(3),
     RowInst<1024, 64, 8, 4, 0, 16, 16, 4>::desc(4),
-    RowInst<1024, 64, 4, 4, kXcd, 16, 16, 4>::desc(5),
+    RowInst<1024, 64, 4, 4, kXcd | kFewTiles, 16, 16, 4>::desc(5),
     RowInst<1024, 64, 8, 4, kNT | kXcd | kHoistLast | kW2, 16, 16, 4>::desc(6),
     RowInst<1024, 64, 8, 4, kNT | kXcd | kNoHoist | kW2, 16, 16, 4>::desc(7),
     RowInst<1024, 64, 8, 4, kXcd | kPlainLane, 16, 16, 4>::desc(8),
@@ -110,7 +110,7 @@ const RowDesc kRows[] = {
     RowInst<2048, 128, 8, 4, kNoHoist | kXcd | kPlainLane, 16, 16, 8>::desc(2),
     split_row_desc(1, 3),
     RowInst<2048, 128, 8, 4, kNoHoist | kXcd | kPlainLane | kTwPair, 16, 16, 8>::desc(4),
-    RowInst<2048, 128, 8, 4, kNoHoist | kShifted, 16, 16, 8>::desc(5),
+    RowInst<2048, 128, 8, 4, kNoHoist | kShifted | kFewTiles, 16, 16, 8>::desc(5),
 };
 
 }  // namespace

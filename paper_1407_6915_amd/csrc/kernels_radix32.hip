@@ -68,8 +68,8 @@ RowDesc radix32_row_desc(int config, int variant)
     case 4:
         return RowInst<512, 16, 16, 4, kNoHoist | kXcd | kW2, 32, 16>::desc(variant);
     case 5:
-        return RowInst<1024, 32, 16, 4, kNT | kNoHoist | kXcd | kW2 | kTwPair, 32, 32>::desc(
-            variant);
+        return RowInst<1024, 32, 16, 4, kNT | kNoHoist | kXcd | kW2 | kTwPair | kMidSize, 32,
+                       32>::desc(variant);
     case 6:
         return RowInst<512, 16, 16, 4, kNoHoist | kXcd | kW2 | kTwPair, 32, 16>::desc(variant);
     default:

@@ -61,7 +61,9 @@ const SinglePassDesc kTable[] = {
     SpInst<4096, 256, 1, 0, kNT | kPlain | kAux, 16, 16, 16>::desc(3, 16),
     SpInst<4096, 512, 1, 4, kNT | kPlain | kAux, 8, 8, 8, 8>::desc(2, 64),
     SpInst<4096, 128, 2, 0, kNT | kPlain, 16, 16, 16>::desc(4, 32),
-    SpInst<4096, 256, 1, 4, kPlain, 16, 16, 16>::desc(5, 32),
+    // tiny batches: 5.9 us for one segment against 8.1 (variant 0 has half
+    // the threads and two segments a workgroup)
+    SpInst<4096, 256, 1, 4, kPlain | kTinyBatch, 16, 16, 16>::desc(5, 32),
     SpInst<4096, 256, 1, 0, kClassic | kNT, 16, 16, 16>::desc(6, 32),
     SpInst<4096, 512, 1, 4, kClassic | kNT, 8, 8, 8, 8>::desc(7, 32),
     shuffle4096_desc(8, 64, 2),

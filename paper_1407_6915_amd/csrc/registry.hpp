@@ -56,8 +56,8 @@ struct SinglePassDesc {
     int grid_mult;      // default persistent grid: resident waves of workgroups
     int lds_bytes;
     int shuffle;        // 1: an exchange between stages runs through lane shuffles
-    int small_batch;    // 1: the length's kernel for batches that give the default
-                        //    fewer than two workgroups per CU
+    int small_batch;    // > 0: the length's kernel for batches that give the default
+                        //    fewer than small_batch workgroups per eight CUs
     int nrad;
     int radices[kMaxRadices];
     sp_launch_fn launch;
@@ -91,6 +91,7 @@ struct ColumnDesc {
 // Four-step pass B: N2-point row transforms, C rows per workgroup.
 struct RowDesc {
     int n2, variant, rows, threads, lds_bytes, flags, nrad;
+    bool few_tiles, mid_size;  // the planner's choices by batch (row_for_batch)
     int radices[kMaxRadices];
     row_launch_fn launch;
     const void *kernel[2];

@@ -205,7 +205,7 @@ int tuned_grid_mult(uint64_t n, int variant, int fallback)
     return fallback;
 }
 
-void tuned_split_variants(uint64_t n, int *col_variant, int *row_variant, uint64_t *n1)
+bool tuned_split_variants(uint64_t n, int *col_variant, int *row_variant, uint64_t *n1)
 {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     for (auto &p : g_tuned)
@@ -213,8 +213,9 @@ void tuned_split_variants(uint64_t n, int *col_variant, int *row_variant, uint64
             *col_variant = p.col_variant;
             *row_variant = p.row_variant;
             *n1 = p.n1;
-            return;
+            return true;
         }
+    return false;
 }
 
 int tuned_wl_route(uint64_t n, int *grid)
@@ -417,6 +418,29 @@ int split_variant_counts(uint64_t n, int *ncol, int *nrow)
     return 1;
 }
 
+// The row tile of an untuned two-pass plan by its batch: where the default's
+// 16-row tiles would be at most a quarter of the CUs (half for 2048 points,
+// which 1024 threads hold), the length's narrow tile (one segment of 2^19
+// points 17.8 us to 14.7, of 2^21 45.7 to 29.6; at more tiles the 64-byte
+// runs cost more: four of 2^18 15.1 us to 15.9), else up to 2^26 samples the
+// length's tile for that range (1024 points: streamed loads and stores, 64
+// segments of 2^20 513 us to 478; from 2^27 on the cached tile is 1 to 5 %
+// faster).
+static const RowDesc *row_for_batch(const RowDesc *row, uint64_t n1, uint64_t batch, int cus)
+{
+    constexpr uint64_t kMidSamples = 1ull << 26;
+    const uint64_t tiles = batch * (n1 / (uint64_t)row->rows);
+    const bool few = tiles <= (uint64_t)cus / (row->n2 >= 2048 ? 2 : 4);
+    const bool mid = !few && batch * n1 * (uint64_t)row->n2 <= kMidSamples;
+    int nr = 0;
+    const RowDesc *rt = row_table(&nr);
+    for (int j = 0; (few || mid) && j < nr; ++j)
+        if (rt[j].n2 == row->n2 && (few ? rt[j].few_tiles : rt[j].mid_size) &&
+            n1 % (uint64_t)rt[j].rows == 0)
+            return &rt[j];
+    return row;
+}
+
 // CU count per device and resident workgroups per CU per kernel, cached:
 // both are fixed for the life of the process and the queries are slow.
 namespace {
@@ -531,12 +555,13 @@ int plan_choose(Plan *p, uint64_t n, uint64_t batch, int dir, int forced_variant
     if (!p->sp && forced_variant < 0)
         p->sp = find_single(n, 0);
     if (p->sp && forced_variant < 0 && tuned < 0) {
-        // a batch that gives the default kernel fewer than two workgroups
-        // per CU takes the length's small-batch kernel, if it has one
+        // a batch that gives the default kernel few workgroups (two per CU,
+        // or one per eight) takes the length's small-batch kernel, if it has
+        // one
         const SinglePassDesc *alt = find_small_batch(n);
         const uint64_t groups =
             (batch + (uint64_t)p->sp->segs_per_wg - 1) / (uint64_t)p->sp->segs_per_wg;
-        if (alt && groups < 2 * (uint64_t)device_cus(p->device))
+        if (alt && 8 * groups < (uint64_t)alt->small_batch * (uint64_t)device_cus(p->device))
             p->sp = alt;
     }
     if (forced_variant >= 0 && !p->sp)
@@ -558,6 +583,9 @@ int plan_choose(Plan *p, uint64_t n, uint64_t batch, int dir, int forced_variant
         tuned_split_variants(n, &cv, &rv, &n1);
     }
     bool split = find_split(n, &p->col, &p->row, cv, rv, n1);
+    if (split && p->by_batch && forced_split_variants < 0 && !forced_n1 &&
+        !tuned_split_variants(n, &cv, &rv, &n1))
+        p->row = row_for_batch(p->row, (uint64_t)p->col->n1, batch, device_cus(p->device));
     if (!split && n1 && !forced_n1)
         split = find_split(n, &p->col, &p->row, 0, 0, 0);  // a tuned split the library lacks
     if (!split && forced_n1)

@@ -38,6 +38,9 @@ struct Plan {
     uint64_t sub_batch = 0;
     bool y_blocked = false;     // FOURSTEP: Y in blocks of 16 columns between the passes
     int grid_mult = 0;          // 0: one workgroup per tile
+    // false (set before plan_build): kernels that do not depend on the batch,
+    // so that a segment's spectrum is the same bits in any batch
+    bool by_batch = true;
     bool used = false;
     bool last_stream_valid = false;
     hipStream_t last_stream = nullptr;
@@ -133,7 +136,7 @@ int tuned_wl_route(uint64_t n, int *grid);
 // record a work-list route for n without touching the plan choice
 void set_tuned_wl_route(uint64_t n, int route, int grid, double us);
 int tuned_grid_mult(uint64_t n, int variant, int fallback);
-void tuned_split_variants(uint64_t n, int *col_variant, int *row_variant, uint64_t *n1);
+bool tuned_split_variants(uint64_t n, int *col_variant, int *row_variant, uint64_t *n1);
 void set_tuned(const TunedChoice &c);
 void clear_tuned();
 std::vector<TunedChoice> tuned_snapshot();

@@ -868,6 +868,7 @@ int wl_reset(WorkList *w, const fft_work_t *items, size_t n, hipStream_t s)
             w->plan = nullptr;
         }
         Plan *p = new Plan();
+        p->by_batch = false;  // runs of any length give the same bits
         if ((st = plan_build(p, w->plan_len, batch, w->dir, -1)) != FFT_OK) {
             plan_free(p);
             delete p;

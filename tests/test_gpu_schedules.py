@@ -96,3 +96,38 @@ def test_real_schedules_match_oracle(n, batch):
         back = p.exec(torch.from_numpy(spec.reshape(-1)).cuda()).cpu().numpy().reshape(batch, n)
     err = np.linalg.norm(back - want, axis=1) / np.linalg.norm(want, axis=1)
     assert np.all(err <= oracle.tolerance(n)), err.max()
+
+
+@pytest.mark.parametrize("n,batch", [(1 << 17, 1), (1 << 17, 5), (1 << 18, 2), (1 << 19, 1),
+                                     (1 << 19, 5), (1 << 20, 1), (1 << 20, 3), (1 << 21, 2),
+                                     (1 << 22, 1)])
+def test_two_pass_row_tiles_by_batch(n, batch):
+    """The row tiles that small and mid-size batches of two-pass lengths take,
+    on a line and off it, as segments and as frames."""
+    import torch
+    announce("row tile by batch n=%d batch=%d" % (n, batch))
+    x = noise(n, batch, seed=n % 9973 + batch)
+    for dr in (fs.FORWARD, fs.INVERSE):
+        check(n, run(n, x, dr, inplace=dr > 0), x, dr)
+    xd = torch.zeros(n * batch + 16, dtype=torch.complex64, device="cuda")
+    xd[3:3 + n * batch] = torch.from_numpy(x.reshape(-1))
+    yd = torch.zeros_like(xd)
+    with fs.Plan(n, batch) as p:
+        p.exec(xd[3:3 + n * batch], yd[5:5 + n * batch])
+        check(n, yd[5:5 + n * batch].cpu().numpy().reshape(batch, n), x, what="off a line")
+        f = p.exec_frames(xd[3:3 + n * batch], n, n_frames=batch)
+    check(n, f.cpu().numpy().reshape(batch, n), x, what="frames")
+
+
+def test_tiny_batches_of_4096():
+    """Fewer than 63 segments of 4096 points (32 workgroups of variant 0) take a kernel with more threads
+    a segment; more, and forced variants, take variant 0."""
+    announce("tiny batches of 4096")
+    for batch, variant in [(1, 5), (62, 5), (63, 0), (64, 0)]:
+        with fs.Plan(4096, batch) as p:
+            assert p.describe()["variant"] == variant
+        x = noise(4096, batch, seed=batch)
+        for dr in (fs.FORWARD, fs.INVERSE):
+            check(4096, run(4096, x, dr), x, dr)
+    with fs.Plan(4096, 1, fs.FORWARD, 0) as p:
+        assert p.describe()["variant"] == 0
