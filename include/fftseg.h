@@ -77,7 +77,8 @@ typedef struct fftseg_plan *fft_plan_t;
  * LDS-resident pass up to 16384 samples, a two-pass "four-step" split
  * N = N1*N2 above; lengths without compiled tiles run a radix schedule
  * chosen here, in one pass where a segment fits a workgroup's LDS and in
- * two otherwise; a tuned choice
+ * two or three otherwise; two-pass lengths take their row tile by the batch;
+ * a tuned choice
  * first, and for a batch that would give the length's default one-pass
  * kernel fewer than two workgroups per CU, the length's small-batch
  * kernel where it has one), uploads the

@@ -56,8 +56,8 @@ int scratch_ptr(int dev, void **out)
 }
 
 // exp(-2 pi i m / n) in FP64, the angle folded to the first octant in exact
-// integer arithmetic (8 m < 2^28 here), rounded once to float32
-__device__ c32 device_root(uint64_t m, uint64_t n)
+// integer arithmetic (8 m < 2^28 here)
+__device__ c64 device_root(uint64_t m, uint64_t n)
 {
     m %= n;
     const uint64_t m8 = m * 8u;
@@ -75,15 +75,17 @@ __device__ c32 device_root(uint64_t m, uint64_t n)
     case 2: c = -cx; s = -sx; break;
     default: c = sx; s = -cx; break;
     }
-    return c32{(float)c, (float)(-s)};
+    return c64{c, -s};
 }
 
 // Consecutive tables: table t holds count[t] entries W_{mod[t]}^{j step[t]},
 // j < count[t], or, with rows of l[t] entries (the twiddles of one stage of
-// a run-time schedule), W_{mod[t]}^{(1 + j / l[t]) (j mod l[t])}.
-constexpr int kMaxTables = 2 + 2 * kMaxLdsStages;
+// a run-time schedule), W_{mod[t]}^{(1 + j / l[t]) (j mod l[t])}.  The first
+// `wide` tables are in FP64, the others rounded once to float32.
+constexpr int kMaxTables = 4 + 3 * kMaxLdsStages;
 struct TableSet {
     uint64_t count[kMaxTables], mod[kMaxTables], step[kMaxTables], l[kMaxTables];
+    int wide;
 };
 
 // the tables of a schedule's stages from table t on; returns the next table
@@ -103,13 +105,19 @@ __global__ void __launch_bounds__(256) static_tables_kernel(c32 *tables, TableSe
     for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < total;
          i += (uint64_t)gridDim.x * 256) {
         uint64_t j = i;
+        uint64_t at = 0;  // in float32 entries
         int t = 0;
         while (t + 1 < kMaxTables && j >= ts.count[t]) {
+            at += ts.count[t] * (t < ts.wide ? 2 : 1);
             j -= ts.count[t];
             ++t;
         }
         const uint64_t l = ts.l[t];
-        tables[i] = device_root(l ? (1 + j / l) * (j % l) : j * ts.step[t], ts.mod[t]);
+        const c64 w = device_root(l ? (1 + j / l) * (j % l) : j * ts.step[t], ts.mod[t]);
+        if (t < ts.wide)
+            reinterpret_cast<c64 *>(tables + at)[j] = w;
+        else
+            tables[at + j] = c32{(float)w.x, (float)w.y};
     }
 }
 
@@ -148,7 +156,19 @@ int noalloc_enqueue(uint64_t n, uint64_t batch, int dir, const void *in, void *o
             ts.count[2] = p.n1; ts.mod[2] = p.n1; ts.step[2] = 1;         // W_N1
             ts.count[3] = p.n2; ts.mod[3] = p.n2; ts.step[3] = 1;         // W_N2
         } else {
-            add_schedule(ts, add_schedule(ts, 2, p.stages.a), p.stages.b);
+            // the two-level tables, in FP64, before the schedules'
+            int t = 2;
+            if (p.stages.passes == 3) {
+                const uint64_t m = n / (uint64_t)p.stages.a.n;
+                p.sh2 = two_level_shift(m);
+                const uint64_t lo2 = 1ull << p.sh2;
+                ts.count[2] = lo2; ts.mod[2] = m; ts.step[2] = 1;                     // tl2
+                ts.count[3] = (m + lo2 - 1) / lo2; ts.mod[3] = m; ts.step[3] = lo2;  // th2
+                t = 4;
+            }
+            ts.wide = t;
+            add_schedule(ts, add_schedule(ts, add_schedule(ts, t, p.stages.a), p.stages.b),
+                         p.stages.mid);
         }
         break;
     }
@@ -157,10 +177,13 @@ int noalloc_enqueue(uint64_t n, uint64_t batch, int dir, const void *in, void *o
     }
     for (int t = 0; t < kMaxTables; ++t)
         total += ts.count[t];
-    if (total > kTableSamples)
+    uint64_t room = total;  // in float32 entries
+    for (int t = 0; t < ts.wide; ++t)
+        room += ts.count[t];
+    if (room > kTableSamples)
         return set_error(FFT_ERR_UNSUPPORTED_LENGTH,
                          "the tables of length %llu (%llu entries) exceed the %llu of static "
-                         "scratch", (unsigned long long)n, (unsigned long long)total,
+                         "scratch", (unsigned long long)n, (unsigned long long)room,
                          (unsigned long long)kTableSamples);
     void *base = nullptr;
     if ((st = scratch_ptr(p.device, &base)) != FFT_OK)
@@ -185,10 +208,17 @@ int noalloc_enqueue(uint64_t n, uint64_t batch, int dir, const void *in, void *o
             p.tw = tables;
             break;
         }
-        p.tl = tables;
-        p.th = tables + ts.count[0];
-        p.tw = tables + ts.count[0] + ts.count[1];
-        p.tw2 = (c32 *)p.tw + lds_table_size(p.stages.a);
+        {
+            c32 *at = tables;
+            void **wide[4] = {&p.tl, &p.th, &p.tl2, &p.th2};
+            for (int t = 0; t < ts.wide; ++t) {
+                *wide[t] = at;
+                at += 2 * ts.count[t];
+            }
+            p.tw = at;
+            p.tw2 = at + lds_table_size(p.stages.a);
+            p.w1 = (c32 *)p.tw2 + lds_table_size(p.stages.b);
+        }
         p.scratch = y;
         break;
     default: break;

@@ -21,6 +21,10 @@ struct alignas(8) c32 {
     float x, y;
 };
 
+struct alignas(16) c64 {
+    double x, y;
+};
+
 __device__ __forceinline__ c32 cadd(c32 a, c32 b) { return {a.x + b.x, a.y + b.y}; }
 __device__ __forceinline__ c32 csub(c32 a, c32 b) { return {a.x - b.x, a.y - b.y}; }
 __device__ __forceinline__ c32 cmul(c32 a, c32 b)

@@ -51,7 +51,7 @@ const char *last_message() { return t_msg; }
 // ---------------------------------------------------------------------------
 // twiddles: exp(-2 pi i m / n) in FP64 with the angle folded to the first
 // octant in exact integer arithmetic, rounded once to float32
-c32 root_forward(uint64_t m, uint64_t n)
+static c64 root_forward64(uint64_t m, uint64_t n)
 {
     m %= n;
     // angle 2 pi m / n = (pi/4) (o + r/n) with 8m = o*n + r; quadrant
@@ -73,7 +73,30 @@ c32 root_forward(uint64_t m, uint64_t n)
     case 2: c = -cx; s = -sx; break;
     default: c = sx; s = -cx; break;
     }
-    return c32{(float)c, (float)(-s)};
+    return c64{c, -s};
+}
+
+c32 root_forward(uint64_t m, uint64_t n)
+{
+    const c64 w = root_forward64(m, n);
+    return c32{(float)w.x, (float)w.y};
+}
+
+std::vector<c32> root_products(uint64_t n, uint64_t count)
+{
+    // W_n^{j + 128 h} = W_n^j W_n^{128 h}, multiplied in FP64
+    c64 low[128];
+    for (uint64_t j = 0; j < 128; ++j)
+        low[j] = root_forward64(j, n);
+    std::vector<c32> t((count + 127) / 128 * 128);
+    for (uint64_t m = 0; m < count; m += 128) {
+        const c64 h = root_forward64(m, n);
+        for (uint64_t j = 0; j < 128; ++j)
+            t[m + j] = c32{(float)(h.x * low[j].x - h.y * low[j].y),
+                           (float)(h.x * low[j].y + h.y * low[j].x)};
+    }
+    t.resize(count);
+    return t;
 }
 
 std::vector<c32> root_table(uint64_t n)
@@ -97,26 +120,37 @@ int ilog2_ceil(uint64_t v)
     return k;
 }
 
-// the two-level table of W_n: low entries W_n^j, j < 2^sh, and high ones
-// W_n^{j 2^sh}
+}  // namespace
+
 int two_level_shift(uint64_t n) { return ilog2_ceil(n) / 2 + (ilog2_ceil(n) & 1); }
 
-std::vector<c32> two_level_low(uint64_t n, int *sh)
+namespace {
+
+// the two-level table of W_n: low entries W_n^j, j < 2^sh, and high ones
+// W_n^{j 2^sh}, in float32 or (run-time schedules) in FP64, whose product is
+// rounded once
+template <class Entry>
+std::vector<c32> two_level(uint64_t n, uint64_t count, int shift, Entry root)
 {
-    *sh = two_level_shift(n);
-    std::vector<c32> t((size_t)1 << *sh);
-    for (uint64_t j = 0; j < t.size(); ++j)
-        t[j] = root_forward(j, n);
+    using E = decltype(root(0, n));
+    std::vector<c32> t((size_t)(count * sizeof(E) / sizeof(c32)));
+    for (uint64_t j = 0; j < count; ++j) {
+        const E w = root(j << shift, n);
+        std::memcpy((char *)t.data() + j * sizeof(E), &w, sizeof(E));
+    }
     return t;
 }
 
-std::vector<c32> two_level_high(uint64_t n, int sh)
-{
-    std::vector<c32> t((n + (1ull << sh) - 1) >> sh);
-    for (uint64_t j = 0; j < t.size(); ++j)
-        t[j] = root_forward(j << sh, n);
-    return t;
-}
+struct TwoLevel {
+    std::vector<c32> low, high;
+    int sh;
+    TwoLevel(uint64_t n, bool wide) : sh(two_level_shift(n))
+    {
+        const uint64_t lo = 1ull << sh, hi = (n + lo - 1) >> sh;
+        low = wide ? two_level(n, lo, 0, root_forward64) : two_level(n, lo, 0, root_forward);
+        high = wide ? two_level(n, hi, sh, root_forward64) : two_level(n, hi, sh, root_forward);
+    }
+};
 
 bool is_pow2(uint64_t v) { return v && !(v & (v - 1)); }
 
@@ -613,7 +647,7 @@ int plan_choose(Plan *p, uint64_t n, uint64_t batch, int dir, int forced_variant
             return set_error(FFT_ERR_UNSUPPORTED_LENGTH, "no schedule for length %llu",
                              (unsigned long long)n);
         p->sub_batch = std::min<uint64_t>(batch, max_sub_samples / n);
-        if (p->stages.passes == 2) {
+        if (p->stages.passes > 1) {
             // Y pads the last row tile of a segment
             if (p->sub_batch > 1)
                 p->sub_batch = std::max<uint64_t>(
@@ -650,11 +684,23 @@ int plan_build(Plan *p, uint64_t n, uint64_t batch, int dir, int forced_variant,
         return upload_tables(p, {{root_table(n), &p->tw}});
     if (!four && p->stages.passes == 1)
         return upload_tables(p, {{lds_table(p->stages.a), &p->tw}});
-    const std::vector<c32> tl = two_level_low(n, &p->sh), th = two_level_high(n, p->sh);
-    if (upload_tables(p, {{four ? root_table(p->n1) : lds_table(p->stages.a), &p->tw},
+    const TwoLevel w(n, !four);
+    p->sh = w.sh;
+    if (!four && p->stages.passes == 3) {
+        const TwoLevel w2(n / (uint64_t)p->stages.a.n, true);
+        p->sh2 = w2.sh;
+        if (upload_tables(p, {{lds_table(p->stages.a), &p->tw},
+                              {lds_table(p->stages.b), &p->tw2},
+                              {lds_table(p->stages.mid), &p->w1},
+                              {w.low, &p->tl},
+                              {w.high, &p->th},
+                              {w2.low, &p->tl2},
+                              {w2.high, &p->th2}}) != FFT_OK)
+            return last_status();
+    } else if (upload_tables(p, {{four ? root_table(p->n1) : lds_table(p->stages.a), &p->tw},
                           {four ? root_table(p->n2) : lds_table(p->stages.b), &p->tw2},
-                          {tl, &p->tl},
-                          {th, &p->th}}) != FFT_OK)
+                          {w.low, &p->tl},
+                          {w.high, &p->th}}) != FFT_OK)
         return last_status();
     hipError_t e = hipMalloc(&p->scratch, p->scratch_bytes);
     if (e != hipSuccess) {
@@ -675,18 +721,12 @@ int plan_build_real(Plan *p, uint64_t n, uint64_t batch, int dir)
         return set_error(FFT_ERR_HIP, "no HIP device available");
     }
     const uint64_t m = n / 2;
-    auto roots = [](uint64_t count, uint64_t mod) {
-        std::vector<c32> t(count);
-        for (uint64_t k = 0; k < count; ++k)
-            t[k] = root_forward(k, mod);
-        return t;
-    };
     p->sp = find_aux(m);
     if (p->sp && p->sp->launch_real) {
         // the split fused into the m-point one-pass kernel
         p->kind = Plan::REAL;
         p->grid_mult = p->sp->grid_mult;
-        return upload_tables(p, {{root_table(m), &p->tw}, {roots(m + 1, n), &p->tw2}});
+        return upload_tables(p, {{root_table(m), &p->tw}, {root_products(n, m + 1), &p->tw2}});
     }
     // a run-time schedule of the m-point transform, the split fused into it
     p->sp = nullptr;
@@ -702,18 +742,19 @@ int plan_build_real(Plan *p, uint64_t n, uint64_t batch, int dir)
     if (p->stages.passes == 1) {
         p->sub_batch = batch;
         return upload_tables(
-            p, {{lds_table(p->stages.a), &p->tw}, {roots(m / 2 + 1, n), &p->w1}});
+            p, {{lds_table(p->stages.a), &p->tw}, {root_products(n, m / 2 + 1), &p->w1}});
     }
     const uint64_t max_sub_samples = 1ull << 28;  // 2 GiB of complex64, before Y's padding
     p->sub_batch = std::max<uint64_t>(1, std::min<uint64_t>(batch, max_sub_samples / m));
     const uint64_t n1 = (uint64_t)p->stages.a.n, n2 = (uint64_t)p->stages.b.n;
-    const std::vector<c32> tl = two_level_low(m, &p->sh), th = two_level_high(m, p->sh);
+    const TwoLevel w(m, true);
+    p->sh = w.sh;
     if (upload_tables(p, {{lds_table(p->stages.a), &p->tw},
                           {lds_table(p->stages.b), &p->tw2},
-                          {tl, &p->tl},
-                          {th, &p->th},
-                          {roots((dir < 0 ? n1 : n2) / 2 + 1, n), &p->w1},
-                          {roots(dir < 0 ? n2 : n1, 2 * (dir < 0 ? n2 : n1)), &p->w2}}) != FFT_OK)
+                          {w.low, &p->tl},
+                          {w.high, &p->th},
+                          {root_products(n, (dir < 0 ? n1 : n2) / 2 + 1), &p->w1},
+                          {root_products(2 * (dir < 0 ? n2 : n1), dir < 0 ? n2 : n1), &p->w2}}) != FFT_OK)
         return last_status();
     p->scratch_bytes = p->sub_batch * p->stages.y_samples * sizeof(c32);
     if (hipMalloc(&p->scratch, p->scratch_bytes) != hipSuccess) {
@@ -749,7 +790,8 @@ void plan_free(Plan *p)
     p->graph_exec = nullptr;
     p->graph = nullptr;
     p->capture_stream = nullptr;
-    p->tables = p->tw = p->tw2 = p->tl = p->th = p->w1 = p->w2 = p->scratch = nullptr;
+    p->tables = p->tw = p->tw2 = p->tl = p->th = p->w1 = p->w2 = p->tl2 = p->th2 =
+        p->scratch = nullptr;
 }
 
 // ---------------------------------------------------------------------------
@@ -856,8 +898,8 @@ hipError_t stages_enqueue(const Plan *p, const void *in, void *out, uint64_t bat
     for (uint64_t s0 = 0; s0 < batch; s0 += p->sub_batch) {
         const hipError_t e = stages_two_pass(
             p->stages, p->dir, (const c32 *)in + s0 * hop, (c32 *)out + s0 * p->n, p->scratch,
-            p->tw, p->tw2, p->tl, p->th, p->sh, std::min(p->sub_batch, batch - s0), hop, window,
-            s);
+            {p->tw, p->tw2, p->w1, p->tl, p->th, p->sh, p->tl2, p->th2, p->sh2},
+            std::min(p->sub_batch, batch - s0), hop, window, s);
         if (e != hipSuccess)
             return e;
     }
@@ -1074,18 +1116,21 @@ int plan_describe(const Plan *p, std::string &js)
         std::vector<int> r;
         const StagesPlan &g = p->stages;
         lds_radices(g.a, &r);
-        if (g.passes == 2)
+        if (g.passes == 3)
+            lds_radices(g.mid, &r);
+        if (g.passes > 1)
             lds_radices(g.b, &r);
         snprintf(buf, sizeof buf,
                  "{\"kind\":\"radix_stages\",\"n\":%llu,\"batch\":%llu,\"direction\":%d,"
-                 "\"radices\":%s,\"passes\":%d,\"n1\":%d,\"n2\":%d,"
+                 "\"radices\":%s,\"passes\":%d,\"n1\":%d,\"n2\":%d,\"n3\":%d,"
                  "\"segments_per_workgroup\":%d,\"columns_per_workgroup\":%d,"
                  "\"rows_per_workgroup\":%d,\"threads\":[%d,%d],\"sub_batch\":%llu,"
                  "\"scratch_bytes\":%zu}",
                  (unsigned long long)p->n, (unsigned long long)p->batch, p->dir,
-                 rad(r.data(), (int)r.size()).c_str(), g.passes, g.a.n, g.passes == 2 ? g.b.n : 1,
-                 g.passes == 1 ? g.segs : 0, g.passes == 2 ? 1 << g.lc : 0,
-                 g.passes == 2 ? 1 << g.lr : 0, g.threads_a, g.threads_b,
+                 rad(r.data(), (int)r.size()).c_str(), g.passes, g.a.n,
+                 g.passes == 3 ? g.mid.n : g.passes == 2 ? g.b.n : 1, g.passes == 3 ? g.b.n : 1,
+                 g.passes == 1 ? g.segs : 0, g.passes > 1 ? 1 << g.lc : 0,
+                 g.passes > 1 ? 1 << g.lr : 0, g.threads_a, g.threads_b,
                  (unsigned long long)p->sub_batch, p->scratch_bytes);
         break;
     }
@@ -1133,7 +1178,9 @@ int factorize(uint64_t n, int *radices, int max)
         r.assign(d->radices, d->radices + d->nrad);
     } else if (n > 1 && !find_split(n, &cd, &rd, 0, 0) && stages_choose(n, 1, 1, &g)) {
         lds_radices(g.a, &r);
-        if (g.passes == 2)
+        if (g.passes == 3)
+            lds_radices(g.mid, &r);
+        if (g.passes > 1)
             lds_radices(g.b, &r);
     } else {
         r = generic_radices(n);

@@ -31,8 +31,10 @@ struct Plan {
     void *tw2 = nullptr;        // W_N2 table (four-step); W_N^k, k <= N/2 (real);
                                 // GENERIC: the row schedule's table
     void *tl = nullptr, *th = nullptr;  // two-level W_N table
-    void *w1 = nullptr, *w2 = nullptr;  // REAL_STAGES: the split's factors
-    int sh = 0;
+    // REAL_STAGES: the split's factors; GENERIC in three passes: w1 the middle
+    // schedule's table, tl2, th2 the two-level table of its rows
+    void *w1 = nullptr, *w2 = nullptr, *tl2 = nullptr, *th2 = nullptr;
+    int sh = 0, sh2 = 0;
     void *scratch = nullptr;
     size_t scratch_bytes = 0;
     uint64_t sub_batch = 0;
@@ -64,6 +66,12 @@ const char *last_message();
 c32 root_forward(uint64_t m, uint64_t n);
 // W_n^m, m < n
 std::vector<c32> root_table(uint64_t n);
+// the same for m < count from products of two FP64 roots, rounded once: a
+// sixtieth of the sines and cosines (19683 entries in 40 us where root_table
+// takes 150)
+std::vector<c32> root_products(uint64_t n, uint64_t count);
+// low bits of the index of a two-level table of W_n
+int two_level_shift(uint64_t n);
 const SinglePassDesc *find_single(uint64_t n, int variant);
 const SinglePassDesc *find_aux(uint64_t n);
 // the length's default frame kernel: the first row of n with one

@@ -44,7 +44,7 @@ __global__ void STAGES_KERNEL(F, false)
 template <int D, int F>
 __global__ void STAGES_KERNEL(F, true)
     stages_columns_kernel(const c32 *in, c32 *ybuf, const c32 *__restrict__ tw,
-                          const c32 *__restrict__ tl, const c32 *__restrict__ th, int sh,
+                          const c64 *__restrict__ tl, const c64 *__restrict__ th, int sh,
                           LdsSched s, int n2, int lc, int lr, unsigned blocks, uint64_t tiles,
                           uint64_t ysamples, uint64_t hop, const float *__restrict__ window)
 {
@@ -60,17 +60,45 @@ __global__ void STAGES_KERNEL(F, true)
 }
 
 template <int D, int F>
-__global__ void STAGES_KERNEL(F, false)
-    stages_rows_kernel(const c32 *ybuf, c32 *out, const c32 *__restrict__ tw, LdsSched s, int n1,
-                       int lr, unsigned blocks, uint64_t tiles, uint64_t ysamples)
+__global__ void STAGES_KERNEL(F, true)
+    stages_middle_columns_kernel(c32 *ybuf, const c32 *__restrict__ tw,
+                                 const c64 *__restrict__ tl, const c64 *__restrict__ th, int sh,
+                                 LdsSched s, int n1, int n3, int lr, unsigned blocks,
+                                 uint64_t tiles, uint64_t ysamples)
 {
+    // (tile = (segment, row block, column j), j fastest)
     const uint64_t t = xcd_tile();
     if (t >= tiles)
         return;
-    const uint64_t seg = t / blocks;
-    const unsigned blk = (unsigned)(t - seg * blocks);
-    const RowIo<false> io{ybuf + seg * ysamples + ((uint64_t)blk << lr) * (unsigned)s.n,
-                   out + seg * ((uint64_t)n1 * (unsigned)s.n), n1, (int)(blk << lr), lr};
+    const uint64_t q = t / (unsigned)n3, seg = q / blocks;
+    const int j = (int)(t - q * (unsigned)n3), blk = (int)(q - seg * blocks);
+    c32 *wr = stage_lds + ((unsigned)s.n << lr);
+    MiddleIo io{ybuf + seg * ysamples +
+                    (((uint64_t)blk * (unsigned)s.n * (unsigned)n3 + (unsigned)j) << lr),
+                tl, th, wr, sh, n3, j, n1 - (blk << lr), lr};
+    const LdsStage &last = s.st[s.ns - 1];
+    if ((int)threadIdx.x < last.r)
+        wr[threadIdx.x] = io.root((unsigned)j * (threadIdx.x * (unsigned)last.nb));
+    run_stages<D, F>(io, s, stage_lds, tw);
+}
+
+// n2: rows of s.n points that a row of Y consists of (1 in two passes)
+template <int D, int F>
+__global__ void STAGES_KERNEL(F, false)
+    stages_rows_kernel(const c32 *ybuf, c32 *out, const c32 *__restrict__ tw, LdsSched s, int n1,
+                       int n2, int lr, unsigned blocks, uint64_t tiles, uint64_t ysamples)
+{
+    // (tile = (segment, k2, row block), the block fastest: neighbours share
+    // the output's lines where n1 is no multiple of 16)
+    const uint64_t t = xcd_tile();
+    if (t >= tiles)
+        return;
+    const uint64_t q = t / blocks, seg = q / (unsigned)n2;
+    const unsigned blk = (unsigned)(t - q * blocks), k2 = (unsigned)(q - seg * (unsigned)n2);
+    const RowIo<false> io{
+        ybuf + seg * ysamples + (((uint64_t)blk * (unsigned)n2 + k2) << lr) * (unsigned)s.n,
+        out + seg * ((uint64_t)n1 * (unsigned)n2 * (unsigned)s.n) + (uint64_t)k2 * (unsigned)n1,
+        n1, (int)(blk << lr), lr, n1 * n2};
     run_stages<D, F>(io, s, stage_lds, tw);
 }
 
@@ -95,7 +123,11 @@ void best_radices(int n, int from, bool wide, std::vector<int> &cur, std::vector
             best = cur;
         return;
     }
-    if (!best.empty() && cur.size() + 1 > best.size())
+    // (radices do not increase: at least this many more)
+    size_t need = 0;
+    for (int left = n; left > 1; left = (left + kRadixList[from] - 1) / kRadixList[from])
+        ++need;
+    if (!best.empty() && cur.size() + need > best.size())
         return;
     for (int i = from; i < (int)(sizeof(kRadixList) / sizeof(kRadixList[0])); ++i) {
         // (one stage of a composite length would put the lanes of a load n
@@ -178,7 +210,7 @@ int lds_table_size(const LdsSched &s)
 std::vector<c32> lds_table(const LdsSched &s)
 {
     std::vector<c32> t((size_t)std::max(lds_table_size(s), 1));
-    const std::vector<c32> w = root_table((uint64_t)s.n);
+    const std::vector<c32> w = root_products((uint64_t)s.n, (uint64_t)s.n);
     for (int i = 1; i < s.ns; ++i) {
         const LdsStage &st = s.st[i];
         c32 *to = &t[(size_t)st.tw];
@@ -259,6 +291,65 @@ bool choose_tile(int n, bool column, int group, bool paired, Tile *t)
                 tile_lds(*t, column) <= (size_t)kLdsBytes / fill)
                 return true;
     return false;
+}
+
+// n = n1 n2 n3 with tiles of 16 that leave room for two workgroups a CU in
+// all three passes, if that costs less than `best` (the units of
+// stages_choose; the factors fit the sum to whole transforms)
+void choose_three(uint64_t n, double best, StagesPlan *p)
+{
+    // lengths near the cube root: 85 to 435 points at 2^24
+    const double third = std::cbrt((double)n);
+    const uint64_t least = (uint64_t)(third / 3), most = (uint64_t)(third * 1.7);
+    struct Known {
+        uint64_t n;
+        Tile column, row;
+        bool ok;
+    };
+    std::vector<Known> known;
+    for (uint64_t m = std::max<uint64_t>(least, 32); m <= most; ++m) {
+        if (n % m)
+            continue;
+        Known k{m, {}, {}, false};
+        k.column.l = k.row.l = 4;
+        k.ok = choose_form((int)m, 16, 16, true, &k.column) && k.column.s.ns >= 2 &&
+               choose_form((int)m, 16, 1, false, &k.row) && k.row.s.ns >= 2;
+        known.push_back(k);
+    }
+    for (const Known &a : known)
+        for (const Known &c : known) {
+            if (!a.ok || !c.ok || n / a.n % c.n)
+                continue;
+            const uint64_t n2 = n / a.n / c.n;
+            for (const Known &m : known) {
+                if (m.n != n2 || !m.ok)
+                    continue;
+                const double cost =
+                    ((a.column.s.st[a.column.s.ns - 1].nb % 16 ? 1.25 : 1) *
+                         (n / a.n % 16 ? 1.08 : 1) +
+                     0.95 + 0.9 * (a.n % 16 ? 1.15 : 1) +
+                     0.12 * (a.column.s.ns + m.row.s.ns + c.row.s.ns) +
+                     0.1 * std::log2((double)std::max({a.n, c.n, n2}) / 256.0 + 1)) *
+                    (a.n % 16 ? 0.95 : 0.85);
+                if (cost >= best)
+                    continue;
+                Tile mid;
+                if (!choose_form((int)n2, 16, 1, true, &mid) || mid.s.ns < 2)
+                    continue;
+                best = cost;
+                p->passes = 3;
+                p->a = a.column.s;
+                p->form_a = a.column.form;
+                p->threads_a = a.column.threads;
+                p->mid = mid.s;
+                p->form_mid = mid.form;
+                p->threads_mid = mid.threads;
+                p->b = c.row.s;
+                p->form_b = c.row.form;
+                p->threads_b = c.row.threads;
+                p->lc = p->lr = 4;
+            }
+        }
 }
 
 }  // namespace
@@ -344,6 +435,23 @@ bool stages_choose(uint64_t n, uint64_t batch, int cus, StagesPlan *p, int real)
         p->lc = a.l;
         p->lr = b.l;
     }
+    // three passes of short tiles, where the long tiles of two cost more: 2^24
+    // as 256 x 256 x 256 moves half as much again at twice the rate (2^26
+    // samples: 870 us to 648, 2^23 816 to 653, 12 10^6 738 to 609; not where
+    // the two lengths are odd or near 2000: 8 10^6 636 us against 669).  Two
+    // passes are a fifth faster than their sum says where the strides are no
+    // multiples of 8 KB.
+    if (!real && best > 3.2) {
+        const bool far = p->a.n % 1024 == 0 && p->b.n % 1024 == 0;
+        choose_three(n, best * (far ? 1 : 0.8), p);
+    }
+    if (p->passes == 3) {
+        const uint64_t n1 = (uint64_t)p->a.n, m = n / n1;
+        p->blocks_a = (unsigned)((m + (1u << p->lc) - 1) >> p->lc);
+        p->blocks_b = (unsigned)((n1 + (1u << p->lr) - 1) >> p->lr);
+        p->y_samples = ((uint64_t)p->blocks_b << p->lr) * m;
+        return true;
+    }
     if (p->passes != 2)
         return false;
     // few segments: narrower tiles until every CU has one
@@ -392,7 +500,7 @@ hipError_t launch_segments(const StagesPlan &p, const c32 *in, c32 *out, const c
 
 template <int D, int F>
 hipError_t launch_columns(const StagesPlan &p, const c32 *in, c32 *y, const c32 *tw,
-                          const c32 *tl, const c32 *th, int sh, uint64_t batch, uint64_t hop,
+                          const c64 *tl, const c64 *th, int sh, uint64_t batch, uint64_t hop,
                           const float *window, hipStream_t s)
 {
     const size_t lds = columns_lds(p.a, p.lc);
@@ -400,8 +508,9 @@ hipError_t launch_columns(const StagesPlan &p, const c32 *in, c32 *y, const c32 
     if (e != hipSuccess)
         return e;
     const unsigned blocks = p.blocks_a;
+    const int n2 = p.passes == 3 ? p.mid.n * p.b.n : p.b.n;
     hipLaunchKernelGGL((stages_columns_kernel<D, F>), dim3(xcd_grid(batch * blocks)),
-                       dim3(p.threads_a), (unsigned)lds, s, in, y, tw, tl, th, sh, p.a, p.b.n,
+                       dim3(p.threads_a), (unsigned)lds, s, in, y, tw, tl, th, sh, p.a, n2,
                        p.lc, p.lr, blocks, batch * blocks, p.y_samples, hop, window);
     return hipGetLastError();
 }
@@ -415,9 +524,27 @@ hipError_t launch_rows(const StagesPlan &p, const c32 *y, c32 *out, const c32 *t
     if (e != hipSuccess)
         return e;
     const unsigned blocks = p.blocks_b;
-    hipLaunchKernelGGL((stages_rows_kernel<D, F>), dim3(xcd_grid(batch * blocks)),
-                       dim3(p.threads_b), (unsigned)lds, s, y, out, tw, p.b, p.a.n, p.lr, blocks,
-                       batch * blocks, p.y_samples);
+    const int n2 = p.passes == 3 ? p.mid.n : 1;
+    const uint64_t tiles = batch * blocks * (unsigned)n2;
+    hipLaunchKernelGGL((stages_rows_kernel<D, F>), dim3(xcd_grid(tiles)), dim3(p.threads_b),
+                       (unsigned)lds, s, y, out, tw, p.b, p.a.n, n2, p.lr, blocks, tiles,
+                       p.y_samples);
+    return hipGetLastError();
+}
+
+template <int D, int F>
+hipError_t launch_middle(const StagesPlan &p, c32 *y, const c32 *tw, const c64 *tl,
+                         const c64 *th, int sh, uint64_t batch, hipStream_t s)
+{
+    const size_t lds =
+        rows_lds(p.mid, p.lr) + (size_t)p.mid.st[p.mid.ns - 1].r * sizeof(c32);
+    const hipError_t e = allow_lds(stages_middle_columns_kernel<D, F>, lds);
+    if (e != hipSuccess)
+        return e;
+    const uint64_t tiles = batch * p.blocks_b * (unsigned)p.b.n;
+    hipLaunchKernelGGL((stages_middle_columns_kernel<D, F>), dim3(xcd_grid(tiles)),
+                       dim3(p.threads_mid), (unsigned)lds, s, y, tw, tl, th, sh, p.mid, p.a.n,
+                       p.b.n, p.lr, p.blocks_b, tiles, p.y_samples);
     return hipGetLastError();
 }
 
@@ -443,16 +570,23 @@ hipError_t stages_rows(const StagesPlan &p, int dir, const void *y, void *out, c
 }
 
 hipError_t stages_two_pass(const StagesPlan &p, int dir, const void *in, void *out, void *y,
-                           const void *tw_a, const void *tw_b, const void *tl, const void *th,
-                           int sh, uint64_t batch, uint64_t hop, const float *window,
-                           hipStream_t s)
+                           const StagesTables &t, uint64_t batch, uint64_t hop,
+                           const float *window, hipStream_t s)
 {
     static constexpr auto f = {launch_columns<-1, kNarrow>, launch_columns<-1, kMost>,
                                launch_columns<-1, kWide>,   launch_columns<1, kNarrow>,
                                launch_columns<1, kMost>,    launch_columns<1, kWide>};
-    const hipError_t e = f.begin()[p.form_a + (dir < 0 ? 0 : 3)](p, (const c32 *)in, (c32 *)y, (const c32 *)tw_a, (const c32 *)tl,
-                            (const c32 *)th, sh, batch, hop, window, s);
-    return e == hipSuccess ? stages_rows(p, dir, y, out, tw_b, batch, s) : e;
+    static constexpr auto fm = {launch_middle<-1, kNarrow>, launch_middle<-1, kMost>,
+                                launch_middle<-1, kWide>,   launch_middle<1, kNarrow>,
+                                launch_middle<1, kMost>,    launch_middle<1, kWide>};
+    hipError_t e = f.begin()[p.form_a + (dir < 0 ? 0 : 3)](
+        p, (const c32 *)in, (c32 *)y, (const c32 *)t.a, (const c64 *)t.tl, (const c64 *)t.th,
+        t.sh, batch, hop, window, s);
+    if (e == hipSuccess && p.passes == 3)
+        e = fm.begin()[p.form_mid + (dir < 0 ? 0 : 3)](p, (c32 *)y, (const c32 *)t.mid,
+                                                       (const c64 *)t.tl2, (const c64 *)t.th2,
+                                                       t.sh2, batch, s);
+    return e == hipSuccess ? stages_rows(p, dir, y, out, t.b, batch, s) : e;
 }
 
 }  // namespace fftseg

@@ -74,17 +74,20 @@ void lds_radices(const LdsSched &s, std::vector<int> *out);
 
 // The plan of a length without compiled tiles.
 struct StagesPlan {
-    int passes = 0;          // 1: whole segments in LDS; 2: columns, then rows
+    // 1: whole segments in LDS; 2: columns, then rows; 3: columns, then the
+    // rows themselves in two passes
+    int passes = 0;
     LdsSched a{}, b{};       // the pass (or column pass), the row pass
+    LdsSched mid{};          // three passes: the one between
     int segs = 1;            // one pass: segments per workgroup
     int lc = 0, lr = 0;      // two passes: log2 of the columns / rows per workgroup
     int threads_a = 0, threads_b = 0;
-    int form_a = kNarrow, form_b = kNarrow;
+    int form_a = kNarrow, form_b = kNarrow, form_mid = kNarrow, threads_mid = 0;
     unsigned blocks_a = 0, blocks_b = 0;  // two passes: tiles of a segment
     int real = 0;            // real segments of 2n samples: -1 forward (the row tiles pair
                              // rows k1 and n1 - k1), +1 inverse (the column tiles pair
                              // columns)
-    uint64_t y_samples = 0;  // two passes: samples of Y per segment
+    uint64_t y_samples = 0;  // two and three passes: samples of Y per segment
 };
 // false if the length has no plan (none of the supported lengths)
 bool stages_choose(uint64_t n, uint64_t batch, int cus, StagesPlan *p, int real = 0);
@@ -94,10 +97,16 @@ bool stages_choose(uint64_t n, uint64_t batch, int cus, StagesPlan *p, int real 
 hipError_t stages_one_pass(const StagesPlan &p, int dir, const void *in, void *out,
                            const void *tw, uint64_t batch, uint64_t hop, const float *window,
                            hipStream_t s);
+struct StagesTables {          // device addresses
+    const void *a, *b, *mid;   // the schedules' twiddles
+    const void *tl, *th;       // two-level W_n (c64)
+    int sh;
+    const void *tl2, *th2;     // three passes: two-level W_{n / n1}
+    int sh2;
+};
 hipError_t stages_two_pass(const StagesPlan &p, int dir, const void *in, void *out, void *y,
-                           const void *tw_a, const void *tw_b, const void *tl, const void *th,
-                           int sh, uint64_t batch, uint64_t hop, const float *window,
-                           hipStream_t s);
+                           const StagesTables &t, uint64_t batch, uint64_t hop,
+                           const float *window, hipStream_t s);
 
 hipError_t stages_rows(const StagesPlan &p, int dir, const void *y, void *out, const void *tw,
                        uint64_t batch, hipStream_t s);

@@ -161,6 +161,15 @@ __device__ __forceinline__ void run_stages(const Io &io, const LdsSched &s, c32 
     }
 }
 
+// W^m from its two-level table: two FP64 entries, their product rounded once
+// (a factor in float32 took three roundings: 2^24 points with three unit
+// tones were 3.3e-7 off, now 2.8e-7).
+__device__ __forceinline__ c32 two_level_root(const c64 *tl, const c64 *th, int sh, unsigned m)
+{
+    const c64 a = th[m >> sh], b = tl[m & ((1u << sh) - 1u)];
+    return {(float)(a.x * b.x - a.y * b.y), (float)(a.x * b.y + a.y * b.x)};
+}
+
 // Whole segments: transform c is segment c of the tile, its elements in
 // consecutive slots; butterflies of a segment on consecutive lanes, so the
 // first stage loads and the last stage stores runs of nb samples.
@@ -233,14 +242,14 @@ struct ColumnIo {
     const c32 *x;
     c32 *y;
     const float *window;
-    const c32 *__restrict__ tl;
-    const c32 *__restrict__ th;
+    const c64 *__restrict__ tl;
+    const c64 *__restrict__ th;
     const c32 *wr;  // LDS: W_N^{n2 r nb} of the last stage's outputs, [r][column]
     int sh, n2, first, lc, lr;
     unsigned n1;
     __device__ __forceinline__ c32 root(unsigned m) const
     {
-        return cmul(th[m >> sh], tl[m & ((1u << sh) - 1u)]);
+        return two_level_root(tl, th, sh, m);
     }
     __device__ __forceinline__ bool map(const LdsStage &st, bool gs, int g, int &b, int &c) const
     {
@@ -324,6 +333,8 @@ struct ColumnIo {
 
 // Four-step row pass: transform c is row first + c of Y (one contiguous tile,
 // the rows on consecutive lanes), stored transposed as X[k1 + n1 k2].
+// Row k2 of the n2 that a three-pass row consists of starts k2 n1 samples
+// into the output (y), with outputs n1 n2 apart (`stride`; n1 in two passes).
 // Pair: the tile of rows first + c and n1 - (first + c) (see ColumnIo), left
 // in LDS by the last stage.
 template <bool Pair>
@@ -331,7 +342,7 @@ struct RowIo {
     static constexpr bool kFirstLds = false, kLastLds = Pair;
     const c32 *x;  // the tile
     c32 *y;        // segment output
-    int n1, first, lr;
+    int n1, first, lr, stride;
     template <int R, int D>
     __device__ __forceinline__ void finish(c32 *, int, int, int) const
     {
@@ -365,11 +376,62 @@ struct RowIo {
     __device__ __forceinline__ void store(const c32 *v, int b, int c, int nb) const
     {
         const Buffer yb(y);
-        const unsigned at = 8u * (unsigned)(b * n1 + first + c);
-        const int d = nb * n1;
+        const unsigned at = 8u * (unsigned)(b * stride + first + c);
+        const int d = nb * stride;
 #pragma unroll
         for (int r = 0; r < R; ++r)
             yb.store(at, r * d, v[r]);
+    }
+};
+
+// Middle pass of a three-pass transform n = n1 n2 n3: the row k1 of Y is
+// transformed as n2 x n3, its n2-point columns here.  Y keeps 2^lr rows
+// together, Y[(k1 >> lr)][i n3 + j][k1 mod 2^lr], so the tile of one column j
+// of those rows moves whole runs of 2^lr samples, and goes back in place.
+struct MiddleIo {
+    static constexpr bool kFirstLds = false, kLastLds = false;
+    c32 *y;  // row block, column j
+    const c64 *__restrict__ tl;
+    const c64 *__restrict__ th;
+    const c32 *wr;  // LDS: W_{n2 n3}^{j r nb} of the last stage's outputs
+    int sh, n3, j, rows, lr;  // rows the block holds
+    __device__ __forceinline__ c32 root(unsigned m) const
+    {
+        return two_level_root(tl, th, sh, m);
+    }
+    __device__ __forceinline__ bool map(const LdsStage &st, bool, int g, int &b, int &c) const
+    {
+        c = g & ((1 << lr) - 1);
+        b = g >> lr;
+        return b < st.nb && c < rows;
+    }
+    __device__ __forceinline__ int step() const { return 1 << lr; }
+    __device__ __forceinline__ int slot(int i, int c) const { return (i << lr) + c; }
+    template <int R>
+    __device__ __forceinline__ void load(c32 *v, int b, int c, int nb) const
+    {
+        const Buffer yb(y);
+        const unsigned at = 8u * (unsigned)(((b * n3) << lr) + c);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            v[r] = yb.load(at, (r * nb * n3) << lr);
+    }
+    template <int R>
+    __device__ __forceinline__ void store(const c32 *v, int b, int c, int nb) const
+    {
+        const Buffer yb(y);
+        const unsigned at = 8u * (unsigned)(((b * n3) << lr) + c);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            yb.store(at, (r * nb * n3) << lr, v[r]);
+    }
+    template <int R, int D>
+    __device__ __forceinline__ void finish(c32 *v, int b, int, int) const
+    {
+        const c32 wb = root((unsigned)j * (unsigned)b);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            v[r] = twiddle<D>(v[r], cmul(wb, wr[r]));
     }
 };
 

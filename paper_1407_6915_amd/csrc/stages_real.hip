@@ -138,7 +138,7 @@ __global__ void STAGES_KERNEL(F, false)
 template <int F>
 __global__ void STAGES_KERNEL(F, true)
     stages_real_columns_kernel(const c32 *in, c32 *ybuf, const c32 *__restrict__ tw,
-                               const c32 *__restrict__ tl, const c32 *__restrict__ th, int sh,
+                               const c64 *__restrict__ tl, const c64 *__restrict__ th, int sh,
                                LdsSched s, int n2, int lc, int lr, unsigned blocks,
                                uint64_t tiles, uint64_t ysamples)
 {
@@ -169,7 +169,7 @@ __global__ void STAGES_KERNEL(F, false)
     const unsigned blk = (unsigned)(t - seg * blocks);
     const int n2 = s.n, m = n1 * n2, half = 1 << (lr - 1);
     const RowIo<true> io{ybuf + seg * ysamples + ((uint64_t)blk << lr) * (unsigned)n2,
-                         out + seg * (uint64_t)(m + 1), n1, (int)blk * half, lr};
+                         out + seg * (uint64_t)(m + 1), n1, (int)blk * half, lr, n1};
     run_stages<-1, F>(io, s, stage_lds, tw);
     c32 wa[kAhead], wb[kAhead];
     int vk[kAhead], va[kAhead], vz[kAhead];  // k (< 0: none), slots of the pair
@@ -207,7 +207,7 @@ __global__ void STAGES_KERNEL(F, false)
 template <int F>
 __global__ void STAGES_KERNEL(F, true)
     stages_real_inverse_columns_kernel(const c32 *in, c32 *ybuf, const c32 *__restrict__ tw,
-                                       const c32 *__restrict__ tl, const c32 *__restrict__ th,
+                                       const c64 *__restrict__ tl, const c64 *__restrict__ th,
                                        int sh, const c32 *__restrict__ w1,
                                        const c32 *__restrict__ w2, LdsSched s, int n2, int lc,
                                        int lr, unsigned blocks, uint64_t tiles,
@@ -276,7 +276,7 @@ hipError_t launch_segments(const StagesPlan &p, const c32 *in, c32 *out, const c
 
 template <int F>
 hipError_t launch_columns(const StagesPlan &p, const c32 *in, c32 *y, const c32 *tw,
-                          const c32 *tl, const c32 *th, int sh, const c32 *w1, const c32 *w2,
+                          const c64 *tl, const c64 *th, int sh, const c32 *w1, const c32 *w2,
                           uint64_t batch, hipStream_t s)
 {
     const size_t lds = columns_lds(p.a, p.lc);
@@ -329,8 +329,8 @@ hipError_t stages_real_two_pass(const StagesPlan &p, const void *in, void *out, 
     static constexpr auto fc = {launch_columns<kNarrow>, launch_columns<kMost>,
                                 launch_columns<kWide>};
     static constexpr auto fr = {launch_rows<kNarrow>, launch_rows<kMost>, launch_rows<kWide>};
-    const hipError_t e = fc.begin()[p.form_a](p, (const c32 *)in, (c32 *)y, (const c32 *)tw_a, (const c32 *)tl,
-                            (const c32 *)th, sh, (const c32 *)w1, (const c32 *)w2, batch, s);
+    const hipError_t e = fc.begin()[p.form_a](p, (const c32 *)in, (c32 *)y, (const c32 *)tw_a, (const c64 *)tl,
+                            (const c64 *)th, sh, (const c32 *)w1, (const c32 *)w2, batch, s);
     if (e != hipSuccess)
         return e;
     if (p.real > 0)
