@@ -82,20 +82,20 @@ c32 root_forward(uint64_t m, uint64_t n)
     return c32{(float)w.x, (float)w.y};
 }
 
+RootProducts::RootProducts(uint64_t n, uint64_t count) : low(128), high(count / 128 + 1)
+{
+    for (uint64_t j = 0; j < low.size(); ++j)
+        low[j] = root_forward64(j, n);
+    for (uint64_t j = 0; j < high.size(); ++j)
+        high[j] = root_forward64(128 * j, n);
+}
+
 std::vector<c32> root_products(uint64_t n, uint64_t count)
 {
-    // W_n^{j + 128 h} = W_n^j W_n^{128 h}, multiplied in FP64
-    c64 low[128];
-    for (uint64_t j = 0; j < 128; ++j)
-        low[j] = root_forward64(j, n);
-    std::vector<c32> t((count + 127) / 128 * 128);
-    for (uint64_t m = 0; m < count; m += 128) {
-        const c64 h = root_forward64(m, n);
-        for (uint64_t j = 0; j < 128; ++j)
-            t[m + j] = c32{(float)(h.x * low[j].x - h.y * low[j].y),
-                           (float)(h.x * low[j].y + h.y * low[j].x)};
-    }
-    t.resize(count);
+    const RootProducts w(n, count);
+    std::vector<c32> t(count);
+    for (uint64_t m = 0; m < count; ++m)
+        t[m] = w[m];
     return t;
 }
 

@@ -210,14 +210,14 @@ int lds_table_size(const LdsSched &s)
 std::vector<c32> lds_table(const LdsSched &s)
 {
     std::vector<c32> t((size_t)std::max(lds_table_size(s), 1));
-    const std::vector<c32> w = root_products((uint64_t)s.n, (uint64_t)s.n);
+    const RootProducts w((uint64_t)s.n, (uint64_t)s.n);
     for (int i = 1; i < s.ns; ++i) {
         const LdsStage &st = s.st[i];
         c32 *to = &t[(size_t)st.tw];
         for (int j = 1; j < st.r; ++j) {
             const int step = j * (s.n / (st.l * st.r));  // j k step < n
             for (int k = 0; k < st.l; ++k)
-                *to++ = w[(size_t)k * step];
+                *to++ = w[(uint64_t)k * step];
         }
     }
     return t;

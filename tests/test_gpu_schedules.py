@@ -133,3 +133,15 @@ def test_tiny_batches_of_4096():
             check(4096, run(4096, x, dr), x, dr)
     with fs.Plan(4096, 1, fs.FORWARD, 0) as p:
         assert p.describe()["variant"] == 0
+
+
+def test_default_stream_is_the_current_one():
+    """Without a stream argument a call goes to torch's current stream of the
+    current device, also inside a stream context."""
+    import torch
+    announce("current stream")
+    assert fs._stream_handle(None) == torch.cuda.current_stream().cuda_stream
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        assert fs._stream_handle(None) == s.cuda_stream != 0
+    assert fs._stream_handle(None) == torch.cuda.current_stream().cuda_stream
