@@ -323,7 +323,8 @@ int fft_worklist_supported(uint32_t segment_len);
  * one-pass kernels; 65536: 1, its two passes as launches of their own; 0
  * for 16384, 2^20 and unsupported lengths.  Route 0 is the tiles, route
  * 1 + k the k-th indexed kernel; fft_autotune picks one per length,
- * untuned one-pass lengths take route 1, untuned 65536 route 0. */
+ * untuned one-pass lengths take route 1, and so does untuned 65536 up to
+ * 4096 segments in a list (route 0 above). */
 int fft_worklist_indexed_count(uint32_t segment_len);
 
 /* Compile n entries into workgroup tasks: segments are grouped by length,

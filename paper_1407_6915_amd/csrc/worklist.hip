@@ -324,10 +324,13 @@ int route_of(uint32_t n, int *grid_mult)
 
 // Route of a two-pass length: 0 = column and row tasks of the work-list
 // kernel, 1 = the two passes over the listed segments as launches of their
-// own (the plan's tiles, indexed).  Tuned, else 0: on the uneven workload
-// (65536-point segments packed at unaligned offsets among others) the
-// tasks took 12.1 ms and the indexed passes 13.7.
-int route_two_pass(uint32_t n, int *grid_mult)
+// own (the plan's tiles, indexed; the tasks' arithmetic, so the bits are the
+// same).  Tuned, else 1 up to kIndexedTwoPass segments, one workgroup per
+// tile, and 0 above (lists of seven lengths in equal numbers: 570 segments of
+// 65536 points 390 us by tasks, 309 indexed; 4570 2.30 ms and 2.19; 9140
+// 4.42 and 5.65).
+constexpr size_t kIndexedTwoPass = 4096;
+int route_two_pass(uint32_t n, size_t count, int *grid_mult)
 {
     *grid_mult = 0;
     const ColumnDesc *c = nullptr;
@@ -339,7 +342,7 @@ int route_two_pass(uint32_t n, int *grid_mult)
         *grid_mult = g;
         return t;
     }
-    return 0;
+    return have && count <= kIndexedTwoPass ? 1 : 0;
 }
 
 }  // namespace wl
@@ -713,7 +716,7 @@ int wl_compile(WorkList *w, const fft_work_t *items, size_t n, std::vector<wl::T
             for (uint32_t idx : b)
                 wide_items.push_back({items[idx].in_off, items[idx].out_off, 0});
             counts[L.a] += b.size();
-        } else if (int gm = 0, r = route_two_pass(L.n, &gm); L.two_pass && r == 1) {
+        } else if (int gm = 0, r = route_two_pass(L.n, b.size(), &gm); L.two_pass && r == 1) {
             if (!b.empty()) {
                 indexed_four_step(L.n, &tp_idx.col, &tp_idx.row);
                 tp_idx.n = L.n;
@@ -963,7 +966,8 @@ int wl_enqueue(WorkList *w, const void *in, void *out, hipStream_t s)
         hipError_t e = hipGetLastError();
         return e == hipSuccess ? set_ok() : hip_error(e, "indexed launch");
     }
-    hipLaunchKernelGGL(clear_kernel, dim3(1), dim3(256), 0, s, w->d_ctl, 2u);
+    if (w->n_tasks)
+        hipLaunchKernelGGL(clear_kernel, dim3(1), dim3(256), 0, s, w->d_ctl, 2u);
     // launch 0: pass-A and single-pass tasks; then the wide tiles; launch 1:
     // pass-B tasks
     const uint32_t first[2] = {0, w->n_first};

@@ -145,3 +145,34 @@ def test_default_stream_is_the_current_one():
     with torch.cuda.stream(s):
         assert fs._stream_handle(None) == s.cuda_stream != 0
     assert fs._stream_handle(None) == torch.cuda.current_stream().cuda_stream
+
+
+@pytest.mark.parametrize("count", [1, 3, 4096, 4097])
+def test_two_pass_work_list_route_by_count(count):
+    """65536-point work lists: the indexed passes up to 4096 segments, tasks
+    above, from unaligned offsets (few distinct segments, repeated, so that
+    the largest lists fit); the bits do not depend on the list."""
+    import torch
+    n, kinds = 1 << 16, 3
+    announce("work-list route count=%d" % count)
+    src = noise(n, kinds, seed=91)
+    in_off = (np.arange(count) % kinds) * (n + 5) + 3
+    out_off = np.arange(count, dtype=np.int64) * (n + 7) + 1
+    x = torch.zeros(kinds * (n + 5) + 16, dtype=torch.complex64, device="cuda")
+    for k in range(kinds):
+        x[k * (n + 5) + 3:k * (n + 5) + 3 + n] = torch.from_numpy(src[k])
+    y = torch.zeros(count * (n + 7) + 8, dtype=torch.complex64, device="cuda")
+    with fs.WorkList([(int(i), int(o), n) for i, o in zip(in_off, out_off)]) as wl:
+        d = wl.describe()
+        assert d["indexed_two_pass_segments"] == (count if count <= 4096 else 0)
+        wl.exec(x, y)
+        wl.status()
+    with fs.WorkList([(3, 1, n), (n + 8, n + 8, n)]) as wl:
+        z = torch.zeros(2 * (n + 8), dtype=torch.complex64, device="cuda")
+        wl.exec(x, z)
+    for s in {0, 1 % count, count // 2, count - 1}:
+        got = y[int(out_off[s]):int(out_off[s]) + n]
+        check(n, got.cpu().numpy()[None], src[s % kinds][None])
+        if s % kinds < 2:
+            o = 1 if s % kinds == 0 else n + 8
+            assert torch.equal(got, z[o:o + n])
