@@ -171,19 +171,21 @@ __global__ void STAGES_KERNEL(F, false)
     const RowIo<true> io{ybuf + seg * ysamples + ((uint64_t)blk << lr) * (unsigned)n2,
                          out + seg * (uint64_t)(m + 1), n1, (int)blk * half, lr, n1};
     run_stages<-1, F>(io, s, stage_lds, tw);
-    c32 wa[kAhead], wb[kAhead];
+    c32 wb[kAhead];
     int vk[kAhead], va[kAhead], vz[kAhead];  // k (< 0: none), slots of the pair
+    // (a workgroup is whole waves, so a thread stays with one row pair)
+    const int c = (int)threadIdx.x & (half - 1), k1 = io.first + c;
+    const bool zero = k1 == 0, self = zero || 2 * k1 == n1, row = 2 * k1 <= n1;
+    const c32 wa = row ? w1[k1] : c32{0.f, 0.f};
     walk_pairs(
         n2 << (lr - 1),
         [&](int e, int i) {
-            const int c = e & (half - 1), k2 = e >> (lr - 1), k1 = io.first + c;
-            const bool zero = k1 == 0, self = zero || 2 * k1 == n1;
+            const int k2 = e >> (lr - 1);
             const int p2 = zero ? (k2 == 0 ? 0 : n2 - k2) : n2 - 1 - k2;
-            const bool none = k2 >= n2 || 2 * k1 > n1 ||
+            const bool none = k2 >= n2 || !row ||
                               (self && k2 != 0 && p2 < k2);  // (the partner's)
             vk[i] = none ? -1 : k1 + n1 * k2;
             if (!none) {
-                wa[i] = w1[k1];
                 wb[i] = w2[k2];
                 va[i] = io.slot(k2, c);
                 vz[i] = io.slot(p2, self ? c : half + c);
@@ -194,7 +196,7 @@ __global__ void STAGES_KERNEL(F, false)
             if (k < 0)
                 return;
             c32 lo, hi;
-            split_forward(stage_lds[va[i]], stage_lds[vz[i]], cmul(wa[i], wb[i]), lo, hi);
+            split_forward(stage_lds[va[i]], stage_lds[vz[i]], cmul(wa, wb[i]), lo, hi);
             io.y[k] = lo;
             if (2 * k != m)
                 io.y[m - k] = hi;
@@ -222,22 +224,24 @@ __global__ void STAGES_KERNEL(F, true)
     ColumnIo<false, true> io{in + seg * (uint64_t)(m + 1), ybuf + seg * ysamples, nullptr, tl, th,
                              nullptr, sh, n2, first, lc, lr, (unsigned)n1};
     io.wr = column_factors(io, s);
-    c32 va[kAhead], vz[kAhead], wa[kAhead], wb[kAhead];
+    c32 va[kAhead], vz[kAhead], wb[kAhead];
     int vk[kAhead], sa[kAhead], sz[kAhead];  // k (< 0: none), slots of the pair
+    // (a workgroup is whole waves, so a thread stays with one column pair)
+    const int c = (int)threadIdx.x & (half - 1), j = first + c;
+    const bool zero = j == 0, self = zero || 2 * j == n2, column = 2 * j <= n2;
+    const c32 wa = column ? w1[j] : c32{0.f, 0.f};
     walk_pairs(
         n1 << (lc - 1),
         [&](int e, int q) {
-            const int c = e & (half - 1), i = e >> (lc - 1), j = first + c;
-            const bool zero = j == 0, self = zero || 2 * j == n2;
+            const int i = e >> (lc - 1);
             const int pi = zero ? (i == 0 ? 0 : n1 - i) : n1 - 1 - i;
-            const bool none = i >= n1 || 2 * j > n2 ||
+            const bool none = i >= n1 || !column ||
                               (self && i != 0 && pi < i);  // (the partner's)
             const int k = i * n2 + j;
             vk[q] = none ? -1 : k;
             if (!none) {
                 va[q] = io.x[k];
                 vz[q] = io.x[m - k];
-                wa[q] = w1[j];
                 wb[q] = w2[i];
                 sa[q] = io.slot(i, c);
                 sz[q] = io.slot(pi, self ? c : half + c);
@@ -250,7 +254,7 @@ __global__ void STAGES_KERNEL(F, true)
             if (k == 0)
                 va[q].y = vz[q].y = 0.f;
             c32 lo, hi;
-            split_inverse(va[q], vz[q], cmul(wa[q], wb[q]), lo, hi);
+            split_inverse(va[q], vz[q], cmul(wa, wb[q]), lo, hi);
             stage_lds[sa[q]] = lo;
             if (k != 0 && 2 * k != m)
                 stage_lds[sz[q]] = hi;
