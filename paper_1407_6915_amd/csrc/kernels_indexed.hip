@@ -20,7 +20,7 @@ const SinglePassDesc kIdx256[] = {
     SpInst<256, 16, 8, 4, kClassic | kNT | kIndexed, 16, 16>::desc(2, 64),
 };
 const SinglePassDesc kIdx1000[] = {
-    SpInst<1000, 100, 2, 4, kClassic | kIndexed, 10, 10, 10>::desc(0, 64),
+    SpInst<1000, 100, 2, 4, kClassic | kWalk | kIndexed, 10, 10, 10>::desc(0, 64),
     SpInst<1000, 100, 2, 4, kClassic | kNT | kIndexed, 10, 10, 10>::desc(1, 64),
 };
 const SinglePassDesc kIdx1024[] = {
@@ -45,7 +45,7 @@ const SinglePassDesc kIdx16384[] = {
         0, 0),
 };
 
-// the 65536-point two-pass tiles (256 x 256), as the plan's defaults
+// the 65536-point two-pass tiles (256 x 256); the work-list tasks' arithmetic
 const ColumnDesc kIdxCol65536 =
     fs::ColInst<256, 16, 16, 4,
                 fs::kNT | fs::kXcd | fs::kNoHoist | fs::kTwPair | fs::kIndexed | fs::kLdsTw, 16,

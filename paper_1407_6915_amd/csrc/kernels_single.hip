@@ -29,9 +29,9 @@ const SinglePassDesc kTable[] = {
     SpInst<512, 64, 4, 4, kNT | kPlain, 8, 8, 8>::desc(0, 0),
     SpInst<512, 64, 4, 4, kPlain, 8, 8, 8>::desc(1, 32),
     SpInst<512, 32, 8, 4, kNT | kPlain, 16, 16, 2>::desc(2, 64),
-    SpInst<512, 64, 4, 4, kClassic | kNT | kAux, 8, 8, 8>::desc(3, 32),
+    SpInst<512, 64, 4, 4, kClassic | kNT | kAux | kWalkAux, 8, 8, 8>::desc(3, 32),
     SpInst<512, 16, 16, 4, kClassic | kNT, 32, 16>::desc(4, 32),
-    SpInst<1024, 64, 2, 4, kNT | kPlain | kAux | kSmallBatch, 16, 16, 4>::desc(7, 64),
+    SpInst<1024, 64, 2, 4, kNT | kPlain | kAux | kWalkAux | kSmallBatch, 16, 16, 4>::desc(7, 64),
     SpInst<1024, 64, 4, 4, kNT | kPlain, 16, 16, 4>::desc(1, 64),
     SpInst<1024, 64, 4, 4, kPlain, 16, 16, 4>::desc(2, 32),
     SpInst<1024, 64, 4, 4, kNT, 16, 16, 4>::desc(3, 32),
@@ -44,7 +44,7 @@ const SinglePassDesc kTable[] = {
     SpInst<1024, 32, 8, 4, kClassic | kNT, 32, 32>::desc(0, 32),
     SpInst<1024, 32, 4, 4, kClassic | kNT, 32, 32>::desc(8, 32),
     SpInst<1024, 32, 16, 4, kClassic | kNT, 32, 32>::desc(9, 32),
-    SpInst<2048, 128, 1, 4, kNT | kPlain | kAux | kSmallBatch, 16, 16, 8>::desc(6, 64),
+    SpInst<2048, 128, 1, 4, kNT | kPlain | kAux | kWalkAux | kSmallBatch, 16, 16, 8>::desc(6, 64),
     SpInst<2048, 128, 2, 4, kNT | kPlain, 16, 16, 8>::desc(1, 64),
     SpInst<2048, 128, 2, 4, kPlain, 16, 16, 8>::desc(2, 32),
     SpInst<2048, 128, 2, 4, kClassic, 16, 16, 8>::desc(3, 32),
@@ -53,12 +53,12 @@ const SinglePassDesc kTable[] = {
     // 2.86-2.87 ms per 8 GiB against 2.99-3.04 for the 16-16-8 kernel of variant 6
     // (small batches)
     SpInst<2048, 64, 4, 4, kClassic | kNT, 32, 8, 8>::desc(0, 32),
-    SpInst<4096, 128, 2, 4, kClassic | kNT, 16, 16, 16>::desc(0, 32),
+    SpInst<4096, 128, 2, 4, kClassic | kNT | kWalk, 16, 16, 16>::desc(0, 32),
     SpInst<4096, 128, 2, 4, kClassic, 16, 16, 16>::desc(1, 64),
     // (variant 3 first: the length's frame and real-input kernels are the
     // first row with them; the frame kernel takes 2.89 ms per 2^18 frames
     // every 1024 samples at this grid of 16, 2.92-2.98 at 32)
-    SpInst<4096, 256, 1, 0, kNT | kPlain | kAux, 16, 16, 16>::desc(3, 16),
+    SpInst<4096, 256, 1, 0, kNT | kPlain | kAux | kWalkAux, 16, 16, 16>::desc(3, 16),
     SpInst<4096, 512, 1, 4, kNT | kPlain | kAux, 8, 8, 8, 8>::desc(2, 64),
     SpInst<4096, 128, 2, 0, kNT | kPlain, 16, 16, 16>::desc(4, 32),
     // tiny batches: 5.9 us for one segment against 8.1 (variant 0 has half
@@ -81,7 +81,7 @@ const SinglePassDesc kTable[] = {
     // frame, 3.05 ms per 2^17 frames every 2048 samples against 4.06 through
     // the real-input row below
     SpInst<8192, 512, 1, 4, kNT | kNoHoist | kTwPair | kW4 | kFrames, 16, 16, 16, 2>::desc(7, 0),
-    SpInst<8192, 512, 1, 4, kNT | kPlain | kAux, 16, 16, 16, 2>::desc(3, 32),
+    SpInst<8192, 512, 1, 4, kNT | kPlain | kAux | kWalkAux, 16, 16, 16, 2>::desc(3, 32),
     SpInst<8192, 256, 1, 4, kNT | kNoHoist, 32, 16, 16>::desc(4, 32),
     SpInst<8192, 512, 1, 4, kPrefetch | kNT, 16, 16, 16, 2>::desc(5, 32),
     SpInst<8192, 512, 1, 4, kPrefetch, 16, 16, 16, 2>::desc(6, 16),
@@ -98,11 +98,11 @@ const SinglePassDesc kTable[] = {
     split_desc(4, 7, 32),
     split_desc(5, 8, 32),
     // mixed radix 2/3/5
-    SpInst<1000, 100, 2, 4, kClassic, 10, 10, 10>::desc(0, 64),
+    SpInst<1000, 100, 2, 4, kClassic | kWalk, 10, 10, 10>::desc(0, 64),
     SpInst<1000, 100, 2, 4, kPlain, 10, 10, 10>::desc(1, 64),
-    SpInst<1000, 100, 2, 4, kNT | kPlain | kAux, 10, 10, 10>::desc(2, 32),
+    SpInst<1000, 100, 2, 4, kNT | kPlain | kAux | kWalkAux, 10, 10, 10>::desc(2, 32),
     SpInst<1000, 125, 2, 4, kNT | kPlain, 8, 5, 5, 5>::desc(3, 32),
-    SpInst<1536, 96, 2, 4, kNT | kPlain | kAux, 16, 16, 6>::desc(0, 64),
+    SpInst<1536, 96, 2, 4, kNT | kPlain | kAux | kWalk | kWalkAux, 16, 16, 6>::desc(0, 64),
     SpInst<1536, 96, 2, 4, kPlain, 16, 16, 6>::desc(1, 32),
     SpInst<1536, 96, 2, 4, kNT, 16, 16, 6>::desc(2, 32),
     SpInst<1536, 96, 2, 4, kClassic | kNT, 16, 16, 6>::desc(3, 64),

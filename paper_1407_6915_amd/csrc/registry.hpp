@@ -44,6 +44,9 @@ using col_frames_launch_fn = void (*)(int dir, const void *in, void *ybuf, const
                                       uint64_t batch, uint64_t hop, const float *window,
                                       unsigned grid, hipStream_t s);
 
+// Groups that a kWalk / kWalkAux kernel's workgroup walks (grid_for).
+constexpr int kWalkGroups = 4;
+
 // One LDS-resident pass over whole segments.
 struct SinglePassDesc {
     int n;              // segment length
@@ -54,6 +57,8 @@ struct SinglePassDesc {
     int nontemporal;    // streamed (non-temporal) global loads and stores
     int hoist;          // bit i: stage i keeps its twiddles in registers across segments
     int grid_mult;      // default persistent grid: resident waves of workgroups
+    int walk;           // groups a workgroup walks at least at that grid (grid_for)
+    int walk_aux;       // the same for the length's frame and real-input kernels
     int lds_bytes;
     int shuffle;        // 1: an exchange between stages runs through lane shuffles
     int small_batch;    // > 0: the length's kernel for batches that give the default

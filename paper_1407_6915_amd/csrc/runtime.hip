@@ -518,14 +518,29 @@ static int resident_per_cu(const void *kernel, int threads, int dev)
     return per_cu;
 }
 
+// Workgroups of a persistent kernel: grid_mult resident waves at most (0: one
+// per group).  Kernels that keep their twiddles in registers across groups are
+// bound by reading them when a workgroup takes only one or two groups, so those
+// with walk > 1 get fewer waves, whole ones, where the batch gives that many
+// less than `walk` groups each (at 2^25 samples, whose groups are 5 to 16 waves,
+// every group used to be a workgroup of its own).  Four measured best: 4096
+// points at 2^27 samples 402 -> 364 us (2 groups each 379, 8 each 369); 1000
+// points 517 -> 395; real forward of 4096 255 -> 211, inverse 303 -> 224, of
+// 16384 431 -> 323 and 556 -> 415; frames of 4096 every 4096 560 -> 379, every
+// 1024 488 -> 355; at 2^23 samples 33.3 -> 31.0, 28.0 -> 25.2, 23.1 -> 20.0.  One-
+// pass lengths whose kernels read few twiddles or reload them per group lose
+// (at 2^27 samples 256 points 9 %, 512 and 1024 2 %, 8192 6 %, 16384 8 %) and have walk = 1.
 unsigned grid_for(const void *kernel, int threads, uint64_t work_groups, int dev,
-                  int grid_mult)
+                  int grid_mult, int walk)
 {
     uint64_t g = work_groups;
     if (grid_mult > 0) {
-        const uint64_t cap = (uint64_t)resident_per_cu(kernel, threads, dev) *
-                             (uint64_t)device_cus(dev) * (uint64_t)grid_mult;
-        g = std::min<uint64_t>(g, cap);
+        const uint64_t wave =
+            (uint64_t)resident_per_cu(kernel, threads, dev) * (uint64_t)device_cus(dev);
+        uint64_t waves = (uint64_t)grid_mult;
+        if (walk > 1)
+            waves = std::min<uint64_t>(waves, std::max<uint64_t>(g / (wave * (uint64_t)walk), 1));
+        g = std::min<uint64_t>(g, wave * waves);
     }
     g = std::min<uint64_t>(g, 0x7fffffffull);
     return (unsigned)std::max<uint64_t>(g, 1);
@@ -603,8 +618,11 @@ int plan_choose(Plan *p, uint64_t n, uint64_t batch, int dir, int forced_variant
                          (unsigned long long)n, forced_variant);
     if (p->sp) {
         p->kind = Plan::SINGLE;
-        if (!getenv("FFTSEG_GRID_MULT"))
-            p->grid_mult = tuned_grid_mult(n, p->sp->variant, p->sp->grid_mult);
+        if (!getenv("FFTSEG_GRID_MULT")) {
+            const int g = tuned_grid_mult(n, p->sp->variant, -1);
+            p->own_grid = g < 0;
+            p->grid_mult = p->own_grid ? p->sp->grid_mult : g;
+        }
         return set_ok();
     }
     p->sh = two_level_shift(n);
@@ -725,7 +743,8 @@ int plan_build_real(Plan *p, uint64_t n, uint64_t batch, int dir)
     if (p->sp && p->sp->launch_real) {
         // the split fused into the m-point one-pass kernel
         p->kind = Plan::REAL;
-        p->grid_mult = p->sp->grid_mult;
+        p->own_grid = !getenv("FFTSEG_GRID_MULT");
+        p->grid_mult = p->own_grid ? p->sp->grid_mult : env_grid_mult();
         return upload_tables(p, {{root_table(m), &p->tw}, {root_products(n, m + 1), &p->tw2}});
     }
     // a run-time schedule of the m-point transform, the split fused into it
@@ -933,14 +952,20 @@ int plan_enqueue(Plan *p, const void *in, void *out, uint64_t batch, hipStream_t
             const sp_rotated_launch_fn rl = rotated_launcher(n, &rv, rk);
             if (rl && rv == d->variant) {
                 const unsigned grid = grid_for(rk[dir > 0], d->threads * d->segs_per_wg, groups,
-                                               p->device, p->grid_mult);
+                                               p->device, p->grid_mult,
+                                               p->own_grid ? d->walk : 1);
                 rl(dir, in, out, p->tw, batch, (int)((kLineSamples - out_m) % kLineSamples),
                    grid, s);
                 break;
             }
         }
+        // (streamed stores that split 64-byte blocks: consecutive workgroups
+        // close together write the halves in time; 1536 points, 2^25 samples
+        // at an output base of 24 bytes 118 us against 130 walking)
         const unsigned grid = grid_for(d->kernel[dir > 0], d->threads * d->segs_per_wg,
-                                       groups, p->device, p->grid_mult);
+                                       groups, p->device, p->grid_mult,
+                                       p->own_grid && !(d->nontemporal && out_m % 8) ? d->walk
+                                                                                     : 1);
         d->launch(dir, in, out, p->tw, batch, grid, s);
         break;
     }
@@ -948,7 +973,8 @@ int plan_enqueue(Plan *p, const void *in, void *out, uint64_t batch, hipStream_t
         const SinglePassDesc *d = p->sp;
         const uint64_t groups = (batch + d->segs_per_wg - 1) / d->segs_per_wg;
         const unsigned grid = grid_for(d->kernel_real[dir > 0], d->threads * d->segs_per_wg,
-                                       groups, p->device, p->grid_mult);
+                                       groups, p->device, p->grid_mult,
+                                       p->own_grid ? d->walk_aux : 1);
         d->launch_real(dir, in, out, p->tw, p->tw2, batch, grid, s);
         break;
     }

@@ -28,12 +28,14 @@ namespace sp {
 // kernels read overlapping frames through the cache
 // (single_pass_strided_kernel).  kSmallBatch = the planner's choice for
 // batches too small to give the default kernel two workgroups per CU;
-// kTinyBatch = for batches that give it fewer than one per eight CUs.
+// kTinyBatch = for batches that give it fewer than one per eight CUs; kWalk /
+// kWalkAux = the transform kernel / the frame and real-input kernels walk four
+// groups a workgroup where the batch has that many (grid_for).
 constexpr int kNT = 1, kNoHoist = 2, kHoistLast = 4, kW2 = 8, kW3 = 16, kPlainLane = 32,
               kPlainLds = 64, kPlain = kPlainLane | kPlainLds, kClassic = 128, kAux = 256,
               kPrefetch = 512, kSplit = 1024, kW4 = 2048, kW8 = 4096, kIndexed = 8192,
               kTwPair = 16384, kFrames = 32768, kXcdFrames = 65536, kSmallBatch = 131072,
-              kTinyBatch = 262144;
+              kTinyBatch = 262144, kWalk = 524288, kWalkAux = 1048576;
 
 template <int NS, int F>
 constexpr int hoist_mask()
@@ -131,6 +133,8 @@ struct SpInst {
         d.pad_shift = PS;
         d.nontemporal = (F & kNT) != 0;
         d.small_batch = (F & kSmallBatch) ? 16 : (F & kTinyBatch) ? 1 : 0;
+        d.walk = (F & kWalk) ? kWalkGroups : 1;
+        d.walk_aux = (F & kWalkAux) ? kWalkGroups : 1;
         d.hoist = hoist_mask<sizeof...(Rs), F>();
         d.lds_bytes = Pol::kLdsElems * (int)((F & kSplit) ? sizeof(float) : sizeof(c32));
         d.nrad = (int)sizeof...(Rs);

@@ -328,6 +328,7 @@ extern "C" int fft_autotune(size_t segment_len, size_t batch, int direction, con
                     break;
                 }
                 p.grid_mult = m;
+                p.own_grid = false;
                 const uint64_t plan_n1 = p.kind == Plan::FOURSTEP ? p.n1 : 0;
                 double us = 0;
                 st = time_plan(&p, in, out, s, 5, &us);

@@ -931,7 +931,8 @@ int wl_reset(WorkList *w, const fft_work_t *items, size_t n, hipStream_t s)
         const SinglePassDesc *d = r.d;
         const uint64_t groups = (r.count + d->segs_per_wg - 1) / d->segs_per_wg;
         r.grid = grid_for(d->kernel_indexed[w->dir > 0], d->threads * d->segs_per_wg, groups,
-                          w->device, r.grid_mult > 0 ? r.grid_mult : d->grid_mult);
+                          w->device, r.grid_mult > 0 ? r.grid_mult : d->grid_mult,
+                          r.grid_mult > 0 ? 1 : d->walk);
     }
     w->ready = true;
     return set_ok();

@@ -176,3 +176,48 @@ def test_two_pass_work_list_route_by_count(count):
         if s % kinds < 2:
             o = 1 if s % kinds == 0 else n + 8
             assert torch.equal(got, z[o:o + n])
+
+
+@pytest.mark.parametrize("what,n", [("segments", 1000), ("segments", 1536), ("segments", 4096),
+                                    ("frames", 512), ("frames", 1000), ("frames", 1024),
+                                    ("frames", 1536), ("frames", 2048), ("frames", 4096),
+                                    ("real", 1024), ("real", 2000), ("real", 2048), ("real", 3072),
+                                    ("real", 4096), ("real", 8192), ("real", 16384)])
+@pytest.mark.parametrize("log2_total", [20, 22, 24, 25])
+def test_walking_grids_give_the_same_bits(monkeypatch, what, n, log2_total):
+    """A kernel's own grid (workgroups that walk several groups) against one
+    workgroup per group: less than one resident wave, a few, many; ragged last
+    groups; an output that starts inside a 64-byte line."""
+    import torch
+    announce("walking grid %s n=%d 2^%d" % (what, n, log2_total))
+    batch = (1 << log2_total) // n + 3
+
+    def both(make, call, count, dtype):
+        got = []
+        for grid in (None, "0"):
+            if grid:
+                monkeypatch.setenv("FFTSEG_GRID_MULT", grid)
+            else:
+                monkeypatch.delenv("FFTSEG_GRID_MULT", raising=False)
+            y = torch.full((count + 8,), -7.0, dtype=dtype, device="cuda")
+            with make() as p:
+                call(p, y[3 if dtype.is_complex else 6:])
+            got.append(y)
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], got[1])
+
+    torch.manual_seed(n)
+    x = torch.randn(batch * (n + 2) + 8, dtype=torch.complex64, device="cuda")
+    for dr in (fs.FORWARD, fs.INVERSE):
+        if what == "real":
+            count, dtype = (batch * (n // 2 + 1), torch.complex64) if dr < 0 else (batch * n, torch.float32)
+            src = torch.view_as_real(x).view(-1)[:batch * n] if dr < 0 else x[:batch * (n // 2 + 1)]
+            both(lambda: fs.RealPlan(n, batch, dr), lambda p, y: p.exec(src, y[:count]), count, dtype)
+        elif what == "frames":
+            hop = n // 4
+            both(lambda: fs.Plan(n, batch, dr),
+                 lambda p, y: p.exec_frames(x[:(batch - 1) * hop + n], hop, batch, out=y[:batch * n]),
+                 batch * n, torch.complex64)
+        else:
+            both(lambda: fs.Plan(n, batch, dr), lambda p, y: p.exec(x[:batch * n], y[:batch * n]),
+                 batch * n, torch.complex64)
