@@ -74,10 +74,10 @@ int frames_enqueue(Plan *p, const c32 *in, c32 *out, uint64_t frames, uint64_t h
             const uint64_t sb = std::min(p->sub_batch, frames - s0);
             const uint64_t ta = sb * (p->n2 / (uint64_t)cd->cols);
             const uint64_t tb = sb * (p->n1 / (uint64_t)rd->rows);
-            const unsigned ga = grid_for(cd->kernel_frames[dir > 0], cd->threads * cd->cols, ta,
-                                         p->device, p->grid_mult);
-            const unsigned gb = grid_for(rd->kernel[dir > 0], rd->threads * rd->rows, tb,
-                                         p->device, p->grid_mult);
+            const unsigned ga = tile_grid(p, cd->kernel_frames[dir > 0], cd->threads * cd->cols,
+                                          ta, one_wave_columns(p->n1));
+            const unsigned gb = tile_grid(p, rd->kernel[dir > 0], rd->threads * rd->rows, tb,
+                                          one_wave_rows(p->n2));
             (yb ? cd->launch_frames_yblocked : cd->launch_frames)(
                 dir, in + s0 * hop, p->scratch, p->tw, p->tl, p->th, p->sh, (int)p->n2, sb, hop,
                 window, ga, s);

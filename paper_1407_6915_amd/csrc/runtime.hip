@@ -572,6 +572,39 @@ int two_pass_grid_mult(uint64_t n1)
     }
 }
 
+// A four-step pass of columns of 1024 points or rows of 1024 or 2048 takes one
+// resident wave of workgroups that walk four tiles or more each:
+// neighbouring tiles then stay in step on an XCD and find the lines that they
+// share, where launching a workgroup per tile lets them drift (2^20 points, 2^24
+// to 2^28 samples: 120 -> 107, 250 -> 208, 473 -> 412, 944 -> 851, 1.77 -> 1.69 ms;
+// an output base off a line, 2^25 samples: 293 -> 238; frames every 2^20: 255 ->
+// 210; 2^21 points, 2^25 samples 289 -> 274; 2^22, rows alone 339 -> 320).  Longer
+// walks lose it again: 64 tiles a workgroup for 2^20 points (at 128, 3.39 ms
+// against 3.35), 16 above (2^21 at 64: 1.93 ms against 1.89), where 4 gain nothing
+// sure either (2^24 samples, frames every n/4: 126.6 us against 123.3).  Shorter columns
+// lose at any size (512 by 512 at 2^27 samples 743 -> 819), 2048-point ones from 2^26.
+unsigned tile_grid(const Plan *p, const void *kernel, int threads, uint64_t tiles,
+                   bool one_wave)
+{
+    if (p->own_grid && one_wave) {
+        const unsigned g = grid_for(kernel, threads, tiles, p->device, 1);
+        const bool longer = p->n > (1u << 20);
+        if (tiles >= (longer ? 8ull : 4ull) * g && tiles <= (longer ? 16ull : 64ull) * g)
+            return g;
+    }
+    return grid_for(kernel, threads, tiles, p->device, p->grid_mult);
+}
+
+bool one_wave_columns(uint64_t n1)
+{
+    return n1 == 1024;
+}
+
+bool one_wave_rows(uint64_t n2)
+{
+    return n2 == 1024 || n2 == 2048;
+}
+
 int env_grid_mult()
 {
     const char *e = getenv("FFTSEG_GRID_MULT");
@@ -643,10 +676,13 @@ int plan_choose(Plan *p, uint64_t n, uint64_t batch, int dir, int forced_variant
     if (!split && forced_n1)
         return set_error(FFT_ERR_INVALID_ARG, "length %llu has no split with %llu columns",
                          (unsigned long long)n, (unsigned long long)forced_n1);
-    if (!getenv("FFTSEG_GRID_MULT"))
-        p->grid_mult = tuned_grid_mult(n, -1,
-                                       split ? two_pass_grid_mult((uint64_t)p->col->n1)
-                                             : kTwoPassGridMult);
+    if (!getenv("FFTSEG_GRID_MULT")) {
+        const int g = tuned_grid_mult(n, -1, -1);
+        p->own_grid = g < 0;
+        p->grid_mult = !p->own_grid ? g
+                       : split      ? two_pass_grid_mult((uint64_t)p->col->n1)
+                                    : kTwoPassGridMult;
+    }
     if (split) {
         p->kind = Plan::FOURSTEP;
         p->n1 = (uint64_t)p->col->n1;
@@ -1021,12 +1057,12 @@ int plan_enqueue(Plan *p, const void *in, void *out, uint64_t batch, hipStream_t
                     const uint64_t sbat = std::min(p->sub_batch, batch - s0);
                     const uint64_t ta = sbat * (p->n2 / (uint64_t)cs->cols);
                     const uint64_t tb = sbat * (p->n1 / (uint64_t)rs->rows);
-                    const unsigned ga = grid_for(cs->kernel_shifted[dir > 0],
-                                                 cs->threads * cs->cols, ta, p->device,
-                                                 p->grid_mult);
-                    const unsigned gb = grid_for(rs->kernel_shifted[dir > 0],
-                                                 rs->threads * rs->rows, tb, p->device,
-                                                 p->grid_mult);
+                    const unsigned ga = tile_grid(p, cs->kernel_shifted[dir > 0],
+                                                  cs->threads * cs->cols, ta,
+                                                  one_wave_columns(p->n1));
+                    const unsigned gb = tile_grid(p, rs->kernel_shifted[dir > 0],
+                                                  rs->threads * rs->rows, tb,
+                                                  one_wave_rows(p->n2));
                     cs->launch_shifted(dir, (const c32 *)in + s0 * n, ybuf, p->tw, p->tl, p->th,
                                        p->sh, (int)p->n2, sbat, sa, ga, s);
                     rs->launch_shifted(dir, ybuf, (c32 *)out + s0 * n, p->tw2, (int)p->n1, sbat,
@@ -1041,10 +1077,10 @@ int plan_enqueue(Plan *p, const void *in, void *out, uint64_t batch, hipStream_t
             c32 *y = (c32 *)out + s0 * n;
             const uint64_t ta = sb * (p->n2 / (uint64_t)cd->cols);
             const uint64_t tb = sb * (p->n1 / (uint64_t)rd->rows);
-            const unsigned ga = grid_for(cd->kernel[dir > 0], cd->threads * cd->cols, ta,
-                                         p->device, p->grid_mult);
-            const unsigned gb = grid_for(rd->kernel[dir > 0], rd->threads * rd->rows, tb,
-                                         p->device, p->grid_mult);
+            const unsigned ga = tile_grid(p, cd->kernel[dir > 0], cd->threads * cd->cols, ta,
+                                          one_wave_columns(p->n1));
+            const unsigned gb = tile_grid(p, rd->kernel[dir > 0], rd->threads * rd->rows, tb,
+                                          one_wave_rows(p->n2));
             (p->y_blocked ? cd->launch_yblocked : cd->launch)(dir, x, p->scratch, p->tw, p->tl,
                                                               p->th, p->sh, (int)p->n2, sb,
                                                               ga, s);

@@ -40,7 +40,7 @@ struct Plan {
     uint64_t sub_batch = 0;
     bool y_blocked = false;     // FOURSTEP: Y in blocks of 16 columns between the passes
     int grid_mult = 0;          // 0: one workgroup per tile
-    bool own_grid = false;      // SINGLE, REAL: the kernel's own grid, not a tuned or forced one
+    bool own_grid = false;      // the kernels' own grid, not a tuned or forced one
     // false (set before plan_build): kernels that do not depend on the batch,
     // so that a segment's spectrum is the same bits in any batch
     bool by_batch = true;
@@ -101,6 +101,13 @@ constexpr uint64_t kLineSamples = 16;
 int split_variant_counts(uint64_t n, int *ncol, int *nrow);
 unsigned grid_for(const void *kernel, int threads, uint64_t work_groups, int dev,
                   int grid_mult, int walk = 1);
+
+// the grid of a four-step pass over `tiles` tiles; one_wave: of a tile that may
+// take one resident wave (one_wave_columns, one_wave_rows)
+unsigned tile_grid(const Plan *p, const void *kernel, int threads, uint64_t tiles,
+                   bool one_wave);
+bool one_wave_columns(uint64_t n1);
+bool one_wave_rows(uint64_t n2);
 
 int validate_create(uint64_t n, uint64_t batch, int dir);
 // forced_variant: single-pass variant (-1: tuned/default); forced_split_variants:

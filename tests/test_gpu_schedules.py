@@ -182,7 +182,10 @@ def test_two_pass_work_list_route_by_count(count):
                                     ("frames", 512), ("frames", 1000), ("frames", 1024),
                                     ("frames", 1536), ("frames", 2048), ("frames", 4096),
                                     ("real", 1024), ("real", 2000), ("real", 2048), ("real", 3072),
-                                    ("real", 4096), ("real", 8192), ("real", 16384)])
+                                    ("real", 4096), ("real", 8192), ("real", 16384),
+                                    ("segments", 1 << 19), ("segments", 1 << 20),
+                                    ("segments", 1 << 21), ("segments", 1 << 22),
+                                    ("frames", 1 << 20)])
 @pytest.mark.parametrize("log2_total", [20, 22, 24, 25])
 def test_walking_grids_give_the_same_bits(monkeypatch, what, n, log2_total):
     """A kernel's own grid (workgroups that walk several groups) against one
