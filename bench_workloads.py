@@ -478,8 +478,8 @@ def real(args):
     yc = torch.empty_like(xc)
     with fs.Plan(n, b) as pc:
         tc = _time(torch, lambda: pc.exec_ptr(xc.data_ptr(), yc.data_ptr(), sh), args.steps)
-    # 2^21-point segments of the same samples: the 2^20-point half runs as a
-    # two-pass plan and the even/odd split as a separate pass
+    # 2^21-point segments of the same samples: the 2^20-point half runs in two
+    # passes with the even/odd split fused into one of them
     nl = 1 << 21
     bl = total // nl
     spec_l = torch.empty(bl * (nl // 2 + 1), dtype=torch.complex64, device="cuda")

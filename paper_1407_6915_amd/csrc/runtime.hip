@@ -1092,7 +1092,7 @@ int plan_enqueue(Plan *p, const void *in, void *out, uint64_t batch, hipStream_t
     case Plan::GENERIC: {
         const hipError_t e = stages_enqueue(p, in, out, batch, n, nullptr, s);
         if (e != hipSuccess)
-            return hip_error(e, "radix-stage launch");
+            return hip_error(e, "schedule launch");
         break;
     }
     }
