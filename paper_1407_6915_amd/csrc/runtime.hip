@@ -521,8 +521,8 @@ static int resident_per_cu(const void *kernel, int threads, int dev)
 // Workgroups of a persistent kernel: grid_mult resident waves at most (0: one
 // per group).  Kernels that keep their twiddles in registers across groups are
 // bound by reading them when a workgroup takes only one or two groups, so those
-// with walk > 1 get fewer waves, whole ones, where the batch gives that many
-// less than `walk` groups each (at 2^25 samples, whose groups are 5 to 16 waves,
+// with walk > 1 get fewer waves, whole ones, where grid_mult waves would have
+// fewer than `walk` groups each (at 2^25 samples, whose groups are 5 to 16 waves,
 // every group used to be a workgroup of its own).  Four measured best: 4096
 // points at 2^27 samples 402 -> 364 us (2 groups each 379, 8 each 369); 1000
 // points 517 -> 395; real forward of 4096 255 -> 211, inverse 303 -> 224, of
