@@ -55,7 +55,7 @@ __global__ void STAGES_KERNEL(F, true)
     const int first = (int)(t - seg * blocks) << lc;
     ColumnIo<false, false> io{in + seg * hop, ybuf + seg * ysamples, window, tl, th, nullptr, sh,
                               n2, first, lc, lr, (unsigned)s.n};
-    io.wr = column_factors(io, s);
+    io.ws = column_factors(io, s);
     run_stages<D, F>(io, s, stage_lds, tw);
 }
 
@@ -72,13 +72,11 @@ __global__ void STAGES_KERNEL(F, true)
         return;
     const uint64_t q = t / (unsigned)n3, seg = q / blocks;
     const int j = (int)(t - q * (unsigned)n3), blk = (int)(q - seg * blocks);
-    c32 *wr = stage_lds + ((unsigned)s.n << lr);
-    MiddleIo io{ybuf + seg * ysamples +
-                    (((uint64_t)blk * (unsigned)s.n * (unsigned)n3 + (unsigned)j) << lr),
-                tl, th, wr, sh, n3, j, n1 - (blk << lr), lr};
-    const LdsStage &last = s.st[s.ns - 1];
-    if ((int)threadIdx.x < last.r)
-        wr[threadIdx.x] = io.root((unsigned)j * (threadIdx.x * (unsigned)last.nb));
+    const MiddleIo io{ybuf + seg * ysamples +
+                          (((uint64_t)blk * (unsigned)s.n * (unsigned)n3 + (unsigned)j) << lr),
+                      tl, th,
+                      two_level_root(tl, th, sh, (unsigned)j * (unsigned)s.st[s.ns - 1].nb),
+                      sh, n3, j, n1 - (blk << lr), lr};
     run_stages<D, F>(io, s, stage_lds, tw);
 }
 
@@ -536,8 +534,7 @@ template <int D, int F>
 hipError_t launch_middle(const StagesPlan &p, c32 *y, const c32 *tw, const c64 *tl,
                          const c64 *th, int sh, uint64_t batch, hipStream_t s)
 {
-    const size_t lds =
-        rows_lds(p.mid, p.lr) + (size_t)p.mid.st[p.mid.ns - 1].r * sizeof(c32);
+    const size_t lds = rows_lds(p.mid, p.lr);
     const hipError_t e = allow_lds(stages_middle_columns_kernel<D, F>, lds);
     if (e != hipSuccess)
         return e;

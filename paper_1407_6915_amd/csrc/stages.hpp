@@ -124,10 +124,12 @@ hipError_t stages_real_two_pass(const StagesPlan &p, const void *in, void *out, 
 
 constexpr int kLdsBytes = 160 * 1024;
 
-// LDS of a column tile (with the last stage's W_N factors) and of a row tile
+// LDS of a column tile: its samples, from an even slot on one W_N factor (c64) a
+// column; of a row tile
+constexpr int column_slots(int n, int lc) { return (n * ((1 << lc) + 1) + 1) & ~1; }
 inline size_t columns_lds(const LdsSched &s, int lc)
 {
-    return ((size_t)s.n * ((1u << lc) + 1) + ((size_t)s.st[s.ns - 1].r << lc)) * sizeof(c32);
+    return column_slots(s.n, lc) * sizeof(c32) + (sizeof(c64) << lc);
 }
 inline size_t rows_lds(const LdsSched &s, int lr) { return ((size_t)s.n << lr) * sizeof(c32); }
 

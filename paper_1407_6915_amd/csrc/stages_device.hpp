@@ -161,13 +161,41 @@ __device__ __forceinline__ void run_stages(const Io &io, const LdsSched &s, c32 
     }
 }
 
-// W^m from its two-level table: two FP64 entries, their product rounded once
-// (a factor in float32 took three roundings: 2^24 points with three unit
-// tones were 3.3e-7 off, now 2.8e-7).
-__device__ __forceinline__ c32 two_level_root(const c64 *tl, const c64 *th, int sh, unsigned m)
+__device__ __forceinline__ c64 cmul(c64 a, c64 b)
 {
-    const c64 a = th[m >> sh], b = tl[m & ((1u << sh) - 1u)];
-    return {(float)(a.x * b.x - a.y * b.y), (float)(a.x * b.y + a.y * b.x)};
+    return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
+}
+__device__ __forceinline__ c32 rounded(c64 a) { return {(float)a.x, (float)a.y}; }
+
+// W^m from its two-level table
+__device__ __forceinline__ c64 two_level_root(const c64 *tl, const c64 *th, int sh, unsigned m)
+{
+    return cmul(th[m >> sh], tl[m & ((1u << sh) - 1u)]);
+}
+
+// The factors between two passes: v[r] times W^{m (b + r nb)}, r < R, from
+// W^{m b} and W^{m nb}.  The powers run on in FP64, where a step costs what one
+// in float32 does, and each factor is rounded once (the product of two rounded
+// factors in float32: 2^24 points 2.03e-7 off where this is 1.99e-7, 48000
+// 1.42e-7 and 1.40e-7).  One factor a column in LDS in place of R also leaves
+// the kernels fewer registers (narrow columns 92 for 118, wide ones 125 for 156):
+// 2^24 samples of 48000 points 111 -> 106 us, of 2^24 156 -> 153.
+template <int R, int D>
+__device__ __forceinline__ void twiddle_powers(c32 *v, c64 first, c64 step)
+{
+    // (two chains: half the dependent products)
+    c64 even = first, odd = cmul(first, step);
+    const c64 two = cmul(step, step);
+#pragma unroll
+    for (int r = 0; r < R; r += 2) {
+        v[r] = twiddle<D>(v[r], rounded(even));
+        if (r + 1 < R)
+            v[r + 1] = twiddle<D>(v[r + 1], rounded(odd));
+        if (r + 2 < R)
+            even = cmul(even, two);
+        if (r + 3 < R)
+            odd = cmul(odd, two);
+    }
 }
 
 // Whole segments: transform c is segment c of the tile, its elements in
@@ -229,9 +257,10 @@ struct SegmentIo {
 //     Y[(k1 >> lr)][n2][k1 mod 2^lr],
 // so that a wave stores one run here and the row pass loads its tile as one
 // W_N^{n2 k1} of output k1 = b + r nb is W_N^{n2 b}, looked up once per
-// butterfly, times W_N^{n2 r nb}, looked up once per tile into LDS: a lookup
-// is two gathers from tables of a few thousand entries, and one per output
-// held the pass to half its rate (20000 points: 606 us per 2^26 samples).
+// butterfly, times the r-th power of W_N^{n2 nb}, looked up once per column
+// into LDS (twiddle_powers): a lookup is two gathers from tables of a few
+// thousand entries, and one per output held the pass to half its rate (20000
+// points: 606 us per 2^26 samples).
 // PairRows (real segments, forward): a row tile holds rows k1 and n1 - k1,
 // the first half of its slots and the second, so Y groups the rows so.
 // PairColumns (real segments, inverse): the tile holds columns n2' and
@@ -244,10 +273,10 @@ struct ColumnIo {
     const float *window;
     const c64 *__restrict__ tl;
     const c64 *__restrict__ th;
-    const c32 *wr;  // LDS: W_N^{n2 r nb} of the last stage's outputs, [r][column]
+    const c64 *ws;  // LDS: W_N^{n2 nb} of the columns, nb the last stage's
     int sh, n2, first, lc, lr;
     unsigned n1;
-    __device__ __forceinline__ c32 root(unsigned m) const
+    __device__ __forceinline__ c64 root(unsigned m) const
     {
         return two_level_root(tl, th, sh, m);
     }
@@ -324,10 +353,7 @@ struct ColumnIo {
     template <int R, int D>
     __device__ __forceinline__ void finish(c32 *v, int b, int c, int) const
     {
-        const c32 wb = root((unsigned)column(c) * (unsigned)b);
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-            v[r] = twiddle<D>(v[r], cmul(wb, wr[(r << lc) + c]));
+        twiddle_powers<R, D>(v, root((unsigned)column(c) * (unsigned)b), ws[c]);
     }
 };
 
@@ -393,9 +419,9 @@ struct MiddleIo {
     c32 *y;  // row block, column j
     const c64 *__restrict__ tl;
     const c64 *__restrict__ th;
-    const c32 *wr;  // LDS: W_{n2 n3}^{j r nb} of the last stage's outputs
+    c64 ws;                   // W_{n2 n3}^{j nb}, nb the last stage's
     int sh, n3, j, rows, lr;  // rows the block holds
-    __device__ __forceinline__ c32 root(unsigned m) const
+    __device__ __forceinline__ c64 root(unsigned m) const
     {
         return two_level_root(tl, th, sh, m);
     }
@@ -428,10 +454,7 @@ struct MiddleIo {
     template <int R, int D>
     __device__ __forceinline__ void finish(c32 *v, int b, int, int) const
     {
-        const c32 wb = root((unsigned)j * (unsigned)b);
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-            v[r] = twiddle<D>(v[r], cmul(wb, wr[r]));
+        twiddle_powers<R, D>(v, root((unsigned)j * (unsigned)b), ws);
     }
 };
 
@@ -443,21 +466,18 @@ __device__ __forceinline__ uint64_t xcd_tile()
     return (uint64_t)(blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
 }
 
-extern __shared__ c32 stage_lds[];
+extern __shared__ __attribute__((aligned(16))) c32 stage_lds[];
 
-// Factors W_N^{n2 r nb} of a column tile's last stage into LDS behind the
-// tile (read after the barriers of the first exchange)
+// Factors W_N^{n2 nb} of a column tile into LDS behind the tile (read after
+// the barriers of the first exchange; a workgroup has at least 64 threads)
 template <class Io>
-__device__ __forceinline__ c32 *column_factors(const Io &io, const LdsSched &s)
+__device__ __forceinline__ c64 *column_factors(const Io &io, const LdsSched &s)
 {
-    c32 *wr = stage_lds + s.n * ((1 << io.lc) + 1);
-    const LdsStage &last = s.st[s.ns - 1];
-    for (int e = threadIdx.x; e < last.r << io.lc; e += blockDim.x) {
-        const int r = e >> io.lc, c = e & ((1 << io.lc) - 1);
-        if (io.has(c))
-            wr[e] = io.root((unsigned)io.column(c) * (unsigned)(r * last.nb));
-    }
-    return wr;
+    c64 *ws = reinterpret_cast<c64 *>(stage_lds + column_slots(s.n, io.lc));
+    const int c = threadIdx.x;
+    if (c < 1 << io.lc && io.has(c))
+        ws[c] = io.root((unsigned)io.column(c) * (unsigned)s.st[s.ns - 1].nb);
+    return ws;
 }
 
 }  // namespace stages

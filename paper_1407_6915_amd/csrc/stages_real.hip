@@ -149,7 +149,7 @@ __global__ void STAGES_KERNEL(F, true)
     const int first = (int)(t - seg * blocks) << lc;
     ColumnIo<true, false> io{in + seg * ((uint64_t)s.n * (unsigned)n2), ybuf + seg * ysamples,
                              nullptr, tl, th, nullptr, sh, n2, first, lc, lr, (unsigned)s.n};
-    io.wr = column_factors(io, s);
+    io.ws = column_factors(io, s);
     run_stages<-1, F>(io, s, stage_lds, tw);
 }
 
@@ -223,7 +223,7 @@ __global__ void STAGES_KERNEL(F, true)
     const int first = (int)(t - seg * blocks) * half;
     ColumnIo<false, true> io{in + seg * (uint64_t)(m + 1), ybuf + seg * ysamples, nullptr, tl, th,
                              nullptr, sh, n2, first, lc, lr, (unsigned)n1};
-    io.wr = column_factors(io, s);
+    io.ws = column_factors(io, s);
     c32 va[kAhead], vz[kAhead], wb[kAhead];
     int vk[kAhead], sa[kAhead], sz[kAhead];  // k (< 0: none), slots of the pair
     // (a workgroup is whole waves, so a thread stays with one column pair)

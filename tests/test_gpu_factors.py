@@ -1,0 +1,60 @@
+"""Factors that the kernels apply, seen through unit impulses: where every other
+factor on an output's way is 1, -1, i or -i, the output is the factor itself,
+and one that is rounded once from FP64 is within half a unit in the last
+place (2^-25 below 1) of the exact root of unity."""
+import numpy as np
+import pytest
+
+import paper_1407_6915_amd as fs
+
+from gpu_helpers import announce
+
+pytestmark = pytest.mark.gpu
+
+# half a unit in the last place of a float32 in [0.5, 1), and what FP64
+# arithmetic adds (a few 2^-52)
+ONCE = 2.0 ** -25 * (1 + 2.0 ** -20)
+
+
+def roots(m, n, direction):
+    """exp(direction 2 pi i m / n) for integer arrays m."""
+    m = np.asarray(m, np.int64) % n
+    a = 2 * np.pi / n * np.where(2 * m > n, m - n, m)
+    return np.cos(a) + 1j * direction * np.sin(a)
+
+
+def off(got, want):
+    d = got.astype(np.complex128) - want
+    return max(np.abs(d.real).max(), np.abs(d.imag).max())
+
+
+def impulse(n, at, direction):
+    import torch
+    x = torch.zeros(n, dtype=torch.complex64, device="cuda")
+    x[at] = 1
+    with fs.Plan(n, 1, direction) as p:
+        y = p.exec(x)
+    torch.cuda.synchronize()
+    return y.cpu().numpy()
+
+
+@pytest.mark.parametrize("direction", [fs.FORWARD, fs.INVERSE])
+@pytest.mark.parametrize("n", [40960, 3 << 20, 1 << 23, 1 << 24])
+def test_factors_between_passes_are_rounded_once(n, direction):
+    """An impulse half a row into the columns: the columns' transforms and the
+    rows' are exact (lengths whose rows are powers of two: a 3-point step has
+    factors of its own)."""
+    announce("pass factors n=%d dir=%d" % (n, direction))
+    with fs.Plan(n, 1) as p:
+        d = p.describe()
+    assert d["passes"] in (2, 3)
+    n1, n2, n3 = d["n1"], d["n2"], d.get("n3", 1)
+    k = np.arange(n, dtype=np.int64)
+    # column n2 n3 / 2: the first pass's factor
+    at = n2 * n3 // 2
+    assert off(impulse(n, at, direction), roots(k * at, n, direction)) <= ONCE
+    if d["passes"] == 3:
+        # column n3 / 2: the second pass's factor in the rows k1 = 0
+        at = n3 // 2
+        got = impulse(n, at, direction)[::n1]
+        assert off(got, roots(k[::n1] * at, n, direction)) <= ONCE
