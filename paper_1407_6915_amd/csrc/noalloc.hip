@@ -19,7 +19,8 @@
 namespace fftseg {
 namespace {
 
-// tables: W_N (one pass) or W_N1, W_N2 and the two-level W_N (two passes)
+// tables: W_N or a schedule's (one pass); W_N1, W_N2 or the schedules', and the
+// two-level tables (two and three passes)
 constexpr uint64_t kTableSamples = 1ull << 15;
 // Y: 2^24 samples plus two lines: one sub-batch of a two-pass length with
 // compiled tiles (up to 2^22 points, so at least 4 segments), or of a
@@ -55,17 +56,15 @@ int scratch_ptr(int dev, void **out)
     return FFT_OK;
 }
 
-// exp(-2 pi i m / n) in FP64, the angle folded to the first octant in exact
-// integer arithmetic (8 m < 2^28 here)
-__device__ c64 device_root(uint64_t m, uint64_t n)
+// exp(-2 pi i m / n), m < n <= 2^24, in FP64, the angle folded to the first
+// octant in exact integer arithmetic
+__device__ c64 device_root(uint32_t m, uint32_t n)
 {
-    m %= n;
-    const uint64_t m8 = m * 8u;
-    const uint64_t o = m8 / n, r = m8 - o * n;
-    const uint64_t j = (o + 1) / 2;
+    const uint32_t m8 = m * 8u;
+    const uint32_t o = m8 / n, r = m8 - o * n;
+    const uint32_t j = (o + 1) / 2;
     const double quarter_pi = 0.78539816339744830961566084581987572;
-    const double x = ((double)((long long)o - 2 * (long long)j) + (double)r / (double)n) *
-                     quarter_pi;
+    const double x = ((double)((int)o - 2 * (int)j) + (double)r / (double)n) * quarter_pi;
     double sx, cx;
     sincos(x, &sx, &cx);
     double c, s;
@@ -78,48 +77,99 @@ __device__ c64 device_root(uint64_t m, uint64_t n)
     return c64{c, -s};
 }
 
-// Consecutive tables: table t holds count[t] entries W_{mod[t]}^{j step[t]},
-// j < count[t], or, with rows of l[t] entries (the twiddles of one stage of
-// a run-time schedule), W_{mod[t]}^{(1 + j / l[t]) (j mod l[t])}.  The first
-// `wide` tables are in FP64, the others rounded once to float32.
+// Table t of a set: the entries up to end[t] of all, W_{mod[t]}^{j step[t]} of
+// its entry j, or, with rows of l[t] > 0 entries (the twiddles of one stage of a
+// run-time schedule), W_{mod[t]}^{(1 + j / l[t]) (j mod l[t])}; from at[t] (in
+// float32 entries) on, rounded once to float32 or, if bit t of `wide` is set,
+// in FP64.
 constexpr int kMaxTables = 4 + 3 * kMaxLdsStages;
+template <int T>
 struct TableSet {
-    uint64_t count[kMaxTables], mod[kMaxTables], step[kMaxTables], l[kMaxTables];
-    int wide;
+    uint32_t end[T], at[T], mod[T], step[T], l[T];
+    uint64_t wide;
 };
+static_assert(kMaxTables <= 64, "a bit of `wide` each");
 
-// the tables of a schedule's stages from table t on; returns the next table
-int add_schedule(TableSet &ts, int t, const LdsSched &s)
-{
-    for (int i = 1; i < s.ns; ++i, ++t) {
-        ts.l[t] = (uint64_t)s.st[i].l;
-        ts.count[t] = (uint64_t)(s.st[i].r - 1) * ts.l[t];
-        ts.mod[t] = (uint64_t)s.st[i].r * ts.l[t];
-    }
-    return t;
-}
+// Lengths with compiled tiles have four tables at most and no rows: a set of
+// that size costs their calls no more than the tables themselves (the kernel for
+// any set: 4096 x 64 13.6 us against 12.1, 65536 x 1 13.1 against 12.2).
+constexpr int kPlainTables = 4;
 
-__global__ void __launch_bounds__(256) static_tables_kernel(c32 *tables, TableSet ts,
-                                                            uint64_t total)
+template <int T>
+__global__ void __launch_bounds__(256) static_tables_kernel(c32 *tables, TableSet<T> ts,
+                                                            uint32_t total)
 {
-    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < total;
-         i += (uint64_t)gridDim.x * 256) {
-        uint64_t j = i;
-        uint64_t at = 0;  // in float32 entries
+    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
         int t = 0;
-        while (t + 1 < kMaxTables && j >= ts.count[t]) {
-            at += ts.count[t] * (t < ts.wide ? 2 : 1);
-            j -= ts.count[t];
+        while (t + 1 < T && i >= ts.end[t])
             ++t;
-        }
-        const uint64_t l = ts.l[t];
-        const c64 w = device_root(l ? (1 + j / l) * (j % l) : j * ts.step[t], ts.mod[t]);
-        if (t < ts.wide)
-            reinterpret_cast<c64 *>(tables + at)[j] = w;
+        const uint32_t j = i - (t ? ts.end[t - 1] : 0u);
+        uint32_t m = j * ts.step[t];
+        if constexpr (T > kPlainTables)
+            if (const uint32_t l = ts.l[t]; l)
+                m = (1 + j / l) * (j % l);
+        const c64 w = device_root(m, ts.mod[t]);
+        c32 *to = tables + ts.at[t];
+        if (T > kPlainTables && (ts.wide >> t & 1))
+            reinterpret_cast<c64 *>(to)[j] = w;
         else
-            tables[at + j] = c32{(float)w.x, (float)w.y};
+            to[j] = c32{(float)w.x, (float)w.y};
     }
 }
+
+// The tables of a call, each after the one before
+struct Tables {
+    TableSet<kMaxTables> ts{};
+    int n = 0;
+    uint32_t total = 0, room = 0;  // entries; in float32 entries
+    // where the table starts, in float32 entries
+    uint32_t add(uint64_t count, uint64_t mod, uint64_t step, bool wide, uint64_t l = 0)
+    {
+        if (wide)
+            room = (room + 1) & ~1u;
+        const uint32_t at = room;
+        ts.end[n] = total += (uint32_t)count;
+        ts.at[n] = at;
+        ts.mod[n] = (uint32_t)mod;
+        ts.step[n] = (uint32_t)step;
+        ts.l[n] = (uint32_t)l;
+        ts.wide |= (uint64_t)wide << n;
+        room += (uint32_t)count * (wide ? 2 : 1);
+        ++n;
+        return at;
+    }
+    // the table of a schedule
+    uint32_t add(const LdsSched &s)
+    {
+        const uint32_t base = room;
+        for (int i = 1; i < s.ns; ++i) {
+            const uint64_t l = (uint64_t)s.st[i].l, r = (uint64_t)s.st[i].r;
+            add((r - 1) * l, r * l, 0, false, l);
+        }
+        return base;
+    }
+    void launch(c32 *tables, hipStream_t s)
+    {
+        const dim3 grid(std::min<uint32_t>((total + 255) / 256, 1024));
+        for (int t = n; t < kMaxTables; ++t)
+            ts.end[t] = total;
+        bool plain = n <= kPlainTables && !ts.wide;
+        TableSet<kPlainTables> few{};
+        for (int t = 0; t < kPlainTables; ++t) {
+            plain = plain && !ts.l[t];
+            few.end[t] = ts.end[t];
+            few.at[t] = ts.at[t];
+            few.mod[t] = ts.mod[t];
+            few.step[t] = ts.step[t];
+        }
+        if (plain)
+            hipLaunchKernelGGL(static_tables_kernel<kPlainTables>, grid, dim3(256), 0, s, tables,
+                               few, total);
+        else
+            hipLaunchKernelGGL(static_tables_kernel<kMaxTables>, grid, dim3(256), 0, s, tables,
+                               ts, total);
+    }
+};
 
 int noalloc_enqueue(uint64_t n, uint64_t batch, int dir, const void *in, void *out,
                     hipStream_t s)
@@ -136,96 +186,60 @@ int noalloc_enqueue(uint64_t n, uint64_t batch, int dir, const void *in, void *o
                          "scratch holds %llu",
                          (unsigned long long)n, (unsigned long long)(2 * n),
                          (unsigned long long)kYSamples);
-    TableSet ts{};
-    uint64_t total = 0;
+    Tables tabs;
+    // (offsets from the array, then the array's address added)
+    uint64_t tw = 0, tw2 = 0, w1 = 0, tl = 0, th = 0, tl2 = 0, th2 = 0;
+    const bool two = p.kind == Plan::FOURSTEP || (p.kind == Plan::GENERIC && p.stages.passes > 1);
+    auto two_level = [&](uint64_t m, int sh, bool wide, uint64_t *low, uint64_t *high) {
+        const uint64_t lo = 1ull << sh;
+        *low = tabs.add(lo, m, 1, wide);
+        *high = tabs.add((m + lo - 1) / lo, m, lo, wide);
+    };
     switch (p.kind) {
     case Plan::COPY: break;
-    case Plan::SINGLE:
-        ts.count[0] = n; ts.mod[0] = n; ts.step[0] = 1;
-        break;
+    case Plan::SINGLE: tw = tabs.add(n, n, 1, false); break;
     case Plan::FOURSTEP:
-    case Plan::GENERIC: {
-        if (p.kind == Plan::GENERIC && p.stages.passes == 1) {
-            add_schedule(ts, 0, p.stages.a);
-            break;
-        }
-        const uint64_t lo = 1ull << p.sh;
-        ts.count[0] = lo; ts.mod[0] = n; ts.step[0] = 1;                  // tl
-        ts.count[1] = (n + lo - 1) / lo; ts.mod[1] = n; ts.step[1] = lo;  // th
-        if (p.kind == Plan::FOURSTEP) {
-            ts.count[2] = p.n1; ts.mod[2] = p.n1; ts.step[2] = 1;         // W_N1
-            ts.count[3] = p.n2; ts.mod[3] = p.n2; ts.step[3] = 1;         // W_N2
-        } else {
-            // the two-level tables, in FP64, before the schedules'
-            int t = 2;
-            if (p.stages.passes == 3) {
-                const uint64_t m = n / (uint64_t)p.stages.a.n;
-                p.sh2 = two_level_shift(m);
-                const uint64_t lo2 = 1ull << p.sh2;
-                ts.count[2] = lo2; ts.mod[2] = m; ts.step[2] = 1;                     // tl2
-                ts.count[3] = (m + lo2 - 1) / lo2; ts.mod[3] = m; ts.step[3] = lo2;  // th2
-                t = 4;
-            }
-            ts.wide = t;
-            add_schedule(ts, add_schedule(ts, add_schedule(ts, t, p.stages.a), p.stages.b),
-                         p.stages.mid);
-        }
+        two_level(n, p.sh, false, &tl, &th);
+        tw = tabs.add(p.n1, p.n1, 1, false);
+        tw2 = tabs.add(p.n2, p.n2, 1, false);
         break;
-    }
+    case Plan::GENERIC:
+        if (two)
+            two_level(n, p.sh, true, &tl, &th);
+        if (p.stages.passes == 3) {
+            const uint64_t m = n / (uint64_t)p.stages.a.n;
+            p.sh2 = two_level_shift(m);
+            two_level(m, p.sh2, true, &tl2, &th2);
+        }
+        tw = tabs.add(p.stages.a);
+        tw2 = tabs.add(p.stages.b);
+        w1 = tabs.add(p.stages.mid);
+        break;
     default:
         return set_error(FFT_ERR_INVALID_ARG, "real plans are not served here");
     }
-    for (int t = 0; t < kMaxTables; ++t)
-        total += ts.count[t];
-    uint64_t room = total;  // in float32 entries
-    for (int t = 0; t < ts.wide; ++t)
-        room += ts.count[t];
-    if (room > kTableSamples)
+    if (tabs.room > kTableSamples)
         return set_error(FFT_ERR_UNSUPPORTED_LENGTH,
                          "the tables of length %llu (%llu entries) exceed the %llu of static "
-                         "scratch", (unsigned long long)n, (unsigned long long)room,
+                         "scratch", (unsigned long long)n, (unsigned long long)tabs.room,
                          (unsigned long long)kTableSamples);
     void *base = nullptr;
     if ((st = scratch_ptr(p.device, &base)) != FFT_OK)
         return st;
     c32 *tables = (c32 *)base;
-    c32 *y = tables + kTableSamples;
-    if (total) {
-        const unsigned grid = (unsigned)std::min<uint64_t>((total + 255) / 256, 1024);
-        hipLaunchKernelGGL(static_tables_kernel, dim3(grid), dim3(256), 0, s, tables, ts, total);
-    }
-    switch (p.kind) {
-    case Plan::SINGLE: p.tw = tables; break;
-    case Plan::FOURSTEP:
-        p.tl = tables;
-        p.th = tables + ts.count[0];
-        p.tw = tables + ts.count[0] + ts.count[1];
-        p.tw2 = tables + ts.count[0] + ts.count[1] + ts.count[2];
-        p.scratch = y;
-        break;
-    case Plan::GENERIC:
-        if (p.stages.passes == 1) {
-            p.tw = tables;
-            break;
-        }
-        {
-            c32 *at = tables;
-            void **wide[4] = {&p.tl, &p.th, &p.tl2, &p.th2};
-            for (int t = 0; t < ts.wide; ++t) {
-                *wide[t] = at;
-                at += 2 * ts.count[t];
-            }
-            p.tw = at;
-            p.tw2 = at + lds_table_size(p.stages.a);
-            p.w1 = (c32 *)p.tw2 + lds_table_size(p.stages.b);
-        }
-        p.scratch = y;
-        break;
-    default: break;
-    }
+    if (tabs.total)
+        tabs.launch(tables, s);
+    p.tw = tables + tw;
+    p.tw2 = tables + tw2;
+    p.w1 = tables + w1;
+    p.tl = tables + tl;
+    p.th = tables + th;
+    p.tl2 = tables + tl2;
+    p.th2 = tables + th2;
+    p.scratch = two ? tables + kTableSamples : nullptr;
     st = plan_enqueue(&p, in, out, batch, s);
     // nothing of the description is device memory: keep plan_free's hands off
-    p.tw = p.tw2 = p.tl = p.th = p.scratch = nullptr;
+    p.tw = p.tw2 = p.w1 = p.tl = p.th = p.tl2 = p.th2 = p.scratch = nullptr;
     return st;
 }
 

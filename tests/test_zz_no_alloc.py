@@ -29,8 +29,8 @@ def _noalloc(n, batch, direction, xp, yp, stream):
 
 # one-pass lengths (tables only), two-pass lengths with several sub-batches
 # of the static Y buffer (2^24 samples: 16 segments of 2^20, 256 of 65536),
-# the longest two-pass length, radix-stage lengths (two buffers of N each:
-# 2^23 is the longest that fits, one segment per sub-batch) and length 1
+# the longest two-pass length, run-time schedules (up to 2 N samples of Y: 2^23
+# is the longest that fits, one segment per sub-batch) and length 1
 CASES = [(4096, 40, 24), (1000, 33, 7), (1 << 16, 600, 300), (1 << 20, 40, 17),
          (1 << 22, 5, 3), (1 << 23, 2, 1), (3 ** 9, 30, 11), (1, 64, 3)]
 
