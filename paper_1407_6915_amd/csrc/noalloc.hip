@@ -138,13 +138,17 @@ struct Tables {
         ++n;
         return at;
     }
-    // the table of a schedule
+    // the table of a schedule (LdsStage), from an even entry on
     uint32_t add(const LdsSched &s)
     {
-        const uint32_t base = room;
+        const uint32_t base = room = (room + 1) & ~1u;
         for (int i = 1; i < s.ns; ++i) {
             const uint64_t l = (uint64_t)s.st[i].l, r = (uint64_t)s.st[i].r;
-            add((r - 1) * l, r * l, 0, false, l);
+            if (lds_powers(s.st[i].r)) {
+                add(l, r * l, 1, true);
+            } else {
+                add((r - 1) * l, r * l, 0, false, l);
+            }
         }
         return base;
     }

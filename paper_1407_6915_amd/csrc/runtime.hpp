@@ -73,10 +73,15 @@ std::vector<c32> root_table(uint64_t n);
 struct RootProducts {
     std::vector<c64> low, high;
     RootProducts(uint64_t n, uint64_t count);
-    c32 operator[](uint64_t m) const
+    c64 wide(uint64_t m) const  // before the rounding
     {
         const c64 a = high[m >> 7], b = low[m & 127];
-        return {(float)(a.x * b.x - a.y * b.y), (float)(a.x * b.y + a.y * b.x)};
+        return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
+    }
+    c32 operator[](uint64_t m) const
+    {
+        const c64 w = wide(m);
+        return {(float)w.x, (float)w.y};
     }
 };
 std::vector<c32> root_products(uint64_t n, uint64_t count);

@@ -19,7 +19,7 @@
 
 #include <algorithm>
 #include <cmath>
-#include <mutex>
+#include <cstring>
 
 #include "runtime.hpp"
 #include "stages_device.hpp"
@@ -174,9 +174,11 @@ bool lds_schedule(int n, LdsSched *s, bool wide, int group)
     int l = 1, tw = 0;
     for (int i = 0; i < s->ns; ++i) {
         const int r = best[i];
+        if (lds_powers(r))
+            tw = (tw + 1) & ~1;
         s->st[i] = LdsStage{r, l, n / r, tw, reciprocal(l), reciprocal(n / r)};
         if (l > 1)
-            tw += (r - 1) * l;
+            tw += (lds_powers(r) ? 2 : r - 1) * l;
         l *= r;
     }
     return true;
@@ -202,7 +204,10 @@ int lds_threads(const LdsSched &s, int tiles, int group, int form, bool column)
 
 int lds_table_size(const LdsSched &s)
 {
-    return s.ns > 1 ? s.n - s.st[0].r : 0;
+    if (s.ns < 2)
+        return 0;
+    const LdsStage &st = s.st[s.ns - 1];
+    return (st.tw + (lds_powers(st.r) ? 2 : st.r - 1) * st.l + 1) & ~1;
 }
 
 std::vector<c32> lds_table(const LdsSched &s)
@@ -212,11 +217,17 @@ std::vector<c32> lds_table(const LdsSched &s)
     for (int i = 1; i < s.ns; ++i) {
         const LdsStage &st = s.st[i];
         c32 *to = &t[(size_t)st.tw];
-        for (int j = 1; j < st.r; ++j) {
-            const int step = j * (s.n / (st.l * st.r));  // j k step < n
-            for (int k = 0; k < st.l; ++k)
-                *to++ = w[(uint64_t)k * step];
+        const int step = s.n / (st.l * st.r);
+        if (lds_powers(st.r)) {
+            for (int k = 0; k < st.l; ++k, to += 2) {
+                const c64 v = w.wide((uint64_t)k * step);
+                std::memcpy(to, &v, sizeof v);
+            }
+            continue;
         }
+        for (int j = 1; j < st.r; ++j)
+            for (int k = 0; k < st.l; ++k)
+                *to++ = w[(uint64_t)j * k * step];  // (< n)
     }
     return t;
 }

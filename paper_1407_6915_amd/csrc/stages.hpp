@@ -15,10 +15,16 @@ namespace fftseg {
 
 constexpr int kMaxLdsStages = 8;
 
+// Radices whose stages form their twiddles as powers of one FP64 entry
+// (twiddle_powers); the others read an entry for each (from 12 on 0.9 % and from 5
+// on 0.2 % slower over 150 lengths).
+constexpr bool lds_powers(int r) { return r >= 8; }
+
 // One stage: nb butterflies of radix r at stride l (the product of the
 // radices before it); its twiddles W_{l r}^{j k}, 1 <= j < r, k < l, sit at
-// tw + (j - 1) l + k of the schedule's table.  ml, mnb: reciprocals for
-// fast_div by l and nb.
+// tw + (j - 1) l + k of the schedule's table, or, where lds_powers(r), W_{l r}^k
+// alone in FP64 from tw on (counted in float32 entries, even).  ml, mnb:
+// reciprocals for fast_div by l and nb.
 struct LdsStage {
     int r, l, nb, tw;
     uint32_t ml, mnb;
@@ -65,7 +71,7 @@ bool lds_schedule(int n, LdsSched *s, bool wide, int group = 1);
 // schedule (the last stage's butterflies of each in groups of `group`);
 // 0 if the form's largest workgroup cannot hold it.
 int lds_threads(const LdsSched &s, int tiles, int group, int form, bool column);
-// entries of the schedule's twiddle table (s.n - first radix)
+// float32 entries of the schedule's twiddle table (an FP64 entry is two), even
 int lds_table_size(const LdsSched &s);
 std::vector<c32> lds_table(const LdsSched &s);
 // the radices as the planner reports them: radix 9, 18, 24, 27 and 30 stages

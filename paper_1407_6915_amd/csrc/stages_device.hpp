@@ -5,10 +5,10 @@
 #include "stages.hpp"
 #include "tile.hpp"
 
-// (a register budget of four waves per SIMD, or two for the wide columns)
+// (a register budget of four waves per SIMD)
 #define STAGES_KERNEL(F, COLUMN)               \
     __launch_bounds__(form_threads(F, COLUMN)) \
-        __attribute__((amdgpu_waves_per_eu(form_threads(F, COLUMN) / 256, 4)))
+        __attribute__((amdgpu_waves_per_eu(4, 4)))
 
 namespace fftseg {
 namespace stages {
@@ -16,6 +16,39 @@ namespace stages {
 __device__ __forceinline__ int fast_div(int x, uint32_t m)
 {
     return m ? (int)__umulhi((unsigned)x, m) : x;
+}
+
+__device__ __forceinline__ c64 cmul(c64 a, c64 b)
+{
+    return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
+}
+__device__ __forceinline__ c32 rounded(c64 a) { return {(float)a.x, (float)a.y}; }
+
+// v[r] times first step^r, r < R: a stage's twiddles W^{r k} (from r = 1 on) or
+// the factors W^{m (b + r nb)} between two passes.  The powers run on in FP64, where
+// a step costs what one in float32 does, and each factor is rounded once;
+// products of two rounded factors in float32 left 2^24 points 2.03e-7 off where
+// this is 1.86e-7 (twiddles from pairs of table entries 1.99e-7), 48000 1.42e-7
+// and 1.40e-7.  One entry to read or keep in LDS in place of up to R also leaves the
+// kernels fewer registers: 2^24 samples of 48000 points 111 -> 104 us, of 2^24
+// 156 -> 152; one pass of 15625 points, whose stages wait for the chain, 80.7 ->
+// 82.8 (once-rounded products of FP64 pairs 84.7, an entry each 83.9).
+template <int R, int D>
+__device__ __forceinline__ void twiddle_powers(c32 *v, c64 first, c64 step)
+{
+    // (two chains: half the dependent products)
+    c64 even = first, odd = cmul(first, step);
+    const c64 two = cmul(step, step);
+#pragma unroll
+    for (int r = 0; r < R; r += 2) {
+        v[r] = twiddle<D>(v[r], rounded(even));
+        if (r + 1 < R)
+            v[r + 1] = twiddle<D>(v[r + 1], rounded(odd));
+        if (r + 2 < R)
+            even = cmul(even, two);
+        if (r + 3 < R)
+            odd = cmul(odd, two);
+    }
 }
 
 // Memory seen through a buffer descriptor: an access is at a uniform
@@ -32,6 +65,11 @@ struct Buffer {
     {
         return __builtin_bit_cast(c32,
                                   __builtin_amdgcn_raw_buffer_load_b64(r, lane, 8 * uniform, 0));
+    }
+    __device__ __forceinline__ c64 load_wide(unsigned lane, int uniform) const
+    {
+        return __builtin_bit_cast(c64,
+                                  __builtin_amdgcn_raw_buffer_load_b128(r, lane, 8 * uniform, 0));
     }
     __device__ __forceinline__ float load_float(unsigned lane, int uniform) const
     {
@@ -82,23 +120,9 @@ __device__ __forceinline__ void lds_stage(const Io &io, const LdsStage &st, bool
             if (st.l > 1) {
                 q = fast_div(b, st.ml);
                 k = b - q * st.l;
-                // radices from 12 on read theirs in pairs (tw_pair_low)
-                constexpr int R1 = tw_pair_low(R);
-                if constexpr (R1 > 0) {
-                    c32 wl[R1];
-#pragma unroll
-                    for (int j = 1; j < R1; ++j) {
-                        wl[j] = tw.load(8u * k, st.tw + (j - 1) * st.l);
-                        v[u][j] = twiddle<D>(v[u][j], wl[j]);
-                    }
-#pragma unroll
-                    for (int h = 1; h < R / R1; ++h) {
-                        const c32 wh = tw.load(8u * k, st.tw + (h * R1 - 1) * st.l);
-                        v[u][h * R1] = twiddle<D>(v[u][h * R1], wh);
-#pragma unroll
-                        for (int j = 1; j < R1; ++j)
-                            v[u][h * R1 + j] = twiddle<D>(v[u][h * R1 + j], cmul(wh, wl[j]));
-                    }
+                if constexpr (lds_powers(R)) {
+                    const c64 w = tw.load_wide(16u * k, st.tw);
+                    twiddle_powers<R - 1, D>(v[u] + 1, w, w);
                 } else {
 #pragma unroll
                     for (int r = 1; r < R; ++r)
@@ -161,41 +185,10 @@ __device__ __forceinline__ void run_stages(const Io &io, const LdsSched &s, c32 
     }
 }
 
-__device__ __forceinline__ c64 cmul(c64 a, c64 b)
-{
-    return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
-}
-__device__ __forceinline__ c32 rounded(c64 a) { return {(float)a.x, (float)a.y}; }
-
 // W^m from its two-level table
 __device__ __forceinline__ c64 two_level_root(const c64 *tl, const c64 *th, int sh, unsigned m)
 {
     return cmul(th[m >> sh], tl[m & ((1u << sh) - 1u)]);
-}
-
-// The factors between two passes: v[r] times W^{m (b + r nb)}, r < R, from
-// W^{m b} and W^{m nb}.  The powers run on in FP64, where a step costs what one
-// in float32 does, and each factor is rounded once (the product of two rounded
-// factors in float32: 2^24 points 2.03e-7 off where this is 1.99e-7, 48000
-// 1.42e-7 and 1.40e-7).  One factor a column in LDS in place of R also leaves
-// the kernels fewer registers (narrow columns 92 for 118, wide ones 125 for 156):
-// 2^24 samples of 48000 points 111 -> 106 us, of 2^24 156 -> 153.
-template <int R, int D>
-__device__ __forceinline__ void twiddle_powers(c32 *v, c64 first, c64 step)
-{
-    // (two chains: half the dependent products)
-    c64 even = first, odd = cmul(first, step);
-    const c64 two = cmul(step, step);
-#pragma unroll
-    for (int r = 0; r < R; r += 2) {
-        v[r] = twiddle<D>(v[r], rounded(even));
-        if (r + 1 < R)
-            v[r + 1] = twiddle<D>(v[r + 1], rounded(odd));
-        if (r + 2 < R)
-            even = cmul(even, two);
-        if (r + 3 < R)
-            odd = cmul(odd, two);
-    }
 }
 
 // Whole segments: transform c is segment c of the tile, its elements in

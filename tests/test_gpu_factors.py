@@ -58,3 +58,18 @@ def test_factors_between_passes_are_rounded_once(n, direction):
         at = n3 // 2
         got = impulse(n, at, direction)[::n1]
         assert off(got, roots(k[::n1] * at, n, direction)) <= ONCE
+
+
+# last radices from 15 to 32 in workgroups of both forms
+@pytest.mark.parametrize("direction", [fs.FORWARD, fs.INVERSE])
+@pytest.mark.parametrize("n", [225, 360, 625, 900, 8000, 12288, 15625, 20000, 20480])
+def test_stage_twiddles_are_rounded_once(n, direction):
+    """An impulse at r below the last radix R: the n/R-point transforms before the
+    last stage are exact, and output k < n/R, to which only input r of a
+    butterfly contributes, undivided, is the twiddle W_n^{r k}."""
+    announce("stage twiddles n=%d dir=%d" % (n, direction))
+    with fs.Plan(n, 1) as p:
+        assert p.describe()["passes"] == 1
+    k = np.arange(n // 32)
+    for r in (2, 5, 7, 11, 13):
+        assert off(impulse(n, r, direction)[:n // 32], roots(k * r, n, direction)) <= ONCE, r
