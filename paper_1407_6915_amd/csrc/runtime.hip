@@ -99,6 +99,17 @@ std::vector<c32> root_products(uint64_t n, uint64_t count)
     return t;
 }
 
+std::vector<c32> wide_root_products(uint64_t n, uint64_t count)
+{
+    const RootProducts w(n, count);
+    std::vector<c32> t(2 * count);
+    for (uint64_t m = 0; m < count; ++m) {
+        const c64 v = w.wide(m);
+        std::memcpy(&t[2 * m], &v, sizeof v);
+    }
+    return t;
+}
+
 std::vector<c32> root_table(uint64_t n)
 {
     // the upper half is the lower half's conjugates
@@ -808,8 +819,9 @@ int plan_build_real(Plan *p, uint64_t n, uint64_t batch, int dir)
                           {lds_table(p->stages.b), &p->tw2},
                           {w.low, &p->tl},
                           {w.high, &p->th},
-                          {root_products(n, (dir < 0 ? n1 : n2) / 2 + 1), &p->w1},
-                          {root_products(2 * (dir < 0 ? n2 : n1), dir < 0 ? n2 : n1), &p->w2}}) != FFT_OK)
+                          {wide_root_products(n, (dir < 0 ? n1 : n2) / 2 + 1), &p->w1},
+                          {wide_root_products(2 * (dir < 0 ? n2 : n1), dir < 0 ? n2 : n1),
+                           &p->w2}}) != FFT_OK)
         return last_status();
     p->scratch_bytes = p->sub_batch * p->stages.y_samples * sizeof(c32);
     if (hipMalloc(&p->scratch, p->scratch_bytes) != hipSuccess) {

@@ -85,6 +85,8 @@ struct RootProducts {
     }
 };
 std::vector<c32> root_products(uint64_t n, uint64_t count);
+// the same before the rounding, an FP64 entry in two places
+std::vector<c32> wide_root_products(uint64_t n, uint64_t count);
 // low bits of the index of a two-level table of W_n
 int two_level_shift(uint64_t n);
 const SinglePassDesc *find_single(uint64_t n, int variant);

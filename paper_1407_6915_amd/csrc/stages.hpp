@@ -118,7 +118,7 @@ hipError_t stages_rows(const StagesPlan &p, int dir, const void *y, void *out, c
                        uint64_t batch, hipStream_t s);
 // Real segments of N = 2n samples (plans of stages_choose with `real`): the
 // batch's rows of N float32 (n complex values) and of n + 1 bins.  One pass:
-// hw = W_N^k, k <= n/2.  Two: w1 = W_N^j for the first half of the paired
+// hw = W_N^k, k <= n/2.  Two, in FP64: w1 = W_N^j for the first half of the paired
 // rows (columns) j, w2 = W_{2 n2}^k, k < n2 (forward) or W_{2 n1}^i, i < n1
 // (inverse).
 hipError_t stages_real_one_pass(const StagesPlan &p, const void *in, void *out, const void *tw,

@@ -12,7 +12,9 @@
 // stage (forward) or before the first (inverse).  Two passes: Z[k1 + n1 k2]
 // and its partner sit in rows k1 and n1 - k1, so a row tile holds rows of
 // both kinds (forward); Z[i n2 + j] and its partner sit in columns j and
-// n2 - j, so a column tile does (inverse).  HBM sees 8 B per real sample in
+// n2 - j, so a column tile does (inverse); W_N^k there is the product of a
+// factor of the pair of rows (columns) and one of the place in them, in FP64 and
+// rounded once.  HBM sees 8 B per real sample in
 // one pass and 16 in two; a split pass of its own was 8 more.
 #include "runtime.hpp"
 #include "stages_device.hpp"
@@ -159,7 +161,7 @@ __global__ void STAGES_KERNEL(F, true)
 template <int F>
 __global__ void STAGES_KERNEL(F, false)
     stages_real_rows_kernel(const c32 *ybuf, c32 *out, const c32 *__restrict__ tw,
-                            const c32 *__restrict__ w1, const c32 *__restrict__ w2, LdsSched s,
+                            const c64 *__restrict__ w1, const c64 *__restrict__ w2, LdsSched s,
                             int n1, int lr, unsigned blocks, uint64_t tiles, uint64_t ysamples)
 {
     const uint64_t t = xcd_tile();
@@ -171,12 +173,12 @@ __global__ void STAGES_KERNEL(F, false)
     const RowIo<true> io{ybuf + seg * ysamples + ((uint64_t)blk << lr) * (unsigned)n2,
                          out + seg * (uint64_t)(m + 1), n1, (int)blk * half, lr, n1};
     run_stages<-1, F>(io, s, stage_lds, tw);
-    c32 wb[kAhead];
+    c64 wb[kAhead];
     int vk[kAhead], va[kAhead], vz[kAhead];  // k (< 0: none), slots of the pair
     // (a workgroup is whole waves, so a thread stays with one row pair)
     const int c = (int)threadIdx.x & (half - 1), k1 = io.first + c;
     const bool zero = k1 == 0, self = zero || 2 * k1 == n1, row = 2 * k1 <= n1;
-    const c32 wa = row ? w1[k1] : c32{0.f, 0.f};
+    const c64 wa = row ? w1[k1] : c64{0., 0.};
     walk_pairs(
         n2 << (lr - 1),
         [&](int e, int i) {
@@ -196,7 +198,7 @@ __global__ void STAGES_KERNEL(F, false)
             if (k < 0)
                 return;
             c32 lo, hi;
-            split_forward(stage_lds[va[i]], stage_lds[vz[i]], cmul(wa, wb[i]), lo, hi);
+            split_forward(stage_lds[va[i]], stage_lds[vz[i]], rounded(cmul(wa, wb[i])), lo, hi);
             io.y[k] = lo;
             if (2 * k != m)
                 io.y[m - k] = hi;
@@ -210,8 +212,8 @@ template <int F>
 __global__ void STAGES_KERNEL(F, true)
     stages_real_inverse_columns_kernel(const c32 *in, c32 *ybuf, const c32 *__restrict__ tw,
                                        const c64 *__restrict__ tl, const c64 *__restrict__ th,
-                                       int sh, const c32 *__restrict__ w1,
-                                       const c32 *__restrict__ w2, LdsSched s, int n2, int lc,
+                                       int sh, const c64 *__restrict__ w1,
+                                       const c64 *__restrict__ w2, LdsSched s, int n2, int lc,
                                        int lr, unsigned blocks, uint64_t tiles,
                                        uint64_t ysamples)
 {
@@ -224,12 +226,13 @@ __global__ void STAGES_KERNEL(F, true)
     ColumnIo<false, true> io{in + seg * (uint64_t)(m + 1), ybuf + seg * ysamples, nullptr, tl, th,
                              nullptr, sh, n2, first, lc, lr, (unsigned)n1};
     io.ws = column_factors(io, s);
-    c32 va[kAhead], vz[kAhead], wb[kAhead];
+    c32 va[kAhead], vz[kAhead];
+    c64 wb[kAhead];
     int vk[kAhead], sa[kAhead], sz[kAhead];  // k (< 0: none), slots of the pair
     // (a workgroup is whole waves, so a thread stays with one column pair)
     const int c = (int)threadIdx.x & (half - 1), j = first + c;
     const bool zero = j == 0, self = zero || 2 * j == n2, column = 2 * j <= n2;
-    const c32 wa = column ? w1[j] : c32{0.f, 0.f};
+    const c64 wa = column ? w1[j] : c64{0., 0.};
     walk_pairs(
         n1 << (lc - 1),
         [&](int e, int q) {
@@ -254,7 +257,7 @@ __global__ void STAGES_KERNEL(F, true)
             if (k == 0)
                 va[q].y = vz[q].y = 0.f;
             c32 lo, hi;
-            split_inverse(va[q], vz[q], cmul(wa, wb[q]), lo, hi);
+            split_inverse(va[q], vz[q], rounded(cmul(wa, wb[q])), lo, hi);
             stage_lds[sa[q]] = lo;
             if (k != 0 && 2 * k != m)
                 stage_lds[sz[q]] = hi;
@@ -280,7 +283,7 @@ hipError_t launch_segments(const StagesPlan &p, const c32 *in, c32 *out, const c
 
 template <int F>
 hipError_t launch_columns(const StagesPlan &p, const c32 *in, c32 *y, const c32 *tw,
-                          const c64 *tl, const c64 *th, int sh, const c32 *w1, const c32 *w2,
+                          const c64 *tl, const c64 *th, int sh, const c64 *w1, const c64 *w2,
                           uint64_t batch, hipStream_t s)
 {
     const size_t lds = columns_lds(p.a, p.lc);
@@ -301,8 +304,8 @@ hipError_t launch_columns(const StagesPlan &p, const c32 *in, c32 *y, const c32 
 }
 
 template <int F>
-hipError_t launch_rows(const StagesPlan &p, const c32 *y, c32 *out, const c32 *tw, const c32 *w1,
-                       const c32 *w2, uint64_t batch, hipStream_t s)
+hipError_t launch_rows(const StagesPlan &p, const c32 *y, c32 *out, const c32 *tw, const c64 *w1,
+                       const c64 *w2, uint64_t batch, hipStream_t s)
 {
     const size_t lds = rows_lds(p.b, p.lr);
     const hipError_t e = allow_lds(stages_real_rows_kernel<F>, lds);
@@ -333,14 +336,15 @@ hipError_t stages_real_two_pass(const StagesPlan &p, const void *in, void *out, 
     static constexpr auto fc = {launch_columns<kNarrow>, launch_columns<kMost>,
                                 launch_columns<kWide>};
     static constexpr auto fr = {launch_rows<kNarrow>, launch_rows<kMost>, launch_rows<kWide>};
-    const hipError_t e = fc.begin()[p.form_a](p, (const c32 *)in, (c32 *)y, (const c32 *)tw_a, (const c64 *)tl,
-                            (const c64 *)th, sh, (const c32 *)w1, (const c32 *)w2, batch, s);
+    const hipError_t e = fc.begin()[p.form_a](p, (const c32 *)in, (c32 *)y, (const c32 *)tw_a,
+                                              (const c64 *)tl, (const c64 *)th, sh,
+                                              (const c64 *)w1, (const c64 *)w2, batch, s);
     if (e != hipSuccess)
         return e;
     if (p.real > 0)
         return stages_rows(p, 1, y, out, tw_b, batch, s);
-    return fr.begin()[p.form_b](p, (const c32 *)y, (c32 *)out, (const c32 *)tw_b, (const c32 *)w1,
-              (const c32 *)w2, batch, s);
+    return fr.begin()[p.form_b](p, (const c32 *)y, (c32 *)out, (const c32 *)tw_b,
+                                (const c64 *)w1, (const c64 *)w2, batch, s);
 }
 
 }  // namespace fftseg

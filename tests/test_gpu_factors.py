@@ -73,3 +73,43 @@ def test_stage_twiddles_are_rounded_once(n, direction):
     k = np.arange(n // 32)
     for r in (2, 5, 7, 11, 13):
         assert off(impulse(n, r, direction)[:n // 32], roots(k * r, n, direction)) <= ONCE, r
+
+
+# half lengths in two passes: row and column pairs of odd and even lengths
+REAL = [1 << 16, 100000, 156250, 1 << 21, 3906250, 1 << 24]
+
+
+@pytest.mark.parametrize("n", REAL)
+def test_real_split_factors_forward_are_rounded_once(n):
+    """A one in sample 1: the even samples' transform is 0 and the odd samples' 1, so
+    bin k is the split's factor W_n^k."""
+    import torch
+    announce("real split factors n=%d" % n)
+    x = torch.zeros(n, dtype=torch.float32, device="cuda")
+    x[1] = 1
+    with fs.RealPlan(n, 1) as p:
+        assert p.describe()["passes"] == 2
+        y = p.exec(x).cpu().numpy()
+    assert off(y, roots(np.arange(n // 2 + 1), n, -1)) <= ONCE
+
+
+@pytest.mark.parametrize("n", REAL)
+def test_real_split_factors_inverse_are_rounded_once(n):
+    """Bins k and n/2 - k of 1 and -1 (of i and i): the split's sum is 0 and its
+    difference 2 (2 i), so the two elements that it makes of them add up to
+    4 i cos(2 pi k / n) (-4 i sin), which is samples 0 and 1 by themselves."""
+    import torch
+    announce("real split factors inverse n=%d" % n)
+    m = n // 2
+    ks = np.unique(np.random.default_rng(n).integers(1, m, 12))
+    ks = ks[2 * ks != m]
+    for one, other, want in ((1, -1, np.cos), (1j, 1j, lambda a: -np.sin(a))):
+        spec = torch.zeros(len(ks), m + 1, dtype=torch.complex64, device="cuda")
+        for s, k in enumerate(ks):
+            spec[s, int(k)] = one
+            spec[s, m - int(k)] = other
+        with fs.RealPlan(n, len(ks), fs.INVERSE) as p:
+            assert p.describe()["passes"] == 2
+            y = p.exec(spec.reshape(-1)).view(len(ks), n)[:, :2].cpu().numpy()
+        assert np.all(y[:, 0] == 0)
+        assert np.abs(y[:, 1].astype(np.float64) / 4 - want(2 * np.pi / n * ks)).max() <= ONCE
