@@ -45,24 +45,32 @@ const SinglePassDesc kIdx16384[] = {
         0, 0),
 };
 
-// the 65536-point two-pass tiles (256 x 256); the work-list tasks' arithmetic
+// the 65536-point two-pass tiles (256 x 256): as the plan's defaults, each
+// twiddle a table entry; and with the work-list tasks' arithmetic (twiddles from
+// pairs of entries), for lists whose size decides between those tasks and these
 const ColumnDesc kIdxCol65536 =
+    fs::ColInst<256, 16, 16, 4, fs::kNT | fs::kXcd | fs::kHoistLast | fs::kIndexed | fs::kLdsTw,
+                16, 16>::desc(0);
+const RowDesc kIdxRow65536 =
+    fs::RowInst<256, 16, 16, 4, fs::kNT | fs::kXcd | fs::kHoistLast | fs::kIndexed, 16,
+                16>::desc(0);
+const ColumnDesc kTaskCol65536 =
     fs::ColInst<256, 16, 16, 4,
                 fs::kNT | fs::kXcd | fs::kNoHoist | fs::kTwPair | fs::kIndexed | fs::kLdsTw, 16,
                 16>::desc(0);
-const RowDesc kIdxRow65536 =
+const RowDesc kTaskRow65536 =
     fs::RowInst<256, 16, 16, 4,
                 fs::kNT | fs::kXcd | fs::kNoHoist | fs::kTwPair | fs::kIndexed, 16,
                 16>::desc(0);
 
 }  // namespace
 
-bool indexed_four_step(uint32_t n, const ColumnDesc **col, const RowDesc **row)
+bool indexed_four_step(uint32_t n, bool as_tasks, const ColumnDesc **col, const RowDesc **row)
 {
     if (n != 65536)
         return false;
-    *col = &kIdxCol65536;
-    *row = &kIdxRow65536;
+    *col = as_tasks ? &kTaskCol65536 : &kIdxCol65536;
+    *row = as_tasks ? &kTaskRow65536 : &kIdxRow65536;
     return true;
 }
 

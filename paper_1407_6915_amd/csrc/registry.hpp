@@ -125,9 +125,10 @@ sp_rotated_launch_fn rotated_launcher(uint64_t n, int *variant, const void **ker
 // receives how many there are (0 for other lengths); null if none.
 const SinglePassDesc *indexed_table(uint32_t n, int *count);
 // The two passes over segments at listed offsets for the work list's
-// two-pass length n (kernels_indexed.hip); false if n has none.  Each
+// two-pass length n (kernels_indexed.hip), in the plan's tiles or (as_tasks) with
+// the arithmetic of the work-list kernel's tasks; false if n has none.  Each
 // segment's Y takes n + 16 samples of scratch.
-bool indexed_four_step(uint32_t n, const ColumnDesc **col, const RowDesc **row);
+bool indexed_four_step(uint32_t n, bool as_tasks, const ColumnDesc **col, const RowDesc **row);
 // single-pass instances with one LDS pad element every 32 (kernels_pad.hip)
 SinglePassDesc pad32_desc(int config, int variant, int grid_mult);
 // four-step tiles with radix-32 stages (kernels_radix32.hip)

@@ -324,20 +324,20 @@ int route_of(uint32_t n, int *grid_mult)
 
 // Route of a two-pass length: 0 = column and row tasks of the work-list
 // kernel, 1 = the two passes over the listed segments as launches of their
-// own (the plan's tiles, indexed; the tasks' arithmetic, so the bits are the
-// same).  Tuned, else 1 up to kIndexedTwoPass segments, one workgroup per
-// tile, and 0 above (lists of seven lengths in equal numbers: 570 segments of
+// own (indexed).  A tuned 1 takes the plan's tiles.  Untuned, 1 up to
+// kIndexedTwoPass segments, one workgroup per tile, in tiles with the tasks'
+// arithmetic (so that a segment's bits do not depend on the list's size), and 0
+// above (lists of seven lengths in equal numbers: 570 segments of
 // 65536 points 390 us by tasks, 309 indexed; 4570 2.30 ms and 2.19; 9140
 // 4.42 and 5.65).
 constexpr size_t kIndexedTwoPass = 4096;
-int route_two_pass(uint32_t n, size_t count, int *grid_mult)
+int route_two_pass(uint32_t n, size_t count, int *grid_mult, const ColumnDesc **c,
+                   const RowDesc **r)
 {
     *grid_mult = 0;
-    const ColumnDesc *c = nullptr;
-    const RowDesc *r = nullptr;
-    const bool have = indexed_four_step(n, &c, &r);
     int g = 0;
     const int t = tuned_wl_route(n, &g);
+    const bool have = indexed_four_step(n, t != 1, c, r);
     if (t == 0 || (t == 1 && have)) {
         *grid_mult = g;
         return t;
@@ -685,6 +685,8 @@ int wl_compile(WorkList *w, const fft_work_t *items, size_t n, std::vector<wl::T
     std::vector<Item> wide_items, idx_items, tp_items;
     std::vector<WorkList::IndexedRun> indexed;
     WorkList::IndexedTwoPass tp_idx;
+    const ColumnDesc *tp_col = nullptr;
+    const RowDesc *tp_row = nullptr;
     std::vector<WorkList::PlanRun> plan_runs;
     uint64_t plan_len = 0, plan_max_run = 0;
     uint64_t y_samples = 0;
@@ -716,9 +718,11 @@ int wl_compile(WorkList *w, const fft_work_t *items, size_t n, std::vector<wl::T
             for (uint32_t idx : b)
                 wide_items.push_back({items[idx].in_off, items[idx].out_off, 0});
             counts[L.a] += b.size();
-        } else if (int gm = 0, r = route_two_pass(L.n, b.size(), &gm); L.two_pass && r == 1) {
+        } else if (int gm = 0, r = route_two_pass(L.n, b.size(), &gm, &tp_col, &tp_row);
+                   L.two_pass && r == 1) {
             if (!b.empty()) {
-                indexed_four_step(L.n, &tp_idx.col, &tp_idx.row);
+                tp_idx.col = tp_col;
+                tp_idx.row = tp_row;
                 tp_idx.n = L.n;
                 tp_idx.count = (uint32_t)b.size();
                 tp_idx.grid_mult = gm;
@@ -1314,7 +1318,7 @@ extern "C" int fft_worklist_indexed_count(uint32_t segment_len)
     if (li && li->two_pass && !li->planned) {
         const ColumnDesc *c = nullptr;
         const RowDesc *r = nullptr;
-        return indexed_four_step(segment_len, &c, &r) ? 1 : 0;
+        return indexed_four_step(segment_len, false, &c, &r) ? 1 : 0;
     }
     if (!li || li->two_pass || li->wide || li->planned)
         return 0;
