@@ -184,10 +184,11 @@ struct Dft<3, D, S> {
         c32 s = cadd(b, c);
         c32 d = csub(b, c);
         c32 m = {a.x - 0.5f * s.x, a.y - 0.5f * s.y};
-        c32 r = mul_di<D>(c32{h * d.x, h * d.y});
+        // (one expression: the product is not rounded before the addition)
+        c32 r = mul_di<D>(d);
         v[0] = cadd(a, s);
-        v[S] = cadd(m, r);
-        v[2 * S] = csub(m, r);
+        v[S] = {m.x + h * r.x, m.y + h * r.y};
+        v[2 * S] = {m.x - h * r.x, m.y - h * r.y};
     }
 };
 

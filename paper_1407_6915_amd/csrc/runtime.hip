@@ -647,7 +647,7 @@ int plan_choose(Plan *p, uint64_t n, uint64_t batch, int dir, int forced_variant
     p->sp = find_single(n, variant);
     if (!p->sp && forced_variant < 0)
         p->sp = find_single(n, 0);
-    if (p->sp && forced_variant < 0 && tuned < 0) {
+    if (p->sp && p->by_batch && forced_variant < 0 && tuned < 0) {
         // a batch that gives the default kernel few workgroups (two per CU,
         // or one per eight) takes the length's small-batch kernel, if it has
         // one

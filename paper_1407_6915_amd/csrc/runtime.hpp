@@ -42,7 +42,8 @@ struct Plan {
     int grid_mult = 0;          // 0: one workgroup per tile
     bool own_grid = false;      // the kernels' own grid, not a tuned or forced one
     // false (set before plan_build): kernels that do not depend on the batch,
-    // so that a segment's spectrum is the same bits in any batch
+    // so that a segment's spectrum is the same bits in any batch (run-time schedules
+    // always are)
     bool by_batch = true;
     bool used = false;
     bool last_stream_valid = false;

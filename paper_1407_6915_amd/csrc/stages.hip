@@ -15,6 +15,10 @@
 // stages: 5.0 to 5.6 TB/s with two stages, 4.5 to 5.1 with three, 3.5 to 4.1
 // from 10000 points on; two passes move 4.2 to 5.3 with tiles of two
 // workgroups a CU and 2.5 to 3.9 with larger ones (2^26 samples).
+// (products fuse into additions within an expression, as the source has them, and not
+// across: a segment's bits then do not depend on the copy of an unrolled loop, or
+// on the form of the kernel, that a butterfly falls to)
+#pragma clang fp contract(on)
 #include "stages.hpp"
 
 #include <algorithm>
@@ -277,13 +281,29 @@ bool choose_form(int n, int tiles, int group, bool column, Tile *t)
     return false;
 }
 
+// The same schedule and form for a tile of 2^l transforms, fewer than they were chosen
+// for
+bool refit(Tile *t, int l, int group, bool column)
+{
+    t->l = l;
+    t->threads = lds_threads(t->s, 1 << l, group, t->form, column);
+    return t->threads > 0;
+}
+
 size_t tile_bytes(uint64_t n, int l, bool column)
 {
     return n * ((1u << l) + (column ? 1 : 0)) * sizeof(c32);
 }
+// What a tile counts for in the choice: a column tile its samples and a factor (c32)
+// for each output of its last stage's butterflies, more than it holds.  With what it
+// holds, 600- and 1200-point columns would come 16 wide, slower in 25 of the 90
+// plans that this changes (real inverse, 2^24 samples of 9 10^6: 56 us to 62).
 size_t tile_lds(const Tile &t, bool column)
 {
-    return column ? columns_lds(t.s, t.l) : rows_lds(t.s, t.l);
+    if (!column)
+        return rows_lds(t.s, t.l);
+    return ((size_t)t.s.n * ((1u << t.l) + 1) + ((size_t)t.s.st[t.s.ns - 1].r << t.l)) *
+           sizeof(c32);
 }
 
 // A tile of 2^l columns or rows of n points: the widest of 16 and 8 that
@@ -405,6 +425,7 @@ bool stages_choose(uint64_t n, uint64_t batch, int cus, StagesPlan *p, int real)
                (std::max(a, n / a) == std::max(b, n / b) && a < b);
     });
     double best = 1e30;
+    Tile ta, tb;
     for (uint64_t n1 : sizes) {
         const uint64_t n2 = n / n1;
         auto score = [&](int lc, int lr, bool lc2, bool lr2, bool groups, int stages) {
@@ -438,6 +459,8 @@ bool stages_choose(uint64_t n, uint64_t batch, int cus, StagesPlan *p, int real)
         if (cost >= best)
             continue;
         best = cost;
+        ta = a;
+        tb = b;
         p->passes = 2;
         p->a = a.s;
         p->b = b.s;
@@ -463,22 +486,21 @@ bool stages_choose(uint64_t n, uint64_t batch, int cus, StagesPlan *p, int real)
     }
     if (p->passes != 2)
         return false;
-    // few segments: narrower tiles until every CU has one
-    const uint64_t n1 = (uint64_t)p->a.n, n2 = (uint64_t)p->b.n;
+    // few segments: narrower tiles until every CU has one, of the same schedules (a
+    // segment's spectrum is the same bits in any batch)
+    const uint64_t n1 = (uint64_t)ta.s.n, n2 = (uint64_t)tb.s.n;
     while (p->lc > 2 && batch * ((n2 + (1u << p->lc) - 1) >> p->lc) < (uint64_t)cus)
         --p->lc;
     while (p->lr > 2 && batch * ((n1 + (1u << p->lr) - 1) >> p->lr) < (uint64_t)cus)
         --p->lr;
-    Tile a, b;
-    if (!choose_form((int)n1, 1 << p->lc, 1 << p->lr, true, &a) ||
-        !choose_form((int)n2, 1 << p->lr, 1, false, &b) || a.s.ns < 2)
+    if (!refit(&ta, p->lc, 1 << p->lr, true) || !refit(&tb, p->lr, 1, false))
         return false;
-    p->a = a.s;
-    p->form_a = a.form;
-    p->threads_a = a.threads;
-    p->b = b.s;
-    p->form_b = b.form;
-    p->threads_b = b.threads;
+    p->a = ta.s;
+    p->form_a = ta.form;
+    p->threads_a = ta.threads;
+    p->b = tb.s;
+    p->form_b = tb.form;
+    p->threads_b = tb.threads;
     // paired tiles: the columns or rows up to the middle one, half a tile's
     // slots each
     const uint64_t rows = real < 0 ? 2 * (n1 / 2 + 1) : n1;

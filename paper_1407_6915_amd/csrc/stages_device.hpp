@@ -36,14 +36,18 @@ __device__ __forceinline__ c32 rounded(c64 a) { return {(float)a.x, (float)a.y};
 template <int R, int D>
 __device__ __forceinline__ void twiddle_powers(c32 *v, c64 first, c64 step)
 {
+    if constexpr (D > 0) {
+        first.y = -first.y;
+        step.y = -step.y;
+    }
     // (two chains: half the dependent products)
     c64 even = first, odd = cmul(first, step);
     const c64 two = cmul(step, step);
 #pragma unroll
     for (int r = 0; r < R; r += 2) {
-        v[r] = twiddle<D>(v[r], rounded(even));
+        v[r] = cmul(v[r], rounded(even));
         if (r + 1 < R)
-            v[r + 1] = twiddle<D>(v[r + 1], rounded(odd));
+            v[r + 1] = cmul(v[r + 1], rounded(odd));
         if (r + 2 < R)
             even = cmul(even, two);
         if (r + 3 < R)

@@ -16,6 +16,10 @@
 // factor of the pair of rows (columns) and one of the place in them, in FP64 and
 // rounded once.  HBM sees 8 B per real sample in
 // one pass and 16 in two; a split pass of its own was 8 more.
+// (products fuse into additions within an expression, as the source has them, and not
+// across: a segment's bits then do not depend on the copy of an unrolled loop, or
+// on the form of the kernel, that a butterfly falls to)
+#pragma clang fp contract(on)
 #include "runtime.hpp"
 #include "stages_device.hpp"
 
