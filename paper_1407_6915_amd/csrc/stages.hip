@@ -290,6 +290,15 @@ bool refit(Tile *t, int l, int group, bool column)
     return t->threads > 0;
 }
 
+// threads for a tile of `samples`, `each` a thread
+int spread(uint64_t samples, int each, int threads, int form, bool column)
+{
+    const int most = form_threads(form, column);
+    const int want =
+        (int)std::min<uint64_t>((samples / (unsigned)each + 63) / 64 * 64, (uint64_t)most);
+    return std::max(threads, want);
+}
+
 size_t tile_bytes(uint64_t n, int l, bool column)
 {
     return n * ((1u << l) + (column ? 1 : 0)) * sizeof(c32);
@@ -489,9 +498,15 @@ bool stages_choose(uint64_t n, uint64_t batch, int cus, StagesPlan *p, int real)
     // few segments: narrower tiles until every CU has one, of the same schedules (a
     // segment's spectrum is the same bits in any batch)
     const uint64_t n1 = (uint64_t)ta.s.n, n2 = (uint64_t)tb.s.n;
-    while (p->lc > 2 && batch * ((n2 + (1u << p->lc) - 1) >> p->lc) < (uint64_t)cus)
+    // (paired tiles of 4 slots move runs of 2: only where 8 slots leave more than half of
+    // the CUs without one; two real segments of 2^21 samples forward 38.9 us and 35.6)
+    auto few = [&](uint64_t of, int l, bool paired) {
+        const uint64_t tiles = batch * ((of + (1u << l) - 1) >> l);
+        return l > 2 && tiles < (uint64_t)cus / (paired && l == 3 ? 2 : 1);
+    };
+    while (few(n2, p->lc, real > 0))
         --p->lc;
-    while (p->lr > 2 && batch * ((n1 + (1u << p->lr) - 1) >> p->lr) < (uint64_t)cus)
+    while (few(n1, p->lr, real < 0))
         --p->lr;
     if (!refit(&ta, p->lc, 1 << p->lr, true) || !refit(&tb, p->lr, 1, false))
         return false;
@@ -508,6 +523,17 @@ bool stages_choose(uint64_t n, uint64_t batch, int cus, StagesPlan *p, int real)
     p->blocks_a = (unsigned)((columns + (1u << p->lc) - 1) >> p->lc);
     p->blocks_b = (unsigned)((rows + (1u << p->lr) - 1) >> p->lr);
     p->y_samples = ((uint64_t)p->blocks_b << p->lr) * n2;
+    // a pass with at most two tiles a CU waits for each tile's own chain of loads, stages
+    // and stores: a thread for every 4 samples of a tile that has a CU to itself (one
+    // real segment of 2^19 samples forward, tiles of 64 threads 21.2 us, of 512 15.2;
+    // of 2^18 17.6 and 13.1), for every 16 of two (with 4 there, 2^18-sample segments
+    // forward 16 of them 34 us against 26)
+    auto each = [&](uint64_t tiles) { return tiles <= (uint64_t)cus ? 4 : 16; };
+    const uint64_t tiles_a = batch * p->blocks_a, tiles_b = batch * p->blocks_b;
+    if (tiles_a <= 2 * (uint64_t)cus)
+        p->threads_a = spread(n1 << p->lc, each(tiles_a), p->threads_a, p->form_a, true);
+    if (tiles_b <= 2 * (uint64_t)cus)
+        p->threads_b = spread(n2 << p->lr, each(tiles_b), p->threads_b, p->form_b, false);
     return true;
 }
 
