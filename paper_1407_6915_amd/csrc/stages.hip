@@ -45,6 +45,35 @@ __global__ void STAGES_KERNEL(F, false)
     run_stages<D, F>(io, s, stage_lds, tw);
 }
 
+// Segments of one stage (3 and 5 points; 2 and 4 have compiled tiles): a segment a
+// thread, no LDS.  Bound by HBM; in the kernel above, whose registers are those of a
+// 25-point butterfly, four waves a SIMD were too few for the short loads (2^24
+// samples of 3 points 45 us, here 40; of 5 points 60 and 43).  The grid is bounded, and
+// the threads walk: a launch holds fewer than 2^32 threads.
+template <int R, int D>
+__global__ void __launch_bounds__(256)
+    stages_short_kernel(const c32 *in, c32 *out, uint64_t batch, uint64_t hop,
+                        const float *__restrict__ window)
+{
+    for (uint64_t seg = (uint64_t)blockIdx.x * 256 + threadIdx.x; seg < batch;
+         seg += (uint64_t)gridDim.x * 256) {
+        const c32 *x = in + seg * hop;
+        c32 v[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            v[r] = x[r];
+        if (window)
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                v[r] = c32{v[r].x * window[r], v[r].y * window[r]};
+        dft<R, D>(v);
+        c32 *y = out + seg * R;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            y[r] = v[r];
+    }
+}
+
 template <int D, int F>
 __global__ void STAGES_KERNEL(F, true)
     stages_columns_kernel(const c32 *in, c32 *ybuf, const c32 *__restrict__ tw,
@@ -555,6 +584,20 @@ hipError_t launch_segments(const StagesPlan &p, const c32 *in, c32 *out, const c
     return hipGetLastError();
 }
 
+template <int R>
+hipError_t launch_short(int dir, const c32 *in, c32 *out, uint64_t batch, uint64_t hop,
+                        const float *window, hipStream_t s)
+{
+    const dim3 grid((unsigned)std::min<uint64_t>((batch + 255) / 256, 1u << 20));
+    if (dir < 0)
+        hipLaunchKernelGGL((stages_short_kernel<R, -1>), grid, dim3(256), 0, s, in, out, batch,
+                           hop, window);
+    else
+        hipLaunchKernelGGL((stages_short_kernel<R, 1>), grid, dim3(256), 0, s, in, out, batch,
+                           hop, window);
+    return hipGetLastError();
+}
+
 template <int D, int F>
 hipError_t launch_columns(const StagesPlan &p, const c32 *in, c32 *y, const c32 *tw,
                           const c64 *tl, const c64 *th, int sh, uint64_t batch, uint64_t hop,
@@ -610,6 +653,9 @@ hipError_t stages_one_pass(const StagesPlan &p, int dir, const void *in, void *o
                            const void *tw, uint64_t batch, uint64_t hop, const float *window,
                            hipStream_t s)
 {
+    if (p.a.n == 3 || p.a.n == 5)
+        return (p.a.n == 3 ? launch_short<3> : launch_short<5>)(dir, (const c32 *)in, (c32 *)out,
+                                                                batch, hop, window, s);
     static constexpr auto f = {launch_segments<-1, kNarrow>, launch_segments<-1, kMost>,
                                launch_segments<-1, kWide>,   launch_segments<1, kNarrow>,
                                launch_segments<1, kMost>,    launch_segments<1, kWide>};

@@ -20,6 +20,8 @@
 // across: a segment's bits then do not depend on the copy of an unrolled loop, or
 // on the form of the kernel, that a butterfly falls to)
 #pragma clang fp contract(on)
+#include <algorithm>
+
 #include "runtime.hpp"
 #include "stages_device.hpp"
 
@@ -278,10 +280,16 @@ hipError_t launch_segments(const StagesPlan &p, const c32 *in, c32 *out, const c
     const hipError_t e = allow_lds(stages_real_segments_kernel<D, F>, lds);
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL((stages_real_segments_kernel<D, F>),
-                       dim3((unsigned)((batch + p.segs - 1) / p.segs)), dim3(p.threads_a),
-                       (unsigned)lds, s, in, out, tw, hw, p.a, p.segs, reciprocal(p.a.n / 2 + 1),
-                       batch);
+    // (a launch holds fewer than 2^32 threads: more segments of 6 samples fit the memory)
+    const uint64_t most = ((1ull << 31) / (unsigned)p.threads_a) * (unsigned)p.segs;
+    const uint64_t ir = (uint64_t)p.a.n + (D > 0), orow = (uint64_t)p.a.n + (D < 0);
+    for (uint64_t s0 = 0; s0 < batch; s0 += most) {
+        const uint64_t sb = std::min(most, batch - s0);
+        hipLaunchKernelGGL((stages_real_segments_kernel<D, F>),
+                           dim3((unsigned)((sb + p.segs - 1) / p.segs)), dim3(p.threads_a),
+                           (unsigned)lds, s, in + s0 * ir, out + s0 * orow, tw, hw, p.a, p.segs,
+                           reciprocal(p.a.n / 2 + 1), sb);
+    }
     return hipGetLastError();
 }
 
