@@ -800,18 +800,19 @@ int plan_build_real(Plan *p, uint64_t n, uint64_t batch, int dir)
     if (!stages_choose(m, batch, device_cus(p->device), &p->stages, dir))
         return set_error(FFT_ERR_UNSUPPORTED_LENGTH, "no schedule for length %llu",
                          (unsigned long long)m);
-    // (the cap on a sub-batch refuses what a plan of m points refuses)
+    // (a cap below one segment is refused as for a plan of m points, also in one pass)
     if (max_scratch_samples() < m)
         return set_error(FFT_ERR_INVALID_ARG,
-                         "one %llu-point segment needs more scratch than %llu samples",
+                         "a %llu-point segment is above the cap of %llu samples on a sub-batch",
                          (unsigned long long)m, (unsigned long long)max_scratch_samples());
     if (p->stages.passes == 1) {
         p->sub_batch = batch;
         return upload_tables(
             p, {{lds_table(p->stages.a), &p->tw}, {root_products(n, m / 2 + 1), &p->w1}});
     }
-    const uint64_t max_sub_samples = 1ull << 28;  // 2 GiB of complex64, before Y's padding
-    p->sub_batch = std::max<uint64_t>(1, std::min<uint64_t>(batch, max_sub_samples / m));
+    // 2 GiB of complex64, before Y's padding, or what FFTSEG_SUB_SAMPLES allows
+    const uint64_t max_sub_samples = std::min<uint64_t>(max_scratch_samples(), 1ull << 28);
+    p->sub_batch = std::min<uint64_t>(batch, max_sub_samples / m);
     const uint64_t n1 = (uint64_t)p->stages.a.n, n2 = (uint64_t)p->stages.b.n;
     const TwoLevel w(m, true);
     p->sh = w.sh;
