@@ -425,8 +425,10 @@ int fft_exec_segments_graph(fft_plan_t plan, const void *in, void *out, void *st
  * resident workgroup waves per CU (two-pass lengths: every column-tile x
  * row-tile variant of the planner's split n1 x n2, columns/rows per
  * workgroup, tile order, streamed access, and the default tiles of every
- * other split n1' x n/n1' with compiled tiles, at each grid size), on
- * device buffers of batch segments it allocates and frees.  The fastest
+ * other split n1' x n/n1' with compiled tiles, at each grid size), and the
+ * untuned plan, on device buffers of batch segments it allocates and frees.
+ * Where the untuned plan is fastest, later plans stay as without tuning
+ * (their kernels and grids follow their batch).  The fastest
  * choice goes into the process-wide tuning table used by later plans and,
  * if path != NULL, is merged into that JSON cache file.  For a one-pass
  * length that work lists support it also picks the work-list route (Sec.
@@ -434,7 +436,7 @@ int fft_exec_segments_graph(fft_plan_t plan, const void *in, void *out, void *st
  * or a launch of its own through each indexed one-pass kernel of the length
  * at each grid size, timed on `batch` segments packed at odd offsets; work
  * lists built later use the winner.  Returns the number
- * of configurations timed (negative status on error); *best_us (may be
+ * of configurations timed, the untuned plan left out (negative status on error); *best_us (may be
  * NULL) receives the winner's time per exec in microseconds. */
 int fft_autotune(size_t segment_len, size_t batch, int direction, const char *path,
                  double *best_us);

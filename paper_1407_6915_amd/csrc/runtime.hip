@@ -237,7 +237,7 @@ int tuned_variant(uint64_t n)
     std::lock_guard<std::mutex> lk(g_tune_mu);
     for (auto &p : g_tuned)
         if (p.n == n)
-            return p.variant;
+            return p.keep ? -1 : p.variant;
     return -1;
 }
 
@@ -245,7 +245,7 @@ int tuned_grid_mult(uint64_t n, int variant, int fallback)
 {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     for (auto &p : g_tuned)
-        if (p.n == n && p.variant == variant)
+        if (p.n == n && p.variant == variant && !p.keep)
             return p.grid_mult;
     return fallback;
 }
@@ -254,7 +254,7 @@ bool tuned_split_variants(uint64_t n, int *col_variant, int *row_variant, uint64
 {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     for (auto &p : g_tuned)
-        if (p.n == n && p.variant < 0) {
+        if (p.n == n && p.variant == -1 && !p.keep) {
             *col_variant = p.col_variant;
             *row_variant = p.row_variant;
             *n1 = p.n1;
@@ -640,7 +640,7 @@ int plan_choose(Plan *p, uint64_t n, uint64_t batch, int dir, int forced_variant
         p->kind = Plan::COPY;
         return set_ok();
     }
-    const int tuned = forced_variant >= 0 ? -1 : tuned_variant(n);
+    const int tuned = forced_variant >= 0 || p->untuned ? -1 : tuned_variant(n);
     int variant = forced_variant >= 0 ? forced_variant : tuned;
     if (variant < 0)
         variant = 0;
@@ -663,7 +663,7 @@ int plan_choose(Plan *p, uint64_t n, uint64_t batch, int dir, int forced_variant
     if (p->sp) {
         p->kind = Plan::SINGLE;
         if (!getenv("FFTSEG_GRID_MULT")) {
-            const int g = tuned_grid_mult(n, p->sp->variant, -1);
+            const int g = p->untuned ? -1 : tuned_grid_mult(n, p->sp->variant, -1);
             p->own_grid = g < 0;
             p->grid_mult = p->own_grid ? p->sp->grid_mult : g;
         }
@@ -672,15 +672,15 @@ int plan_choose(Plan *p, uint64_t n, uint64_t batch, int dir, int forced_variant
     p->sh = two_level_shift(n);
     int cv = 0, rv = 0;
     uint64_t n1 = forced_n1;
+    bool tuned_tiles = false;
     if (forced_split_variants >= 0) {
         cv = forced_split_variants & 0xff;
         rv = (forced_split_variants >> 8) & 0xff;
-    } else if (!forced_n1) {
-        tuned_split_variants(n, &cv, &rv, &n1);
+    } else if (!forced_n1 && !p->untuned) {
+        tuned_tiles = tuned_split_variants(n, &cv, &rv, &n1);
     }
     bool split = find_split(n, &p->col, &p->row, cv, rv, n1);
-    if (split && p->by_batch && forced_split_variants < 0 && !forced_n1 &&
-        !tuned_split_variants(n, &cv, &rv, &n1))
+    if (split && p->by_batch && forced_split_variants < 0 && !forced_n1 && !tuned_tiles)
         p->row = row_for_batch(p->row, (uint64_t)p->col->n1, batch, device_cus(p->device));
     if (!split && n1 && !forced_n1)
         split = find_split(n, &p->col, &p->row, 0, 0, 0);  // a tuned split the library lacks
@@ -688,7 +688,7 @@ int plan_choose(Plan *p, uint64_t n, uint64_t batch, int dir, int forced_variant
         return set_error(FFT_ERR_INVALID_ARG, "length %llu has no split with %llu columns",
                          (unsigned long long)n, (unsigned long long)forced_n1);
     if (!getenv("FFTSEG_GRID_MULT")) {
-        const int g = tuned_grid_mult(n, -1, -1);
+        const int g = p->untuned ? -1 : tuned_grid_mult(n, -1, -1);
         p->own_grid = g < 0;
         p->grid_mult = !p->own_grid ? g
                        : split      ? two_pass_grid_mult((uint64_t)p->col->n1)
@@ -974,6 +974,41 @@ hipError_t stages_enqueue(const Plan *p, const void *in, void *out, uint64_t bat
     return hipSuccess;
 }
 
+// the grid of a one-pass plan whose output starts out_m samples into a line
+static unsigned single_grid(const Plan *p, uint64_t batch, uint64_t out_m)
+{
+    // (streamed stores that split 64-byte blocks: consecutive workgroups
+    // close together write the halves in time; 1536 points, 2^25 samples
+    // at an output base of 24 bytes 118 us against 130 walking)
+    const SinglePassDesc *d = p->sp;
+    return grid_for(d->kernel[p->dir > 0], d->threads * d->segs_per_wg,
+                    (batch + d->segs_per_wg - 1) / d->segs_per_wg, p->device, p->grid_mult,
+                    p->own_grid && !(d->nontemporal && out_m % 8) ? d->walk : 1);
+}
+
+static unsigned real_grid(const Plan *p, uint64_t batch)
+{
+    const SinglePassDesc *d = p->sp;
+    return grid_for(d->kernel_real[p->dir > 0], d->threads * d->segs_per_wg,
+                    (batch + d->segs_per_wg - 1) / d->segs_per_wg, p->device, p->grid_mult,
+                    p->own_grid ? d->walk_aux : 1);
+}
+
+// the grids of a two-pass plan's passes over sb segments
+static unsigned column_grid(const Plan *p, uint64_t sb)
+{
+    const ColumnDesc *d = p->col;
+    return tile_grid(p, d->kernel[p->dir > 0], d->threads * d->cols,
+                     sb * (p->n2 / (uint64_t)d->cols), one_wave_columns(p->n1));
+}
+
+static unsigned row_grid(const Plan *p, uint64_t sb)
+{
+    const RowDesc *d = p->row;
+    return tile_grid(p, d->kernel[p->dir > 0], d->threads * d->rows,
+                     sb * (p->n1 / (uint64_t)d->rows), one_wave_rows(p->n2));
+}
+
 // enqueue the transform of `batch` segments (arguments already checked)
 int plan_enqueue(Plan *p, const void *in, void *out, uint64_t batch, hipStream_t s)
 {
@@ -1008,23 +1043,11 @@ int plan_enqueue(Plan *p, const void *in, void *out, uint64_t batch, hipStream_t
                 break;
             }
         }
-        // (streamed stores that split 64-byte blocks: consecutive workgroups
-        // close together write the halves in time; 1536 points, 2^25 samples
-        // at an output base of 24 bytes 118 us against 130 walking)
-        const unsigned grid = grid_for(d->kernel[dir > 0], d->threads * d->segs_per_wg,
-                                       groups, p->device, p->grid_mult,
-                                       p->own_grid && !(d->nontemporal && out_m % 8) ? d->walk
-                                                                                     : 1);
-        d->launch(dir, in, out, p->tw, batch, grid, s);
+        d->launch(dir, in, out, p->tw, batch, single_grid(p, batch, out_m), s);
         break;
     }
     case Plan::REAL: {
-        const SinglePassDesc *d = p->sp;
-        const uint64_t groups = (batch + d->segs_per_wg - 1) / d->segs_per_wg;
-        const unsigned grid = grid_for(d->kernel_real[dir > 0], d->threads * d->segs_per_wg,
-                                       groups, p->device, p->grid_mult,
-                                       p->own_grid ? d->walk_aux : 1);
-        d->launch_real(dir, in, out, p->tw, p->tw2, batch, grid, s);
+        p->sp->launch_real(dir, in, out, p->tw, p->tw2, batch, real_grid(p, batch), s);
         break;
     }
     case Plan::REAL_STAGES: {
@@ -1088,12 +1111,7 @@ int plan_enqueue(Plan *p, const void *in, void *out, uint64_t batch, hipStream_t
             const uint64_t sb = std::min(p->sub_batch, batch - s0);
             const c32 *x = (const c32 *)in + s0 * n;
             c32 *y = (c32 *)out + s0 * n;
-            const uint64_t ta = sb * (p->n2 / (uint64_t)cd->cols);
-            const uint64_t tb = sb * (p->n1 / (uint64_t)rd->rows);
-            const unsigned ga = tile_grid(p, cd->kernel[dir > 0], cd->threads * cd->cols, ta,
-                                          one_wave_columns(p->n1));
-            const unsigned gb = tile_grid(p, rd->kernel[dir > 0], rd->threads * rd->rows, tb,
-                                          one_wave_rows(p->n2));
+            const unsigned ga = column_grid(p, sb), gb = row_grid(p, sb);
             (p->y_blocked ? cd->launch_yblocked : cd->launch)(dir, x, p->scratch, p->tw, p->tl,
                                                               p->th, p->sh, (int)p->n2, sb,
                                                               ga, s);
@@ -1138,11 +1156,11 @@ int plan_describe(const Plan *p, std::string &js)
                  "\"variant\":%d,\"radices\":%s,\"threads_per_segment\":%d,"
                  "\"segments_per_workgroup\":%d,\"lds_pad_shift\":%d,\"nontemporal\":%d,"
                  "\"lds_bytes\":%d,\"shuffle_exchange\":%d,\"grid_mult\":%d,"
-                 "\"scratch_bytes\":0}",
+                 "\"workgroups\":%u,\"scratch_bytes\":0}",
                  (unsigned long long)p->n, (unsigned long long)p->batch, p->dir,
                  p->sp->variant, rad(p->sp->radices, p->sp->nrad).c_str(), p->sp->threads,
                  p->sp->segs_per_wg, p->sp->pad_shift, p->sp->nontemporal,
-                 p->sp->lds_bytes, p->sp->shuffle, p->grid_mult);
+                 p->sp->lds_bytes, p->sp->shuffle, p->grid_mult, single_grid(p, p->batch, 0));
         break;
     case Plan::FOURSTEP:
         snprintf(buf, sizeof buf,
@@ -1151,23 +1169,25 @@ int plan_describe(const Plan *p, std::string &js)
                  "\"columns_per_workgroup\":%d,\"rows_per_workgroup\":%d,"
                  "\"column_variant\":%d,\"row_variant\":%d,\"grid_mult\":%d,"
                  "\"lds_bytes\":[%d,%d],\"sub_batch\":%llu,\"scratch_bytes\":%zu,"
-                 "\"y_blocked\":%d}",
+                 "\"y_blocked\":%d,\"workgroups\":[%u,%u]}",
                  (unsigned long long)p->n, (unsigned long long)p->batch, p->dir,
                  (unsigned long long)p->n1, (unsigned long long)p->n2,
                  rad(p->col->radices, p->col->nrad).c_str(),
                  rad(p->row->radices, p->row->nrad).c_str(), p->col->cols, p->row->rows,
                  p->col->variant, p->row->variant, p->grid_mult,
                  p->col->lds_bytes, p->row->lds_bytes, (unsigned long long)p->sub_batch,
-                 p->scratch_bytes, (int)p->y_blocked);
+                 p->scratch_bytes, (int)p->y_blocked, column_grid(p, p->sub_batch),
+                 row_grid(p, p->sub_batch));
         break;
     case Plan::REAL:
         snprintf(buf, sizeof buf,
                  "{\"kind\":\"real\",\"n\":%llu,\"batch\":%llu,\"direction\":%d,"
                  "\"complex_length\":%llu,\"radices\":%s,\"threads_per_segment\":%d,"
-                 "\"segments_per_workgroup\":%d,\"grid_mult\":%d,\"scratch_bytes\":0}",
+                 "\"segments_per_workgroup\":%d,\"grid_mult\":%d,"
+                 "\"workgroups\":%u,\"scratch_bytes\":0}",
                  (unsigned long long)p->n, (unsigned long long)p->batch, p->dir,
                  (unsigned long long)(p->n / 2), rad(p->sp->radices, p->sp->nrad).c_str(),
-                 p->sp->threads, p->sp->segs_per_wg, p->grid_mult);
+                 p->sp->threads, p->sp->segs_per_wg, p->grid_mult, real_grid(p, p->batch));
         break;
     case Plan::REAL_STAGES: {
         std::vector<int> r;

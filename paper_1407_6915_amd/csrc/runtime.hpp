@@ -45,6 +45,7 @@ struct Plan {
     // so that a segment's spectrum is the same bits in any batch (run-time schedules
     // always are)
     bool by_batch = true;
+    bool untuned = false;       // set before plan_build: as if nothing were tuned
     bool used = false;
     bool last_stream_valid = false;
     hipStream_t last_stream = nullptr;
@@ -159,6 +160,9 @@ struct TunedChoice {
     int wl_route = -1;
     int wl_grid = 0;
     double wl_us = 0;  // its measured time per exec
+    // the untuned plan was the fastest: plans keep their own kernels and grids by
+    // batch (variant, grid_mult and the tiles above: what they were at `batch`)
+    bool keep = false;
 };
 // persistent grid of the four-step passes by column length: resident
 // workgroup waves per CU

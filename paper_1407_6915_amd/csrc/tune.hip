@@ -207,7 +207,7 @@ int write_cache(const char *path)
     if (read_file(path, old) && arch_of(old) == arch) {
         for (const std::string &o : entry_objects(old)) {
             double n = 0, v = 0, g = 0, us = 0, b = 0, cv = 0, rv = 0, n1 = 0;
-            double wr = -1, wg = 0, wus = 0;
+            double wr = -1, wg = 0, wus = 0, keep = 0;
             if (!read_number(o, "n", &n) || !read_number(o, "variant", &v) ||
                 !read_number(o, "grid_mult", &g))
                 continue;
@@ -219,6 +219,7 @@ int write_cache(const char *path)
             read_number(o, "wl_route", &wr);
             read_number(o, "wl_grid", &wg);
             read_number(o, "wl_us", &wus);
+            read_number(o, "keep_defaults", &keep);
             bool have = false;
             for (auto &m : merged)
                 have |= m.n == (uint64_t)n;
@@ -228,6 +229,7 @@ int write_cache(const char *path)
                 c.wl_route = (int)wr;
                 c.wl_grid = (int)wg;
                 c.wl_us = wus;
+                c.keep = keep != 0;
                 merged.push_back(c);
             }
         }
@@ -243,11 +245,12 @@ int write_cache(const char *path)
         fprintf(f,
                 "    {\"n\": %llu, \"variant\": %d, \"grid_mult\": %d, \"us\": %.3f, "
                 "\"batch\": %llu, \"column_variant\": %d, \"row_variant\": %d, "
-                "\"n1\": %llu, \"wl_route\": %d, \"wl_grid\": %d, \"wl_us\": %.3f}%s\n",
+                "\"n1\": %llu, \"wl_route\": %d, \"wl_grid\": %d, \"wl_us\": %.3f, "
+                "\"keep_defaults\": %d}%s\n",
                 (unsigned long long)merged[i].n, merged[i].variant, merged[i].grid_mult,
                 merged[i].us, (unsigned long long)merged[i].batch, merged[i].col_variant,
                 merged[i].row_variant, (unsigned long long)merged[i].n1, merged[i].wl_route,
-                merged[i].wl_grid, merged[i].wl_us, i + 1 < merged.size() ? "," : "");
+                merged[i].wl_grid, merged[i].wl_us, (int)merged[i].keep, i + 1 < merged.size() ? "," : "");
     fprintf(f, "  ]\n}\n");
     fclose(f);
     if (rename(tmp.c_str(), path) != 0)
@@ -347,6 +350,26 @@ extern "C" int fft_autotune(size_t segment_len, size_t batch, int direction, con
                 }
             }
         }
+        // the untuned plan, whose grid no multiple may give (tile_grid, the walk of
+        // grid_for) and which chooses by the batch: the choice where it is not slower
+        // (of the timed configurations it is one more, and not counted)
+        if (st == FFT_OK) {
+            Plan p;
+            p.untuned = true;
+            double us = 0;
+            if ((st = plan_build(&p, segment_len, batch, direction, -1)) == FFT_OK &&
+                (st = time_plan(&p, in, out, s, 5, &us)) == FFT_OK && us <= best) {
+                best = us;
+                choice.variant = p.kind == Plan::SINGLE ? p.sp->variant : -1;
+                choice.col_variant = p.kind == Plan::FOURSTEP ? p.col->variant : 0;
+                choice.row_variant = p.kind == Plan::FOURSTEP ? p.row->variant : 0;
+                choice.n1 = p.kind == Plan::FOURSTEP ? p.n1 : 0;
+                choice.grid_mult = p.grid_mult;
+                choice.us = us;
+                choice.keep = true;
+            }
+            plan_free(&p);
+        }
         (void)hipStreamSynchronize(s);
         (void)hipFree(in);
         (void)hipFree(out);
@@ -395,7 +418,7 @@ extern "C" int fft_tune_load(const char *path)
         int k = 0;
         for (const std::string &o : entry_objects(js)) {
             double n = 0, v = 0, g = 0, us = 0, b = 0, cv = 0, rv = 0, n1 = 0;
-            double wr = -1, wg = 0, wus = 0;
+            double wr = -1, wg = 0, wus = 0, keep = 0;
             if (!read_number(o, "n", &n) || !read_number(o, "variant", &v) ||
                 !read_number(o, "grid_mult", &g))
                 continue;
@@ -405,6 +428,7 @@ extern "C" int fft_tune_load(const char *path)
             read_number(o, "wl_route", &wr);
             read_number(o, "wl_grid", &wg);
             read_number(o, "wl_us", &wus);
+            read_number(o, "keep_defaults", &keep);
             int ncol = 0, nrow = 0;
             if (v < 0)
                 split_variant_counts((uint64_t)n, &ncol, &nrow);
@@ -425,6 +449,7 @@ extern "C" int fft_tune_load(const char *path)
             c.wl_route = (int)wr;
             c.wl_grid = (int)wg;
             c.wl_us = wus;
+            c.keep = keep != 0;
             set_tuned(c);
             ++k;
         }
