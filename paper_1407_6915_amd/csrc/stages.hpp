@@ -65,7 +65,8 @@ constexpr int form_threads(int form, bool column)
 // The schedule of an n-point transform (n >= 2, prime factors 2, 3, 5);
 // false if it would take more than kMaxLdsStages stages.  group > 1: the
 // last stage's lanes take butterflies in groups of `group` (column pass), so
-// the last radix is the one that fills them best.  wide: radices above 16.
+// the last radix is the one that fills them best.  group 0: whole segments, a
+// segment's butterflies on consecutive lanes.  wide: radices above 16.
 bool lds_schedule(int n, LdsSched *s, bool wide, int group = 1);
 // Threads of a workgroup whose tile holds `tiles` transforms of the
 // schedule (the last stage's butterflies of each in groups of `group`);
