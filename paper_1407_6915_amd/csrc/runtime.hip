@@ -468,9 +468,10 @@ int split_variant_counts(uint64_t n, int *ncol, int *nrow)
 // which 1024 threads hold), the length's narrow tile (one segment of 2^19
 // points 17.8 us to 14.7, of 2^21 45.7 to 29.6; at more tiles the 64-byte
 // runs cost more: four of 2^18 15.1 us to 15.9), else up to 2^26 samples the
-// length's tile for that range (1024 points: streamed loads and stores, 64
-// segments of 2^20 513 us to 478; from 2^27 on the cached tile is 1 to 5 %
-// faster).
+// length's tile for that range (1024 points: streamed loads and stores, both tiles
+// on their own grids (tile_grid): segments of 2^20, 2^24 samples 114 us to 102, 2^25
+// 236 to 206, 2^26 438 to 419, 2^27 847 to 837, 2^28 1678 to 1691; of 2^19, 2^25 238
+// to 228, 2^26 432 to 431, 2^26.5 566 to 575, 2^27 807 to 817).
 static const RowDesc *row_for_batch(const RowDesc *row, uint64_t n1, uint64_t batch, int cus)
 {
     constexpr uint64_t kMidSamples = 1ull << 26;

@@ -586,7 +586,8 @@ hipError_t launch_segments(const StagesPlan &p, const c32 *in, c32 *out, const c
         return e;
     const uint64_t groups = (batch + segs - 1) / segs;
     hipLaunchKernelGGL((stages_segments_kernel<D, F>), dim3((unsigned)groups),
-                       dim3(p.threads_a), (unsigned)lds, s, in, out, tw, p.a, segs, batch, hop, window);
+                       dim3(p.threads_a), (unsigned)lds, s, in, out, tw, p.a, segs, batch, hop,
+                       window);
     return hipGetLastError();
 }
 
@@ -665,7 +666,8 @@ hipError_t stages_one_pass(const StagesPlan &p, int dir, const void *in, void *o
     static constexpr auto f = {launch_segments<-1, kNarrow>, launch_segments<-1, kMost>,
                                launch_segments<-1, kWide>,   launch_segments<1, kNarrow>,
                                launch_segments<1, kMost>,    launch_segments<1, kWide>};
-    return f.begin()[p.form_a + (dir < 0 ? 0 : 3)](p, (const c32 *)in, (c32 *)out, (const c32 *)tw, batch, hop, window, s);
+    return f.begin()[p.form_a + (dir < 0 ? 0 : 3)](p, (const c32 *)in, (c32 *)out,
+                                                   (const c32 *)tw, batch, hop, window, s);
 }
 
 hipError_t stages_rows(const StagesPlan &p, int dir, const void *y, void *out, const void *tw,
@@ -674,7 +676,8 @@ hipError_t stages_rows(const StagesPlan &p, int dir, const void *y, void *out, c
     static constexpr auto f = {launch_rows<-1, kNarrow>, launch_rows<-1, kMost>,
                                launch_rows<-1, kWide>,   launch_rows<1, kNarrow>,
                                launch_rows<1, kMost>,    launch_rows<1, kWide>};
-    return f.begin()[p.form_b + (dir < 0 ? 0 : 3)](p, (const c32 *)y, (c32 *)out, (const c32 *)tw, batch, s);
+    return f.begin()[p.form_b + (dir < 0 ? 0 : 3)](p, (const c32 *)y, (c32 *)out,
+                                                   (const c32 *)tw, batch, s);
 }
 
 hipError_t stages_two_pass(const StagesPlan &p, int dir, const void *in, void *out, void *y,

@@ -291,14 +291,16 @@ struct ColumnIo {
     // column of slot c, and whether the slot holds one
     __device__ __forceinline__ int column(int c) const
     {
-        const int half = 1 << (lc - 1);
-        return !PairColumns || c < half ? first + c : n2 - (first + c - half);
+        if constexpr (PairColumns)
+            if (const int half = 1 << (lc - 1); c >= half)
+                return n2 - (first + c - half);
+        return first + c;
     }
     __device__ __forceinline__ bool has(int c) const
     {
-        const int half = 1 << (lc - 1), p = first + c - half;
-        if (!PairColumns)
+        if constexpr (!PairColumns)
             return first + c < n2;
+        const int half = 1 << (lc - 1), p = first + c - half;
         return c < half ? 2 * (first + c) <= n2 : p > 0 && 2 * p < n2;
     }
     __device__ __forceinline__ int step() const { return (1 << lc) + 1; }
@@ -378,9 +380,9 @@ struct RowIo {
     }
     __device__ __forceinline__ bool has(int c) const
     {
-        const int half = 1 << (lr - 1), p = first + c - half;
-        if (!Pair)
+        if constexpr (!Pair)
             return first + c < n1;
+        const int half = 1 << (lr - 1), p = first + c - half;
         return c < half ? 2 * (first + c) <= n1 : p > 0 && 2 * p < n1;
     }
     __device__ __forceinline__ int step() const { return 1 << lr; }

@@ -20,10 +20,10 @@
 // across: a segment's bits then do not depend on the copy of an unrolled loop, or
 // on the form of the kernel, that a butterfly falls to)
 #pragma clang fp contract(on)
-#include <algorithm>
-
 #include "runtime.hpp"
 #include "stages_device.hpp"
+
+#include <algorithm>
 
 namespace fftseg {
 namespace {
@@ -337,7 +337,8 @@ hipError_t stages_real_one_pass(const StagesPlan &p, const void *in, void *out, 
     static constexpr auto f = {launch_segments<-1, kNarrow>, launch_segments<-1, kMost>,
                                launch_segments<-1, kWide>,   launch_segments<1, kNarrow>,
                                launch_segments<1, kMost>,    launch_segments<1, kWide>};
-    return f.begin()[p.form_a + (p.real < 0 ? 0 : 3)](p, (const c32 *)in, (c32 *)out, (const c32 *)tw, (const c32 *)hw, batch, s);
+    return f.begin()[p.form_a + (p.real < 0 ? 0 : 3)](p, (const c32 *)in, (c32 *)out,
+                                                      (const c32 *)tw, (const c32 *)hw, batch, s);
 }
 
 hipError_t stages_real_two_pass(const StagesPlan &p, const void *in, void *out, void *y,

@@ -327,9 +327,10 @@ int route_of(uint32_t n, int *grid_mult)
 // own (indexed).  A tuned 1 takes the plan's tiles.  Untuned, 1 up to
 // kIndexedTwoPass segments, one workgroup per tile, in tiles with the tasks'
 // arithmetic (so that a segment's bits do not depend on the list's size), and 0
-// above (lists of seven lengths in equal numbers: 570 segments of
-// 65536 points 390 us by tasks, 309 indexed; 4570 2.30 ms and 2.19; 9140
-// 4.42 and 5.65).
+// above (lists of seven lengths in equal numbers: 599 segments of 65536 points
+// 423 us by tasks, 325 indexed; 2278 1.23 ms and 1.11; 3961 2.02 and 1.89; 6866
+// 3.40 and 3.21; 9081, with 4.4 GiB of Y, 4.43 and 5.52.  The line is at 2 GiB of Y,
+// short of that fall).
 constexpr size_t kIndexedTwoPass = 4096;
 int route_two_pass(uint32_t n, size_t count, int *grid_mult, const ColumnDesc **c,
                    const RowDesc **r)
