@@ -502,7 +502,7 @@ def real(args):
                       "bytes_per_real_sample": round(fwd_bytes / total, 3),
                       "complex_same_samples_ms": round(tc * 1e3, 3),
                       "speedup_vs_complex": round(tc / tf, 2),
-                      "separate_split_n2097152": long_row}), flush=True)
+                      "two_pass_n2097152": long_row}), flush=True)
     return 0
 
 

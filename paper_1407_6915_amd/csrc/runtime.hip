@@ -1191,6 +1191,8 @@ int plan_describe(const Plan *p, std::string &js)
                  p->sp->threads, p->sp->segs_per_wg, p->grid_mult, real_grid(p, p->batch));
         break;
     case Plan::REAL_STAGES: {
+        // ("separate_split" is 1 where the plan takes two passes, the split in one of
+        // them; it once had a pass of its own)
         std::vector<int> r;
         const StagesPlan &g = p->stages;
         lds_radices(g.a, &r);

@@ -12,12 +12,15 @@
 // pass below the copy rate of 5.8 TB/s is the LDS exchange between stages
 // (about 10 % of a pass each) and, above 10000 points or in tiles of more
 // than half a CU's LDS, that little of a tile's loads overlaps another's
-// stages: 5.0 to 5.6 TB/s with two stages, 4.5 to 5.1 with three, 3.5 to 4.1
-// from 10000 points on; two passes move 4.2 to 5.3 with tiles of two
-// workgroups a CU and 2.5 to 3.9 with larger ones (2^26 samples).
-// (products fuse into additions within an expression, as the source has them, and not
+// stages: 4.1 to 5.0 TB/s up to 125 points, 5.3 to 5.7 with two stages, 4.4 to 5.0
+// with three, 3.4 to 4.0 from 10000 points on; two passes move 4.4 to 5.4 with
+// tiles of two workgroups a CU and 2.8 to 4.2 with larger ones (2^26 samples).  The
+// bytes are the compulsory ones: partial lines add 0 to 2 % to a pass (12 % to the
+// writes of 2048-point rows in 8-row tiles).
+//
+// Products fuse into additions within an expression, as the source has them, and not
 // across: a segment's bits then do not depend on the copy of an unrolled loop, or
-// on the form of the kernel, that a butterfly falls to)
+// on the form of the kernel, that a butterfly falls to.
 #pragma clang fp contract(on)
 #include "stages.hpp"
 
